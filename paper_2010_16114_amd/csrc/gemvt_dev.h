@@ -225,23 +225,36 @@ __device__ __forceinline__ void gemvt_sums_blk(const GemvtArgs& a, int bx, int b
     }
 }
 
-// One workgroup of 256 threads of the epilogue, columns 256 bx ..: one thread
-// per column; a 16-lane group covers one change-list block.
-__device__ __forceinline__ void gemvt_epilogue_blk(const GemvtArgs& a, int bx)
+// One workgroup of 256 threads of the epilogue, columns CB bx ..: 256 / CB
+// threads per column, each walking every (256 / CB)-th vector; a 16-lane group
+// covers one change-list block.  What a column writes does not depend on CB:
+// every (column, vector) is one thread's work and the l1 sums run over the 16
+// columns of a block in one tree order.  flag: LDS of CB ints (unused with CB =
+// 256, where one thread sees every vector of its column).
+template <int CB>
+__device__ __forceinline__ void gemvt_epilogue_blk(const GemvtArgs& a, int bx, int* __restrict__ flag)
 {
+    static_assert(CB % kGemvtCols == 0 && 256 % CB == 0, "whole change-list blocks, whole threads per column");
+    constexpr int BG = 256 / CB;  // threads per column
     const int64_t p = a.x.p;
-    const int64_t j = (int64_t)bx * 256 + threadIdx.x;
+    const int col = threadIdx.x % CB, grp = threadIdx.x / CB;
+    const int64_t j = (int64_t)bx * CB + col;
     const bool valid = j < p;
     const bool geno = a.x.xt != XT_F32;
-    double mu = 0.0, sc = 1.0;
+    double mu = 0.0, sc = 1.0, f = 1.0;
     if (valid && geno) {
         if (a.x.center) mu = a.x.center[j];
         if (a.x.scale) sc = a.x.scale[j];
     }
+    if (valid && a.pf) f = a.pf[j];  // penalty factor: 0 leaves the column unpenalised
+    if constexpr (BG > 1) {
+        if (threadIdx.x < CB) flag[threadIdx.x] = 0;
+        __syncthreads();
+    }
     int changed = 0;
     const int lane16 = threadIdx.x & 15;
     const int64_t blk = j / kGemvtCols;
-    for (int b = 0; b < a.nb; ++b) {
+    for (int b = grp; b < a.nb; b += BG) {
         const int bb = a.b0 + b;
         const int64_t at = (int64_t)bb * p + j;
         double l1o = 0.0, l1n = 0.0;
@@ -254,7 +267,6 @@ __device__ __forceinline__ void gemvt_epilogue_blk(const GemvtArgs& a, int bx)
             } else if (a.mode == GT_GRAD) {
                 a.out32[(int64_t)bb * a.ostride + j] = (float)(-g);
             } else {
-                const double f = a.pf ? a.pf[j] : 1.0;  // penalty factor: 0 leaves the column unpenalised
                 const double old = a.beta[at];
                 double nw = old;
                 if (a.active == nullptr || a.active[bb])
@@ -281,16 +293,22 @@ __device__ __forceinline__ void gemvt_epilogue_blk(const GemvtArgs& a, int bx)
         }
     }
     if (a.mode != GT_PROX) return;
-    int f = 0;
+    if constexpr (BG > 1) {
+        if (changed) flag[col] = 1;  // every writer stores 1
+        __syncthreads();
+        if (threadIdx.x >= CB) return;
+        changed = flag[col];
+    }
+    int fl = 0;
     if (valid) {
-        f = a.first_group ? changed : (a.chg_flag[j] | changed);
-        a.chg_flag[j] = f;
+        fl = a.first_group ? changed : (a.chg_flag[j] | changed);
+        a.chg_flag[j] = fl;
     }
     // compact the changed columns of the block in ascending order
-    const uint64_t ball = __ballot(f != 0);
+    const uint64_t ball = __ballot(fl != 0);
     const int gshift = (threadIdx.x & (kWave - 1)) & ~15;
     const uint32_t mask = (uint32_t)((ball >> gshift) & 0xFFFFu);
-    if (f) a.chg_idx[blk * kGemvtCols + __popc(mask & ((1u << lane16) - 1u))] = (int32_t)j;
+    if (fl) a.chg_idx[blk * kGemvtCols + __popc(mask & ((1u << lane16) - 1u))] = (int32_t)j;
     if (lane16 == 0 && (blk * kGemvtCols) < p) a.chg_cnt[blk] = __popc(mask);
 }
 

@@ -164,7 +164,7 @@ __global__ __launch_bounds__(kPT, (persist_waves<XT, NB>())) void fit_persistent
         }
         if (grid_barrier(br, nwg, &s_flag)) return;
         for (int64_t v = blockIdx.x; v < nepi; v += G) {
-            gemvtdev::gemvt_epilogue_blk(g, (int)v);
+            gemvtdev::gemvt_epilogue_blk<256>(g, (int)v, nullptr);
             __syncthreads();
         }
         if (grid_barrier(br, nwg, &s_flag)) return;
