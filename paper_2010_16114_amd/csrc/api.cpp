@@ -104,7 +104,8 @@ struct cox_ctx {
     int32_t *sel_all = nullptr, *nsel_all = nullptr;  // 0 .. p - 1 and p: every column, for dense passes
     int32_t* nonfin = nullptr;   // [max_batch] a dense pass's coefficient vector holds a NaN or infinity
     long long* eta_part = nullptr;  // [ncu][2][Bmax16][256] partial sums of blocks two eta workgroups share
-    long long* xtr_tail = nullptr;  // [3][Bmax16][ncu * 256] X~' R sums of the split last round (shape 15)
+    long long* xtr_tail = nullptr;  // [Bmax16][tail_cols] X~' R sums of the split last round (shape 15)
+    int64_t tail_cols = 0;       // its columns over all shares: up to 6 shares of a full round, 16 of a small one
     int ncu = 0;                 // compute units of the device
     int64_t dstride = 0;
     double *dscale = nullptr, *dmaxp = nullptr;
@@ -825,7 +826,7 @@ cox_status run_gemvt(cox_ctx* c, GemvtArgs g, int B, int rlimbs = 3)
         MfmaArgs m{c->x.X,   c->x.xt, c->n, c->p,      c->x.ldx,     c->limbs, c->rstride,
                    bpad,     rlimbs,  B,    c->qscale, c->part_xtr, 0};
         m.tail = c->xtr_tail;
-        m.tail_cols = (int64_t)c->ncu * 256;
+        m.tail_cols = c->tail_cols;
         m.ncu = c->ncu;
         int& chosen = c->xtr_by_limbs[rlimbs];
         const int forced = forced_variant("COXHIP_MFMA_VARIANT", kMfmaVariants);
@@ -1117,9 +1118,11 @@ cox_status cox_setup(cox_ctx** out, const cox_matrix* X, const double* time, con
             (void)hipGetLastError();
             c->ncu = 0;
         }
-        if (ok && c->ncu > 0)
+        if (ok && c->ncu > 0) {
+            c->tail_cols = std::min((int64_t)6 * c->ncu * 256, 16 * p);
             ok = dalloc(c, &c->eta_part, (size_t)c->ncu * 2 * c->bpad_max * 256) &&
-                 dalloc(c, &c->xtr_tail, (size_t)3 * c->bpad_max * c->ncu * 256);
+                 dalloc(c, &c->xtr_tail, (size_t)c->bpad_max * c->tail_cols);
+        }
     }
     if (ok) {
         c->pinned_bytes = 64 * 1024;

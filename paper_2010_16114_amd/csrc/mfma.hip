@@ -175,19 +175,22 @@ __global__ __launch_bounds__(64 * (CW + LW), (CW + LW) / 4) void mfma_xtr_split_
             }
         }
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+        for (int bq = 0; bq < NG; ++bq) {
+            const int b = bq * 16 + acol;
+            if (b >= a.B) continue;
+            const double qs = a.qscale[b];  // once: the stores below could alias it
 #pragma unroll
-            for (int bq = 0; bq < NG; ++bq)
+            for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const int b = bq * 16 + acol;
                     const int64_t j = jw + mt * 16 + mfma_c_row(lane, v);
-                    if (j < p && b < a.B) {
+                    if (j < p) {
                         int64_t tot = (int64_t)acc[mt][bq][v] + 256 * (int64_t)acc[mt][NG + bq][v];
                         if constexpr (RL == 3) tot += 65536 * (int64_t)acc[mt][2 * NG + bq][v];
-                        a.out[(int64_t)b * p + j] = a.qscale[b] * (double)tot;
+                        a.out[(int64_t)b * p + j] = qs * (double)tot;
                     }
                 }
+        }
     } else {
         // loader: chunk c of a stage's contiguous limb tile goes to LDS slot (c / NCOL, c % NCOL)
         const int lt = threadIdx.x - 64 * CW;
@@ -242,11 +245,11 @@ __global__ __launch_bounds__(64 * (CW + LW), (CW + LW) / 4) void mfma_xtr_split_
 // takes 16 (QC + 1) bytes (16 of padding), so that the 16 lanes of a fragment
 // read (16 consecutive columns, one 16-byte chunk each) hit distinct banks.
 //
-// KSPLIT > 1 splits the last, partly filled round of workgroups: each block of
-// columns from a.nfull on is taken by KSPLIT workgroups, one run of consecutive
+// SPLIT: the last, partly filled round of workgroups is split.  Each block of
+// columns from a.nfull on is taken by a.ksplit workgroups, one run of consecutive
 // stages each, which write their exact integer sums to a.tail for
 // xtr_tail_kernel to add (integer sums: the result equals the unsplit one).
-template <int XT, int NG, int RL, int CW, int LW, int MT, int LDF, bool NTX = false, int QC = 4, int KSPLIT = 1>
+template <int XT, int NG, int RL, int CW, int LW, int MT, int LDF, bool NTX = false, int QC = 4, bool SPLIT = false>
 __global__ __launch_bounds__(64 * (CW + LW), (CW + LW) / 4) void mfma_xtr_lds_kernel(MfmaArgs a)
 {
     static_assert(LDF >= 2, "the loaders' ring needs two slots");
@@ -272,13 +275,13 @@ __global__ __launch_bounds__(64 * (CW + LW), (CW + LW) / 4) void mfma_xtr_lds_ke
     const int64_t nstage = (n + SUBJ - 1) / SUBJ;
     int64_t blk = blockIdx.x, t0 = 0, t1 = nstage;  // block of columns, stages [t0, t1)
     int part = -1;                                  // share of a split block, or -1
-    if constexpr (KSPLIT > 1) {
+    if constexpr (SPLIT) {
         if (blk >= a.nfull) {
             const int64_t v = blk - a.nfull;
-            blk = a.nfull + v / KSPLIT;
-            part = (int)(v % KSPLIT);
-            t0 = nstage * part / KSPLIT;
-            t1 = nstage * (part + 1) / KSPLIT;
+            blk = a.nfull + v / a.ksplit;
+            part = (int)(v % a.ksplit);
+            t0 = nstage * part / a.ksplit;
+            t1 = nstage * (part + 1) / a.ksplit;
         }
     }
     const int64_t nst = t1 - t0;
@@ -394,33 +397,37 @@ __global__ __launch_bounds__(64 * (CW + LW), (CW + LW) / 4) void mfma_xtr_lds_ke
         __syncthreads();
     }
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int bq = 0; bq < NG; ++bq) {
+        const int b = bq * 16 + acol;
+        if (b >= a.B) continue;
+        const double qs = a.qscale[b];  // once: the stores below could alias it
 #pragma unroll
-        for (int bq = 0; bq < NG; ++bq)
+        for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int b = bq * 16 + acol;
                 const int64_t j = jw + mt * 16 + mfma_c_row(lane, v);
-                if (j < p && b < a.B) {
+                if (j < p) {
                     int64_t tot = (int64_t)acc[mt][bq][v] + 256 * (int64_t)acc[mt][NG + bq][v];
                     if constexpr (RL == 3) tot += 65536 * (int64_t)acc[mt][2 * NG + bq][v];
-                    if (KSPLIT > 1 && part >= 0)
+                    if (SPLIT && part >= 0)
                         a.tail[((int64_t)part * a.B + b) * a.tail_cols + (j - a.nfull * WCOLS)] = tot;
                     else
-                        a.out[(int64_t)b * p + j] = a.qscale[b] * (double)tot;
+                        a.out[(int64_t)b * p + j] = qs * (double)tot;
                 }
             }
+    }
 }
 
-// The split blocks' sums: out[b][j0 + jj] = qscale_b (the sum over the ksplit shares).
-__global__ __launch_bounds__(kT) void xtr_tail_kernel(MfmaArgs a, int ksplit, int64_t j0, int64_t ptail)
+// The split blocks' sums: out[b][j0 + jj] = qscale_b (the sum over the shares).
+__global__ __launch_bounds__(kT) void xtr_tail_kernel(MfmaArgs a, int64_t j0, int64_t ptail)
 {
     const int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x;
     if (i >= (int64_t)a.B * ptail) return;
     const int b = (int)(i / ptail);
     const int64_t jj = i - (int64_t)b * ptail;
     long long tot = 0;
-    for (int k = 0; k < ksplit; ++k) tot += a.tail[((int64_t)k * a.B + b) * a.tail_cols + jj];
+#pragma unroll 4
+    for (int k = 0; k < a.ksplit; ++k) tot += a.tail[((int64_t)k * a.B + b) * a.tail_cols + jj];
     a.out[(int64_t)b * a.p + j0 + jj] = a.qscale[b] * (double)tot;
 }
 
@@ -437,6 +444,36 @@ __device__ __forceinline__ void transpose4x4(const uint32_t (&d)[4], uint32_t (&
     o[1] = __builtin_amdgcn_perm(lo23, lo01, 0x07060302u);                 // x01 x11 x21 x31
     o[2] = __builtin_amdgcn_perm(hi23, hi01, 0x05040100u);
     o[3] = __builtin_amdgcn_perm(hi23, hi01, 0x07060302u);
+}
+
+// eta_b(i) += q_b tot(mt, v) for the 16 consecutive subjects i = i0 + 4 v + mt
+// that one lane of a compute wavefront owns in each b.  The values of eta are
+// read before any of them is written: a store could alias the next load, so one
+// by one each subject waits for memory in turn.
+template <class F>
+__device__ __forceinline__ void add_eta(const MfmaEtaArgs& a, int b, int64_t i0, F&& tot)
+{
+    const int64_t n = a.n;
+    double* __restrict__ e = a.eta + (int64_t)b * n;
+    const double q = a.dscale[b];
+#pragma unroll
+    for (int h = 0; h < 4; h += 2) {  // eight values at a time: sixteen would not fit beside the accumulators
+        double old[2][4];
+#pragma unroll
+        for (int v = 0; v < 2; ++v)
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt) {
+                const int64_t i = i0 + 4 * (h + v) + mt;
+                old[v][mt] = i < n ? e[i] : 0.0;
+            }
+#pragma unroll
+        for (int v = 0; v < 2; ++v)
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt) {
+                const int64_t i = i0 + 4 * (h + v) + mt;
+                if (i < n) e[i] = old[v][mt] + q * (double)tot(mt, h + v);
+            }
+    }
 }
 
 // eta update on the matrix cores: eta (n x B) += G[:, U] D, contracting over the
@@ -619,17 +656,10 @@ __global__ __launch_bounds__(256 * NSPLIT, NSPLIT) void mfma_eta_kernel(MfmaEtaA
     for (int j = 0; j < NGH; ++j) {
         if (half * NGH + j >= NG) continue;  // the repeated group of an odd NG
         const int b = bqs[j] * 16 + (lane & 15);
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int64_t i = i0 + 64 * wsub + 4 * mfma_c_row(lane, v) + mt;
-                if (i < n && b < a.B && (a.active == nullptr || a.active[b])) {
-                    const int64_t tot = (int64_t)acc[mt][0][j][v] + 256 * (int64_t)acc[mt][1][j][v] +
-                                        65536 * (int64_t)acc[mt][2][j][v];
-                    a.eta[(int64_t)b * n + i] += a.dscale[b] * (double)tot;
-                }
-            }
+        if (b >= a.B || (a.active != nullptr && !a.active[b])) continue;
+        add_eta(a, b, i0 + 64 * wsub + 4 * mfma_c_row(lane, 0), [&](int mt, int v) {
+            return (int64_t)acc[mt][0][j][v] + 256 * (int64_t)acc[mt][1][j][v] + 65536 * (int64_t)acc[mt][2][j][v];
+        });
     }
 }
 
@@ -861,22 +891,26 @@ __global__ __launch_bounds__(64 * (CW + LW), (CW + LW) / 4) void mfma_eta_split_
         for (int j = 0; j < NGH; ++j) {
             if (half * NGH + j >= NG) continue;  // the repeated group of an odd NG
             const int b = bqs[j] * 16 + (lane & 15);
+            if (b < a.B && (a.active == nullptr || a.active[b])) {
+                auto tot = [&](int mt, int v) {
+                    return (int64_t)acc[mt][0][j][v] + 256 * (int64_t)acc[mt][1][j][v] +
+                           65536 * (int64_t)acc[mt][2][j][v];
+                };
+                const int r0 = 64 * wsub + 4 * mfma_c_row(lane, 0);
+                if (slot < 0) {
+                    add_eta(a, b, blk * SUB + r0, tot);
+                } else {
+                    long long* __restrict__ part = a.part + ((w * 2 + slot) * a.bpad + b) * SUB + r0;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+#pragma unroll
+                        for (int mt = 0; mt < 4; ++mt) part[4 * v + mt] = tot(mt, v);
+                }
+            }
 #pragma unroll
             for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int r = 64 * wsub + 4 * mfma_c_row(lane, v) + mt;
-                    const int64_t i = blk * SUB + r;
-                    if (i < n && b < a.B && (a.active == nullptr || a.active[b])) {
-                        const int64_t tot = (int64_t)acc[mt][0][j][v] + 256 * (int64_t)acc[mt][1][j][v] +
-                                            65536 * (int64_t)acc[mt][2][j][v];
-                        if (slot < 0)
-                            a.eta[(int64_t)b * n + i] += a.dscale[b] * (double)tot;
-                        else
-                            a.part[((w * 2 + slot) * a.bpad + b) * SUB + r] = tot;
-                    }
-                    acc[mt][0][j][v] = acc[mt][1][j][v] = acc[mt][2][j][v] = 0;
-                }
+                for (int v = 0; v < 4; ++v) acc[mt][0][j][v] = acc[mt][1][j][v] = acc[mt][2][j][v] = 0;
         }
     };
     // a stage's matrix-core work: every limb and b group of the D tile in buffer cb
@@ -1135,14 +1169,20 @@ hipError_t launch_eta_shape(const MfmaEtaArgs& a, hipStream_t s)
 }
 
 // SK: one workgroup per compute unit (a.sk_grid of them) sharing the blocks evenly,
-// then the shared blocks' partial sums; otherwise one workgroup per block.
+// then the shared blocks' partial sums; otherwise one workgroup per block.  With
+// fewer blocks than compute units the shares are runs of a block's stages, at
+// most kEtaShares to a block (eta_fixup_kernel reads them one after another):
+// 12 blocks of 11 stages take 1 stage each over 132 workgroups, 20 us and 8 us
+// for the sums at 64 vectors where one workgroup per block took 30-35 us.
+constexpr int64_t kEtaShares = 16;
 template <int XT, int NG, int CW, int LW, int LDF, int NB = 2, bool NTX = false, bool SK = false>
 hipError_t launch_eta_split(const MfmaEtaArgs& a, hipStream_t s)
 {
     if (a.ldx >= (int64_t(1) << 32)) return hipErrorInvalidValue;  // its loaders index X in 32 bits
     const int64_t nblk = (a.n + 255) / 256;
     int64_t grid = nblk;
-    if (SK && a.part && a.sk_grid > 0 && a.sk_grid < nblk) grid = a.sk_grid;
+    if (SK && a.part && a.sk_grid > 0)
+        grid = min((int64_t)a.sk_grid, nblk * min(kEtaShares, (a.p + 63) / 64));
     hipLaunchKernelGGL((mfma_eta_split_kernel<XT, NG, CW, LW, LDF, NB, NTX>), dim3((unsigned)grid),
                        dim3(64 * (CW + LW)), 0, s, a);
     const int64_t left = nblk % grid;  // blocks after the last whole round
@@ -1199,13 +1239,38 @@ hipError_t launch_lds(const MfmaArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
+// Shares each block of the last round's `ntail` blocks is split into, of nstage
+// stages each, on `slots` resident workgroups: the split with the least
+//     rounds of shares x (stages of a share + the fill and flush of a workgroup)
+//     + the shares' partial sums, written and read once (a stage moves 32 KB of X
+//     per compute unit in about 1.5 us; the sums move at about 4 TB/s).
+// A part-filled round costs a whole one, so 196 blocks of 1,563 stages on 256
+// slots take 4 rounds of 313 stages in fifths (2.32 ms at 200,000 x 50,000 x 64;
+// 2.64 ms in thirds, 2.46 ms unsplit), and 3 blocks of 24 stages take 2 stages in
+// twelfths (15 us; 21 us in thirds).
+int pick_ksplit(int64_t ntail, int64_t nstage, int64_t slots, int64_t ptail, int B, int64_t room)
+{
+    constexpr int64_t kFill = 6;
+    int best = 1;
+    double cost = 1e300;
+    for (int64_t k = 1; k <= 16 && k <= nstage && k * ptail <= room; ++k) {
+        const double c = (double)((ntail * k + slots - 1) / slots * ((nstage + k - 1) / k + kFill)) +
+                         (k > 1 ? 16.0 * (double)(k * ptail) * B / 6e6 : 0.0);
+        if (c < cost) {
+            cost = c;
+            best = (int)k;
+        }
+    }
+    return best;
+}
+
 // Shape 15's launch: the blocks of columns that fill whole rounds of resident
-// workgroups run unsplit, and the rest (the last round's) are split KSPLIT ways.
-template <int XT, int NG, int RL, int CW, int LW, int MT, int LDF, bool NTX, int QC, int KSPLIT>
+// workgroups run unsplit, and the rest (the last round's) are split.
+template <int XT, int NG, int RL, int CW, int LW, int MT, int LDF, bool NTX, int QC>
 hipError_t launch_lds_tail(const MfmaArgs& a, hipStream_t s)
 {
     constexpr int WCOLS = 16 * MT * CW;
-    const void* fn = reinterpret_cast<const void*>(&mfma_xtr_lds_kernel<XT, NG, RL, CW, LW, MT, LDF, NTX, QC, KSPLIT>);
+    const void* fn = reinterpret_cast<const void*>(&mfma_xtr_lds_kernel<XT, NG, RL, CW, LW, MT, LDF, NTX, QC, true>);
     if (!a.tail || a.ncu < 1) return hipErrorInvalidValue;
     int per_cu = 0;
     const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, 64 * (CW + LW), 0);
@@ -1217,11 +1282,13 @@ hipError_t launch_lds_tail(const MfmaArgs& a, hipStream_t s)
     b.nfull = nblk - ntail;
     const int64_t j0 = b.nfull * WCOLS, ptail = a.p - j0;
     if (ntail > 0 && ptail > a.tail_cols) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((mfma_xtr_lds_kernel<XT, NG, RL, CW, LW, MT, LDF, NTX, QC, KSPLIT>),
-                       dim3((unsigned)(b.nfull + KSPLIT * ntail)), dim3(64 * (CW + LW)), 0, s, b);
+    b.ksplit = pick_ksplit(ntail, (a.n + 16 * QC - 1) / (16 * QC), slots, ptail, a.B, a.tail_cols);
+    b.tail_cols = ptail;  // the shares' sums stand close together
+    hipLaunchKernelGGL((mfma_xtr_lds_kernel<XT, NG, RL, CW, LW, MT, LDF, NTX, QC, true>),
+                       dim3((unsigned)(b.nfull + b.ksplit * ntail)), dim3(64 * (CW + LW)), 0, s, b);
     if (ntail > 0)
-        hipLaunchKernelGGL(xtr_tail_kernel, dim3((unsigned)((a.B * ptail + kT - 1) / kT)), dim3(kT), 0, s, b, KSPLIT,
-                           j0, ptail);
+        hipLaunchKernelGGL(xtr_tail_kernel, dim3((unsigned)((a.B * ptail + kT - 1) / kT)), dim3(kT), 0, s, b, j0,
+                           ptail);
     return hipGetLastError();
 }
 
@@ -1239,7 +1306,7 @@ hipError_t launch_ng(const MfmaArgs& a, hipStream_t s)
     case 12: return launch_lds<XT, NG, RL, 8, 4, 2, 3>(a, s);
     case 13: return launch_lds<XT, NG, RL, 4, 4, 4, 2, false, 8>(a, s);
     case 14: return launch_lds<XT, NG, RL, 4, 4, 4, 2, true, 8>(a, s);
-    case 15: return launch_lds_tail<XT, NG, RL, 4, 4, 4, 2, true, 8, 3>(a, s);
+    case 15: return launch_lds_tail<XT, NG, RL, 4, 4, 4, 2, true, 8>(a, s);
     case 1: return launch_split<XT, NG, RL, 7, 1, 3, 1, 4>(a, s);
     case 2: return launch_split<XT, NG, RL, 6, 2, 3, 1, 6>(a, s);
     case 3: return launch_split<XT, NG, RL, 6, 2, 3, 1, 4>(a, s);

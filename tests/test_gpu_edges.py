@@ -39,3 +39,25 @@ def test_epilogue_column_blocks(p):
     assert (b7.cpu().numpy() != beta[:7]).any()
     _bits(b8[:7].cpu().numpy(), b7.cpu().numpy())
     _bits(o8[:7], o7)
+
+
+@pytest.mark.parametrize("n,p,B", [(130, 40, 9), (700, 65, 64), (3001, 257, 20)])
+def test_small_matrix_core_splits(n, p, B, monkeypatch):
+    """With fewer blocks than compute units the eta update shares a block's
+    stages among workgroups and the X~' R pass splits its subjects: one stage per
+    share, more shares than stages, a ragged last stage.  The sums are exact
+    integers, so both agree bit for bit with the unsplit shapes."""
+    d = coxsim.genotype_problem(n, p, 4, 0.3, 700 + n, days=True)
+    cox, M = device_problem(d, "fp8", ldx=(n + 15) // 16 * 16, max_batch=B)
+    lams = coxsim.lambda_grid(oracle.lambda_max(M, d.time, d.event), B, 0.01)
+    sigma = 1.0 / (2.0 * (np.sqrt(n) + np.sqrt(p)) ** 2)
+    out = []
+    for xv, ev in ((14, 2), (15, 8), (15, 11)):
+        monkeypatch.setenv("COXHIP_MFMA_VARIANT", str(xv))
+        monkeypatch.setenv("COXHIP_ETA_VARIANT", str(ev))
+        beta, _, obj, _ = cox.fit_path(lams, max_iter=10, tol=0.0, step=sigma)
+        out.append((beta.cpu().numpy(), obj))
+    assert (out[0][0] != 0).any()
+    for beta, obj in out[1:]:
+        _bits(beta, out[0][0])
+        _bits(obj, out[0][1])
