@@ -15,7 +15,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libcoxhip.so")
-SOURCES = ["api.cpp", "risk.hip", "gemv.hip", "gemvt.hip", "misc.hip", "mfma.hip", "covar.hip", "refit.hip", "nmf.hip",
+SOURCES = ["api.cpp", "risk.hip", "riskb.hip", "gemv.hip", "gemvt.hip", "misc.hip", "mfma.hip", "covar.hip", "refit.hip", "nmf.hip",
            "persist.hip"]
 ARCH = os.environ.get("COXHIP_ARCH", "gfx950")
 FLAGS = [

@@ -46,6 +46,7 @@ constexpr int kMaxBatch = 64;
 constexpr int kGroup = 8;  // coefficient vectors per VALU pass over X
 constexpr int kFreeCovMaxIter = 100000;  // steps of the unpenalised covariate fit inside cox_lambda_max
 constexpr double kFreeCovGtol = 1e-10;   // its stop: max |g_k| below this fraction of its value at zero
+constexpr int kKeys = kKeySets * kKeyRow;  // one set of the batched form's keys
 constexpr double kPersistWaitLimit = 60.0;  // seconds one grid barrier of the persistent fit may wait
 
 int64_t round_up(int64_t a, int64_t m) { return (a + m - 1) / m * m; }
@@ -97,8 +98,11 @@ struct cox_ctx {
     // batched matrix-core pass (one-byte allele counts, B > kGroup)
     int8_t* limbs = nullptr;     // [3][Bmax16][rstride]
     int bpad_max = 0;
-    double *qscale = nullptr, *rmaxp = nullptr;
-    long long* rsump = nullptr;
+    double* qscale = nullptr;
+    // its state of the subjects stands in rows [n][Bmax16] (riskb.hip)
+    int32_t* egrank = nullptr;   // [n + 1] event groups that end before a sorted position
+    double *rb_tot = nullptr, *rb_wg = nullptr;  // tile and workgroup totals of the risk-set passes
+    unsigned long long* keys = nullptr;          // [3][kKeys]: max eta, max |r|, sums of R; then a counter
     int* geno_bad = nullptr;
     int8_t* dlimbs = nullptr;    // [3][Bmax16][dstride] eta-update limbs
     int32_t *sel_all = nullptr, *nsel_all = nullptr;  // 0 .. p - 1 and p: every column, for dense passes
@@ -131,6 +135,7 @@ struct cox_ctx {
     // produced it, for a resumed call (warm_start = 2); any other call that uses the
     // workspace clears fit_valid
     bool fit_valid = false;
+    bool fit_rows = false;       // on the matrix cores, its state in rows
     int fit_B = 0, fit_max_iter = 0, fit_eta_mode = 0, fit_rlimbs = 3;
     int64_t fit_q = 0;
     double fit_step = 0.0;
@@ -439,7 +444,10 @@ int64_t ptot(const cox_ctx* c) { return c->p + c->q; }
 // Penalty factors of X's columns as the kernels take them (null: all 1).
 const double* pf_x(const cox_ctx* c) { return c->pf_x_custom ? c->pf : nullptr; }
 
-CovArgs cov_args(cox_ctx* c) { return CovArgs{c->Z, c->n, c->ldz, (int)c->q, c->nrb, c->cov_part}; }
+CovArgs cov_args(cox_ctx* c, bool rows = false)
+{
+    return CovArgs{c->Z, c->n, c->ldz, (int)c->q, rows ? cov_row_blocks_rows(c->n) : c->nrb, c->cov_part};
+}
 
 // Caller's [B][ptot] FP32 coefficients -> the FP64 iterate of X's columns (and the covariates').
 cox_status load_beta(cox_ctx* c, const float* beta, int B)
@@ -460,12 +468,15 @@ cox_status store_beta(cox_ctx* c, float* beta, int B)
     return COX_OK;
 }
 
-// eta_b += Z coef_b (no covariates: nothing)
-cox_status cov_eta(cox_ctx* c, const double* coef, int B, const int32_t* active)
+// eta_b += Z coef_b (no covariates: nothing); rows: eta stands in rows
+cox_status cov_eta(cox_ctx* c, const double* coef, int B, const int32_t* active, bool rows)
 {
     if (!c->q) return COX_OK;
     tmark(c, COX_PHASE_COV);
-    HIPCHK(launch_cov_eta(cov_args(c), coef, B, c->eta, active, c->stream), "Z beta");
+    if (rows)
+        HIPCHK(launch_cov_eta_rows(cov_args(c), coef, B, (int)round_up(B, 16), c->eta, active, c->stream), "Z beta");
+    else
+        HIPCHK(launch_cov_eta(cov_args(c), coef, B, c->eta, active, c->stream), "Z beta");
     tmark(c, COX_PHASE_COV);
     return COX_OK;
 }
@@ -475,9 +486,12 @@ cox_status cov_eta(cox_ctx* c, const double* coef, int B, const int32_t* active)
 cox_status cov_grad(cox_ctx* c, const RiskArgs& ra, int B, const int32_t* active, const CovStep& st)
 {
     if (!c->q) return COX_OK;
-    const CovArgs ca = cov_args(c);
+    const CovArgs ca = cov_args(c, ra.bpad > 0);
     tmark(c, COX_PHASE_COV);
-    HIPCHK(launch_cov_xtr(ca, ra.r64 ? nullptr : ra.r32, c->rstride, ra.r64, B, active, c->stream), "Z' r");
+    if (ra.bpad)
+        HIPCHK(launch_cov_xtr_rows(ca, ra.r64, B, ra.bpad, active, c->stream), "Z' r");
+    else
+        HIPCHK(launch_cov_xtr(ca, ra.r64 ? nullptr : ra.r32, c->rstride, ra.r64, B, active, c->stream), "Z' r");
     HIPCHK(launch_cov_epilogue(ca, st, B, c->stream), "Z' r epilogue");
     tmark(c, COX_PHASE_COV);
     return COX_OK;
@@ -504,11 +518,12 @@ bool use_mfma(cox_ctx* c, int B);
 
 // eta[b] = X~ coef[b] (no centring) for b < B; coef is b-major [B][p].  More
 // than 8 vectors over one-byte allele counts go through the matrix cores (three
-// passes over X for any B, against one FP64 pass per 8 vectors).
-cox_status dense_eta(cox_ctx* c, const double* coef, int B, const double* shift)
+// passes over X for any B, against one FP64 pass per 8 vectors) and leave eta in
+// rows (rows = use_mfma(c, B), from the caller).
+cox_status dense_eta(cox_ctx* c, const double* coef, int B, const double* shift, bool rows)
 {
     tmark(c, COX_PHASE_ETA);
-    if (!shift && c->sel_all && use_mfma(c, B)) {
+    if (rows) {
         const cox_status st = dense_eta_mfma(c, coef, B);
         tmark(c, COX_PHASE_ETA);
         return st;
@@ -712,7 +727,7 @@ cox_status dense_eta_mfma(cox_ctx* c, const double* coef, int B)
     const int bpad = (int)round_up(B, 16);
     HIPCHK(launch_fill_i32(c->nonfin, 0, B, c->stream), "clear flags");
     HIPCHK(launch_nonfinite(coef, c->p, B, c->nonfin, c->stream), "coefficient check");
-    HIPCHK(launch_fill_f64(c->eta, 0.0, (int64_t)B * c->n, c->stream), "clear eta");
+    HIPCHK(launch_fill_f64(c->eta, 0.0, bpad * c->n, c->stream), "clear eta");
     MfmaEtaArgs m = mfma_eta_args(c, c->sel_all, c->nsel_all, B, nullptr);
     for (int k = 0; k < 3; ++k) {
         const double* src = k == 0 ? coef : c->dcoef;
@@ -725,7 +740,7 @@ cox_status dense_eta_mfma(cox_ctx* c, const double* coef, int B)
         tmark(c, COX_PHASE_ETA_KERNEL);
         if (k < 2) HIPCHK(launch_coef_remainder(src, c->dcoef, c->p, B, c->dscale, c->stream), "coefficient remainder");
     }
-    HIPCHK(launch_poison_eta(c->eta, c->n, B, c->nonfin, c->stream), "non-finite coefficients");
+    HIPCHK(launch_poison_rows(c->eta, c->n, B, bpad, c->nonfin, c->stream), "non-finite coefficients");
     return COX_OK;
 }
 
@@ -751,7 +766,8 @@ bool use_mfma(cox_ctx* c, int B)
     return c->geno_state == 0;
 }
 
-RiskArgs risk_args(cox_ctx* c, int B)
+// rows: the batched form, its state in rows (use_mfma(c, B), or false)
+RiskArgs risk_args(cox_ctx* c, int B, bool rows)
 {
     RiskArgs a{};
     a.n = c->n;
@@ -782,9 +798,19 @@ RiskArgs risk_args(cox_ctx* c, int B)
     a.sumr = c->sumr;
     a.rstride = c->rstride;
     a.use_ctl = 0;
-    if (use_mfma(c, B)) {  // the matrix-core pass quantises the FP64 residual itself
+    if (rows) {  // the matrix-core pass quantises the FP64 residual itself
         a.r32 = nullptr;
         a.r64 = c->r64;
+        a.bpad = (int)round_up(B, 16);
+        a.egrank = c->egrank;
+        a.egcnt = c->egcnt;
+        a.stot = c->rb_tot;
+        a.qtot = c->rb_tot + 16 * riskb_tiles();
+        a.Lpart = c->rb_wg;
+        a.wgS = c->rb_wg + 64 * riskb_wgs();
+        a.wgQ = c->rb_wg + 128 * riskb_wgs();
+        a.mkey = c->keys;
+        a.rkey = c->keys + kKeys;
     }
     return a;
 }
@@ -815,13 +841,14 @@ GemvtArgs gemvt_args(cox_ctx* c, int mode)
 
 // X~' r for B vectors: the matrix-core pass (residual in rlimbs int8 limbs)
 // when X holds allele counts and B > kGroup, else the vector pass.
-cox_status run_gemvt(cox_ctx* c, GemvtArgs g, int B, int rlimbs = 3)
+cox_status run_gemvt(cox_ctx* c, GemvtArgs g, int B, bool rows, int rlimbs = 3)
 {
-    if (use_mfma(c, B)) {
+    if (rows) {
         tmark(c, COX_PHASE_XTR);
         const int bpad = (int)round_up(B, 16);
-        HIPCHK(launch_quantize(c->r64, c->n, B, c->rmaxp, c->rsump, c->limbs, c->rstride, bpad, rlimbs, c->qscale,
-                               c->sumr, c->stream),
+        HIPCHK(launch_quantize_rows(c->r64, c->n, B, c->keys + kKeys, c->limbs, c->rstride, bpad, rlimbs, c->qscale,
+                                    c->keys + 2 * kKeys, reinterpret_cast<unsigned*>(c->keys + 3 * kKeys), c->sumr,
+                                    c->stream),
                "quantise r");
         MfmaArgs m{c->x.X,   c->x.xt, c->n, c->p,      c->x.ldx,     c->limbs, c->rstride,
                    bpad,     rlimbs,  B,    c->qscale, c->part_xtr, 0};
@@ -948,7 +975,7 @@ cox_status fit_free_covariates(cox_ctx* c, const RiskArgs& ra)
     for (int it = 0; it < kFreeCovMaxIter && !done; ++it) {
         HIPCHK(launch_risk(ra, c->stream), "risk-set sums");
         STCHK(cov_grad(c, ra, 1, nullptr, st));  // g at beta_it, then beta_{it+1}
-        STCHK(cov_eta(c, c->dZ, 1, nullptr));
+        STCHK(cov_eta(c, c->dZ, 1, nullptr, false));
         if (it % 4 == 0) {
             STCHK(d2h(c, gz.data(), c->gZ, sizeof(double) * q));
             double gm = 0.0;
@@ -1078,8 +1105,15 @@ cox_status cox_setup(cox_ctx** out, const cox_matrix* X, const double* time, con
         }
     }
     c->n_egroups = (int64_t)egc.size();
+    std::vector<int32_t> egr;  // event groups that end before position k
+    if (X->xtype != COX_X_F32 && c->x.vec16 && max_batch > kGroup) {
+        egr.resize(n + 1);
+        egr[0] = 0;
+        for (int64_t k = 0; k < n; ++k) egr[k + 1] = egr[k] + (egi[k] >= 0);
+    }
 
-    const int64_t Bn = (int64_t)max_batch * n, Bp = (int64_t)max_batch * p;
+    const bool mfma_able = X->xtype != COX_X_F32 && c->x.vec16 && max_batch > kGroup;
+    const int64_t Bn = (mfma_able ? round_up(max_batch, 16) : max_batch) * n, Bp = (int64_t)max_batch * p;
     bool ok = dalloc(c, &c->perm, n) && dalloc(c, &c->gstart, n) && dalloc(c, &c->gend, n) && dalloc(c, &c->ev, n) &&
               dalloc(c, &c->egidx, n) && dalloc(c, &c->egcnt, std::max<size_t>(1, egc.size())) &&
               dalloc(c, &c->eta, Bn) && dalloc(c, &c->w, Bn) && dalloc(c, &c->S, Bn) && dalloc(c, &c->T, Bn) &&
@@ -1098,19 +1132,18 @@ cox_status cox_setup(cox_ctx** out, const cox_matrix* X, const double* time, con
               dalloc(c, &c->qtot, (size_t)max_batch * c->ntile) && dalloc(c, &c->Lpart, (size_t)max_batch * c->ntile) &&
               dalloc(c, &c->rpart, (size_t)max_batch * c->ntile) &&
               dalloc(c, &c->part_xtr, (size_t)c->nsplit * Bp) &&
-              dalloc(c, &c->cov_part, (size_t)max_batch * cov_row_blocks(n) * kMaxCov) &&
+              dalloc(c, &c->cov_part, (size_t)max_batch * std::max(cov_row_blocks(n), cov_row_blocks_rows(n)) * kMaxCov) &&
               dalloc(c, &c->betaZ, (size_t)max_batch * kMaxCov) && dalloc(c, &c->dZ, (size_t)max_batch * kMaxCov) &&
               dalloc(c, &c->gZ, (size_t)max_batch * kMaxCov) && dalloc(c, &c->l1c_old, max_batch) &&
               dalloc(c, &c->l1c_new, max_batch) && dalloc(c, &c->pf, p + kMaxCov) &&
               dalloc(c, &c->bar_words, persist_barrier_words()) && dalloc(c, &c->col_count, 1) &&
               dalloc(c, &c->red_part, kRedParts);
-    const bool mfma_able = X->xtype != COX_X_F32 && c->x.vec16 && max_batch > kGroup;
     if (ok && mfma_able) {
         c->bpad_max = (int)round_up(max_batch, 16);
-        const int nt = mfma_ntile(n);
         c->dstride = round_up(p, 64);
         ok = dalloc(c, &c->limbs, (size_t)3 * c->bpad_max * c->rstride) && dalloc(c, &c->qscale, max_batch) &&
-             dalloc(c, &c->rmaxp, (size_t)max_batch * nt) && dalloc(c, &c->rsump, (size_t)max_batch * nt) &&
+             dalloc(c, &c->egrank, n + 1) && dalloc(c, &c->rb_tot, (size_t)32 * riskb_tiles()) &&
+             dalloc(c, &c->rb_wg, (size_t)192 * riskb_wgs()) && dalloc(c, &c->keys, 3 * kKeys + 1) &&
              dalloc(c, &c->geno_bad, 1) && dalloc(c, &c->dlimbs, (size_t)3 * c->bpad_max * c->dstride) &&
              dalloc(c, &c->dscale, max_batch) && dalloc(c, &c->dmaxp, (size_t)max_batch * ((c->dstride + 4095) / 4096)) &&
              dalloc(c, &c->sel_all, p) && dalloc(c, &c->nsel_all, 1) && dalloc(c, &c->nonfin, max_batch);
@@ -1147,6 +1180,7 @@ cox_status cox_setup(cox_ctx** out, const cox_matrix* X, const double* time, con
     up(c->ev, evs.data(), n);
     up(c->egidx, egi.data(), sizeof(int32_t) * n);
     if (!egc.empty()) up(c->egcnt, egc.data(), sizeof(int32_t) * egc.size());
+    if (c->egrank) up(c->egrank, egr.data(), sizeof(int32_t) * (n + 1));
     auto chk = [&](hipError_t e) {
         if (st == COX_OK && e != hipSuccess) st = COX_ERR_DEVICE;
     };
@@ -1159,6 +1193,7 @@ cox_status cox_setup(cox_ctx** out, const cox_matrix* X, const double* time, con
     if (c->limbs)
         chk(launch_fill_f64(reinterpret_cast<double*>(c->limbs), 0.0, (int64_t)3 * c->bpad_max * c->rstride / 8,
                             c->stream));
+    if (c->keys) chk(launch_fill_f64(reinterpret_cast<double*>(c->keys), 0.0, 3 * kKeys + 1, c->stream));
     if (c->sel_all) {
         chk(launch_iota_i32(c->sel_all, p, c->stream));
         chk(launch_fill_i32(c->nsel_all, (int32_t)p, 1, c->stream));
@@ -1193,16 +1228,18 @@ cox_status cox_loss_grad(cox_ctx* c, const float* beta, int32_t B, double* loss,
     STCHK(check_batch(c, B));
     STCHK(load_beta(c, beta, B));
     HIPCHK(launch_scale_coef(c->beta64, geno_scale(c), c->coef, c->p, B, c->stream), "coefficients");
-    STCHK(dense_eta(c, c->coef, B, nullptr));
-    STCHK(cov_eta(c, c->betaZ, B, nullptr));
-    RiskArgs ra = risk_args(c, B);
+    const bool rows = use_mfma(c, B);
+    STCHK(dense_eta(c, c->coef, B, nullptr, rows));
+    STCHK(cov_eta(c, c->betaZ, B, nullptr, rows));
+    RiskArgs ra = risk_args(c, B, rows);
     if (!grad) ra.r32 = nullptr;
+    if (!grad && rows) ra.r64 = nullptr;  // no residual
     HIPCHK(launch_risk(ra, c->stream), "risk-set sums");
     if (grad) {
         GemvtArgs g = gemvt_args(c, GT_GRAD);
         g.out32 = grad;
         g.ostride = ptot(c);
-        STCHK(run_gemvt(c, g, B));
+        STCHK(run_gemvt(c, g, B, rows));
         CovStep st{};
         st.mode = GT_GRAD;
         st.out32 = grad + c->p;
@@ -1232,16 +1269,17 @@ cox_status cox_prox_step(cox_ctx* c, float* beta, int32_t B, const double* lambd
     STCHK(h2d(c, c->lam, lambdas, sizeof(double) * B));
     STCHK(load_beta(c, beta, B));
     HIPCHK(launch_scale_coef(c->beta64, geno_scale(c), c->coef, c->p, B, c->stream), "coefficients");
-    STCHK(dense_eta(c, c->coef, B, nullptr));
-    STCHK(cov_eta(c, c->betaZ, B, nullptr));
-    const RiskArgs ra = risk_args(c, B);
+    const bool rows = use_mfma(c, B);
+    STCHK(dense_eta(c, c->coef, B, nullptr, rows));
+    STCHK(cov_eta(c, c->betaZ, B, nullptr, rows));
+    const RiskArgs ra = risk_args(c, B, rows);
     HIPCHK(launch_risk(ra, c->stream), "risk-set sums");
     GemvtArgs g = gemvt_args(c, GT_PROX);
     g.beta = c->beta64;
     g.lam = c->lam;
     g.step = step;
     g.active = nullptr;
-    STCHK(run_gemvt(c, g, B));
+    STCHK(run_gemvt(c, g, B, rows));
     STCHK(cov_grad(c, ra, B, nullptr, cov_prox(c, step, nullptr)));
     STCHK(store_beta(c, beta, B));
     if (obj_before) {
@@ -1288,7 +1326,7 @@ cox_status cox_lambda_max(cox_ctx* c, double* lambda_max)
     bool free_cov = false;
     for (int64_t k = 0; k < q; ++k) free_cov = free_cov || c->pf_host[p + k] == 0.0;
     HIPCHK(launch_fill_f64(c->eta, 0.0, c->n, c->stream), "zero eta");
-    RiskArgs ra = risk_args(c, 1);
+    RiskArgs ra = risk_args(c, 1, false);
     ra.r64 = c->r64;
     cox_status conv = COX_OK;
     if (free_cov) {
@@ -1299,7 +1337,7 @@ cox_status cox_lambda_max(cox_ctx* c, double* lambda_max)
     }
     GemvtArgs g = gemvt_args(c, GT_RAW);
     g.out64 = c->g64;
-    STCHK(run_gemvt(c, g, 1));
+    STCHK(run_gemvt(c, g, 1, false));
     std::vector<double> gh(p + q);
     if (q) {
         CovStep st{};
@@ -1342,13 +1380,13 @@ cox_status cox_opnorm2(cox_ctx* c, double tol, int32_t maxiter, uint64_t seed, d
         if (centred)
             HIPCHK(launch_center_shift(c->x.center, scale, c->beta64, c->p, c->red_part, c->scal + 0, c->stream),
                    "shift");
-        STCHK(dense_eta(c, c->coef, 1, centred ? c->scal + 0 : nullptr));
-        STCHK(cov_eta(c, c->betaZ, 1, nullptr));
+        STCHK(dense_eta(c, c->coef, 1, centred ? c->scal + 0 : nullptr, false));
+        STCHK(cov_eta(c, c->betaZ, 1, nullptr, false));
         HIPCHK(launch_dot(c->eta, c->eta, c->n, c->red_part, c->scal + 1, c->stream), "norm of X v");
         HIPCHK(launch_to_r32(c->eta, nullptr, c->r32, c->sumr, c->n, c->red_part, c->stream), "u to FP32");
         GemvtArgs g = gemvt_args(c, GT_RAW);
         g.out64 = c->g64;
-        STCHK(run_gemvt(c, g, 1));
+        STCHK(run_gemvt(c, g, 1, false));
         HIPCHK(launch_dot(c->g64, c->g64, c->p, c->red_part, c->scal + 2, c->stream), "norm of X' u");
         if (q) {
             RiskArgs ru{};
@@ -1416,7 +1454,9 @@ cox_status cox_fit_path(cox_ctx* c, const double* lambdas, int32_t B, const cox_
         step = 1.0 / (2.0 * s2);
     }
     STCHK(h2d(c, c->lam, lambdas, sizeof(double) * B));
-    const int64_t Bp = (int64_t)B * c->p, Bn = (int64_t)B * c->n;
+    // a resumed fit goes on in the form it ran in: that is how its state stands
+    const bool mfma = resume ? c->fit_rows : use_mfma(c, B);
+    const int64_t Bp = (int64_t)B * c->p, Bn = (mfma ? round_up(B, 16) : B) * c->n;
     const int q = (int)c->q;
     if (resume) {
         // the iterate, eta and the stopping-rule state stay as the last fit left them; the
@@ -1425,8 +1465,8 @@ cox_status cox_fit_path(cox_ctx* c, const double* lambdas, int32_t B, const cox_
     } else if (o.warm_start) {
         STCHK(load_beta(c, beta, B));
         HIPCHK(launch_scale_coef(c->beta64, geno_scale(c), c->coef, c->p, B, c->stream), "coefficients");
-        STCHK(dense_eta(c, c->coef, B, nullptr));
-        STCHK(cov_eta(c, c->betaZ, B, nullptr));
+        STCHK(dense_eta(c, c->coef, B, nullptr, mfma));
+        STCHK(cov_eta(c, c->betaZ, B, nullptr, mfma));
         HIPCHK(launch_l1_blocks(c->beta64, pf_x(c), c->p, B, c->nblk, c->l1new, c->stream), "l1 blocks");
         if (q) HIPCHK(launch_cov_l1(c->betaZ, c->pf + c->p, q, B, c->l1c_new, c->stream), "covariate l1");
     } else {
@@ -1447,8 +1487,7 @@ cox_status cox_fit_path(cox_ctx* c, const double* lambdas, int32_t B, const cox_
         HIPCHK(launch_fill_f64(c->hist, 0.0, (int64_t)B * kMaxHist, c->stream), "reset");
     }
 
-    const bool mfma = use_mfma(c, B);
-    RiskArgs ra = risk_args(c, B);
+    RiskArgs ra = risk_args(c, B, mfma);
     ra.part = (o.eta_mode == 0 && !mfma) ? c->part_upd : nullptr;
     ra.use_ctl = 1;
     ra.ctl = FitCtl{c->lam, c->l1new, c->nblk, c->hist, c->kit, c->active, c->iters, c->status, c->fobj,
@@ -1513,10 +1552,10 @@ cox_status cox_fit_path(cox_ctx* c, const double* lambdas, int32_t B, const cox_
                 tmark(c, COX_PHASE_ETA);
             } else {
                 HIPCHK(launch_scale_coef(c->beta64, geno_scale(c), c->coef, c->p, B, c->stream), "coefficients");
-                STCHK(dense_eta(c, c->coef, B, nullptr));
+                STCHK(dense_eta(c, c->coef, B, nullptr, mfma));
             }
             // the covariates' share: a fresh eta needs all of Z beta_Z, an updated one the change
-            STCHK(cov_eta(c, o.eta_mode == 1 ? c->betaZ : c->dZ, B, o.eta_mode == 1 ? nullptr : c->active));
+            STCHK(cov_eta(c, o.eta_mode == 1 ? c->betaZ : c->dZ, B, o.eta_mode == 1 ? nullptr : c->active, mfma));
         }
         if (!first_resumed) {
             tmark(c, COX_PHASE_RISK);
@@ -1524,7 +1563,7 @@ cox_status cox_fit_path(cox_ctx* c, const double* lambdas, int32_t B, const cox_
             tmark(c, COX_PHASE_RISK);
         }
         if (it < o.max_iter) {
-            STCHK(run_gemvt(c, g, B, rlimbs));
+            STCHK(run_gemvt(c, g, B, mfma, rlimbs));
             STCHK(cov_grad(c, ra, B, c->active, cst));
             if (o.eta_mode == 0) {
                 HIPCHK(launch_compact(c->chg_cnt, c->chg_idx, c->nblk, c->sel, c->nsel, c->stream), "compact");
@@ -1555,6 +1594,7 @@ cox_status cox_fit_path(cox_ctx* c, const double* lambdas, int32_t B, const cox_
     if (!o.persistent) {
         c->fit_valid = true;
         c->fit_B = B;
+        c->fit_rows = mfma;
         c->fit_lams.assign(lambdas, lambdas + B);
         c->fit_step = step;
         c->fit_eta_mode = o.eta_mode;
@@ -1704,7 +1744,7 @@ cox_status cox_refit(cox_ctx* c, const int64_t* cols, int32_t m, const cox_refit
     if (q) HIPCHK(launch_gather_z(c->Z, c->ldz, n, q, c->perm, D + (size_t)m * ldd, ldd, c->stream), "gather covariates");
     STCHK(h2d(c, b, coef, sizeof(double) * M));
 
-    RiskArgs ra = risk_args(c, 1);
+    RiskArgs ra = risk_args(c, 1, false);
     ra.r32 = nullptr;
     ra.r64 = c->r64;
     auto eval = [&](const double* bb, double* Lout) -> cox_status {
@@ -1834,7 +1874,7 @@ cox_status cox_nll_forward(cox_ctx* c, const void* eta, int32_t eta_f64, int32_t
     c->fit_valid = false;
     if (!eta || !loss || (eta_f64 != 0 && eta_f64 != 1)) return fail(c, COX_ERR_INVALID_ARG, "bad nll_forward arguments");
     STCHK(check_batch(c, B));
-    RiskArgs ra = risk_args(c, B);
+    RiskArgs ra = risk_args(c, B, false);
     ra.eta_in = eta;
     ra.eta_in_f32 = !eta_f64;
     ra.r32 = nullptr;

@@ -66,14 +66,68 @@ __global__ __launch_bounds__(kT) void cov_xtr_part_kernel(CovArgs c, const float
     }
 }
 
-// One wavefront per b, lane k = covariate k.
-__global__ __launch_bounds__(kWave) void cov_epilogue_kernel(CovArgs c, CovStep st)
+// Z' r for residuals in rows [i][bpad]: a workgroup takes `rows` rows, bpad
+// adjacent lanes the vectors of one row (so a row of r is one coalesced read and
+// an entry of Z one address for all of them), kChunkR covariates at a time in
+// registers; the kTR / bpad rows in flight are added through LDS in order.
+// Bound by the read of r: with 16 vectors and 11 covariates at n = 100,003 the
+// form above (one row block of 8,192 per workgroup and vector, 208 workgroups)
+// took 100 us, this one 48.
+constexpr int kChunkR = 16;
+constexpr int kTR = 1024;  // threads per workgroup
+__global__ __launch_bounds__(kTR) void cov_xtr_rows_kernel(CovArgs c, const double* __restrict__ r, int B, int bpad,
+                                                          int64_t rows, const int32_t* __restrict__ active)
 {
-    const int b = blockIdx.x, k = threadIdx.x;
+    __shared__ double sh[kTR];
+    const int per = kTR / bpad, s = threadIdx.x / bpad, b = threadIdx.x % bpad;
+    const bool on = s < per && b < B && (active == nullptr || active[b]);
+    const int64_t i0 = (int64_t)blockIdx.x * rows, i1 = min(c.n, i0 + rows);
+    for (int k0 = 0; k0 < c.q; k0 += kChunkR) {
+        double acc[kChunkR];
+#pragma unroll
+        for (int e = 0; e < kChunkR; ++e) acc[e] = 0.0;
+        if (on) {
+#pragma unroll 2
+            for (int64_t i = i0 + s; i < i1; i += per) {
+                const double v = r[i * bpad + b];
+#pragma unroll
+                for (int e = 0; e < kChunkR; ++e)
+                    if (k0 + e < c.q) acc[e] += (double)c.Z[(int64_t)(k0 + e) * c.ldz + i] * v;
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < kChunkR; ++e) {
+            if (k0 + e >= c.q) break;
+            __syncthreads();
+            sh[threadIdx.x] = acc[e];
+            __syncthreads();
+            if (s == 0 && on) {
+                double v = acc[e];
+                for (int u = 1; u < per; ++u) v += sh[u * bpad + b];
+                c.part[((int64_t)b * c.nrb + blockIdx.x) * c.q + k0 + e] = v;
+            }
+        }
+    }
+}
+
+// One workgroup per b, lane k = covariate k; each wavefront adds a quarter of the
+// row blocks.
+__global__ __launch_bounds__(kT) void cov_epilogue_kernel(CovArgs c, CovStep st)
+{
+    __shared__ double sh[kT / kWave][kWave];
+    const int b = blockIdx.x, k = threadIdx.x % kWave, wid = threadIdx.x / kWave;
     const bool valid = k < c.q;
     double g = 0.0;
-    if (valid)
-        for (int rb = 0; rb < c.nrb; ++rb) g += c.part[((int64_t)b * c.nrb + rb) * c.q + k];
+    if (valid) {
+        const int per = (c.nrb + kT / kWave - 1) / (kT / kWave);
+        const int r1 = min(c.nrb, (wid + 1) * per);
+#pragma unroll 8
+        for (int rb = wid * per; rb < r1; ++rb) g += c.part[((int64_t)b * c.nrb + rb) * c.q + k];
+    }
+    sh[wid][k] = g;
+    __syncthreads();
+    if (wid > 0) return;
+    for (int w = 1; w < kT / kWave; ++w) g += sh[w][k];
     if (st.out64 && valid) st.out64[(int64_t)b * st.ostride + k] = g;
     if (st.mode == GT_GRAD) {
         if (valid) st.out32[(int64_t)b * st.ostride + k] = (float)(-g);
@@ -113,6 +167,26 @@ __global__ __launch_bounds__(kT) void cov_eta_kernel(CovArgs c, const double* __
         double s = 0.0;
         for (int k = 0; k < c.q; ++k) s += (double)c.Z[(int64_t)k * c.ldz + i] * cb[k];
         eta[(int64_t)b * c.n + i] += s;
+    }
+}
+
+// eta[i][b] += sum_k Z(i, k) coef_b(k) for eta in rows of bpad
+__global__ __launch_bounds__(kT) void cov_eta_rows_kernel(CovArgs c, const double* __restrict__ coef, int B, int bpad,
+                                                          double* __restrict__ eta, const int32_t* __restrict__ active)
+{
+    __shared__ double cb[kMaxCov][64];
+    for (int t = threadIdx.x; t < c.q * bpad; t += kT) {
+        const int k = t / bpad, b = t % bpad;
+        cb[k][b] = b < B ? coef[(int64_t)b * c.q + k] : 0.0;
+    }
+    __syncthreads();
+    const int per = kT / bpad, s = threadIdx.x / bpad, b = threadIdx.x % bpad;
+    if (s >= per || b >= B || (active && !active[b])) return;
+    for (int64_t i = (int64_t)blockIdx.x * per + s; i < c.n; i += (int64_t)gridDim.x * per) {
+        double v = 0.0;
+#pragma unroll 4
+        for (int k = 0; k < c.q; ++k) v += (double)c.Z[(int64_t)k * c.ldz + i] * cb[k][b];
+        eta[i * bpad + b] += v;
     }
 }
 
@@ -173,6 +247,29 @@ hipError_t launch_cov_xtr(const CovArgs& c, const float* r32, int64_t rstride, c
     return hipGetLastError();
 }
 
+// row blocks of Z' r over rows of vectors: about 256, at least 64 rows each
+static int64_t rows_per_block(int64_t n) { return max((int64_t)64, (n + 255) / 256); }
+int cov_row_blocks_rows(int64_t n) { return (int)((n + rows_per_block(n) - 1) / rows_per_block(n)); }
+
+hipError_t launch_cov_xtr_rows(const CovArgs& c, const double* r64, int B, int bpad, const int32_t* active,
+                               hipStream_t s)
+{
+    if (c.q < 1 || c.q > kMaxCov || c.nrb != cov_row_blocks_rows(c.n) || bpad < B || bpad > 64 || bpad % 16)
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(cov_xtr_rows_kernel, dim3(c.nrb), dim3(kTR), 0, s, c, r64, B, bpad, rows_per_block(c.n), active);
+    return hipGetLastError();
+}
+
+hipError_t launch_cov_eta_rows(const CovArgs& c, const double* coef, int B, int bpad, double* eta,
+                               const int32_t* active, hipStream_t s)
+{
+    if (c.q < 1 || c.q > kMaxCov || bpad < B || bpad > 64 || bpad % 16) return hipErrorInvalidValue;
+    const int64_t per = kT / bpad;
+    const unsigned gx = (unsigned)min((int64_t)2048, (c.n + per - 1) / per);
+    hipLaunchKernelGGL(cov_eta_rows_kernel, dim3(gx), dim3(kT), 0, s, c, coef, B, bpad, eta, active);
+    return hipGetLastError();
+}
+
 hipError_t launch_cov_epilogue(const CovArgs& c, const CovStep& st, int B, hipStream_t s)
 {
     if (c.q < 1 || c.q > kMaxCov) return hipErrorInvalidValue;
@@ -180,7 +277,7 @@ hipError_t launch_cov_epilogue(const CovArgs& c, const CovStep& st, int B, hipSt
     if (st.out64 && st.ostride < c.q) return hipErrorInvalidValue;
     if (st.mode == GT_PROX && (!st.beta || !st.dbeta || !st.pf || !st.lam || !st.l1old || !st.l1new))
         return hipErrorInvalidValue;
-    hipLaunchKernelGGL(cov_epilogue_kernel, dim3(B), dim3(kWave), 0, s, c, st);
+    hipLaunchKernelGGL(cov_epilogue_kernel, dim3(B), dim3(kT), 0, s, c, st);
     return hipGetLastError();
 }
 

@@ -91,7 +91,18 @@ struct RiskArgs {
     double* sumr;          // [B] sum of the stored residual
     int use_ctl;           // 1 inside cox_fit_path
     FitCtl ctl;
+    // The batched form (riskb.hip), used when bpad > 0: eta, w and r64 in rows
+    // [i or k][bpad], S one row per event group, stot and qtot [riskb_tiles()][16],
+    // Lpart, wgS and wgQ [riskb_wgs()][bpad]; r64 null: no residual.
+    int bpad;              // B rounded up to 16, or 0
+    const int32_t* egrank; // [n + 1] event groups that end before sorted position k
+    const int32_t* egcnt;  // [event groups] events of each
+    double* wgS;
+    double* wgQ;
+    unsigned long long* mkey;  // [kKeySets][kKeyRow] keys of max eta; all 0 between steps
+    unsigned long long* rkey;  // the same of max |r|, left by the last step with a residual
 };
+constexpr int kKeySets = 8, kKeyRow = 64;  // copies of the batched form's keys; vectors in each
 
 constexpr int kMaxTiles = 4096;
 constexpr int kFinElems = 512;   // eta elements per workgroup of the eta pass
@@ -160,6 +171,11 @@ hipError_t launch_fit_persistent(const PersistArgs& a, unsigned long long* words
 
 // Launchers (return hipError_t of the launch).
 hipError_t launch_risk(const RiskArgs& a, hipStream_t s);
+hipError_t launch_risk_rows(RiskArgs a, hipStream_t s);  // the batched form (a.bpad > 0)
+int64_t riskb_tiles();  // tiles of the batched form at 16 vectors, at most
+int riskb_wgs();        // its workgroups, at most
+// eta[i * bpad + b] = NaN for i < n, for each b < B with flag[b] set
+hipError_t launch_poison_rows(double* eta, int64_t n, int B, int bpad, const int32_t* flag, hipStream_t s);
 hipError_t launch_gemvt(const GemvtArgs& a, hipStream_t s);       // sums, then epilogue
 hipError_t launch_gemvt_sums(const GemvtArgs& a, hipStream_t s);  // the row-split column sums alone
 // the epilogue alone, on column sums already in a.part (nb may exceed 8)
@@ -217,8 +233,6 @@ hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t m, hipStream_t s);
 hipError_t launch_iota_i32(int32_t* p, int64_t m, hipStream_t s);
 // flag[b] = 1 if coef[b*p + j] is not finite for some j < p (b < B; flags cleared beforehand)
 hipError_t launch_nonfinite(const double* coef, int64_t p, int B, int32_t* flag, hipStream_t s);
-// eta[b*n + i] = NaN for i < n, for each b < B with flag[b] set
-hipError_t launch_poison_eta(double* eta, int64_t n, int B, const int32_t* flag, hipStream_t s);
 // dst[b*p + j] = src[b*p + j] - dscale[b] * llrint(src[b*p + j] / dscale[b]) for b < B, j < p
 // (src == dst allowed): what the eta update's D quantisation leaves of each entry
 hipError_t launch_coef_remainder(const double* src, double* dst, int64_t p, int B, const double* dscale,
@@ -229,7 +243,7 @@ struct CovArgs {
     const float* Z;        // column-major n x q, column k at Z + k * ldz
     int64_t n, ldz;
     int q;                 // 1 .. kMaxCov
-    int nrb;               // cov_row_blocks(n)
+    int nrb;               // row blocks: cov_row_blocks(n), or cov_row_blocks_rows(n) for residuals in rows
     double* part;          // [B][nrb][q] partial sums of Z' r
 };
 
@@ -253,6 +267,12 @@ int cov_row_blocks(int64_t n);
 // partial sums of Z' r for b < B; the residual is r32 ([B][rstride]) or r64 ([B][n])
 hipError_t launch_cov_xtr(const CovArgs& c, const float* r32, int64_t rstride, const double* r64, int B,
                           const int32_t* active, hipStream_t s);
+// the same for residuals and linear predictors in rows [i][bpad]
+int cov_row_blocks_rows(int64_t n);
+hipError_t launch_cov_xtr_rows(const CovArgs& c, const double* r64, int B, int bpad, const int32_t* active,
+                               hipStream_t s);
+hipError_t launch_cov_eta_rows(const CovArgs& c, const double* coef, int B, int bpad, double* eta,
+                               const int32_t* active, hipStream_t s);
 hipError_t launch_cov_epilogue(const CovArgs& c, const CovStep& st, int B, hipStream_t s);
 // eta_b += Z coef_b for b < B (coef [B][q]) unless active[b] == 0
 hipError_t launch_cov_eta(const CovArgs& c, const double* coef, int B, double* eta, const int32_t* active,

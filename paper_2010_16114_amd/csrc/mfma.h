@@ -54,7 +54,7 @@ struct MfmaEtaArgs {
     int64_t dstride;        // positions the buffer holds: a multiple of 64, >= p
     int bpad, B;
     const double* dscale;   // [B]
-    double* eta;            // [B][n] FP64, updated in place
+    double* eta;            // [n][bpad] FP64, updated in place
     const int32_t* active;  // [B] or null
     int variant;            // pipeline shape.  One kernel, 8 wavefronts that load both operands,
                             // 2 stages of 64 columns ahead: 0 = D tile in 8-byte pieces when
@@ -67,19 +67,24 @@ struct MfmaEtaArgs {
                             // with one workgroup per compute unit sharing the blocks evenly
                             // (sk_grid, part): 8 = 6; 9 = 2; 10 = 3 with streaming loads; 11 = 4
                             // with streaming loads; 12 = 5 with streaming loads
-    long long* part;        // [sk_grid][2][bpad][256] partial sums of shared blocks (variants 8..12), or null
+    long long* part;        // [sk_grid][2][256][bpad] partial sums of shared blocks (variants 8..12), or null
     int sk_grid;            // workgroups of variants 8..12: the compute units (0: one per block)
 };
 
-int mfma_ntile(int64_t n);
 // D_b(u) = dcoef[b][sel[u]] -> dlimbs, dscale (per-b step max|D_b| / 2^22)
 hipError_t launch_quantize_d(const double* dcoef, int64_t p, const int32_t* sel, const int32_t* nsel, int B,
                              double* dmaxp, int8_t* dlimbs, int64_t dstride, int bpad, double* dscale,
                              hipStream_t s);
 hipError_t launch_mfma_eta(const MfmaEtaArgs& a, hipStream_t s);
-// r64 [B][n] -> limbs, qscale [B], sumr [B] = q_b * sum_i R_bi
-hipError_t launch_quantize(const double* r64, int64_t n, int B, double* rmaxp, long long* rsump, int8_t* limbs,
-                           int64_t lstride, int bpad, int nlimb, double* qscale, double* sumr, hipStream_t s);
+// r64 [n][bpad] with the keys of max |r| (riskb.hip) -> limbs, qscale [B], sumr [B] = q_b * sum_i R_bi.  Quantised
+// to nlimb int8 limbs per vector (3: |R| <= 2^22; 2: |R| <= 2^14, the top limb within int8 either way).  Limb layout:
+// 16-subject chunks, [i / 16][limb * bpad + b][i % 16], so that a stage's tile (all nlimb * bpad limb columns of its
+// subjects) is one contiguous block.  Rows n .. round_up(n, 256) - 1 are written as zeros: the X~' R kernel reads
+// whole 64- or 128-subject stages, and the layout changes with bpad, so stale limbs from an earlier batch size must
+// not survive there.  rsum (laid out as the keys) and done: all zero between launches.
+hipError_t launch_quantize_rows(const double* r64, int64_t n, int B, const unsigned long long* rkey, int8_t* limbs,
+                                int64_t lstride, int bpad, int nlimb, double* qscale, unsigned long long* rsum,
+                                unsigned* done, double* sumr, hipStream_t s);
 hipError_t launch_mfma_xtr(const MfmaArgs& a, hipStream_t s);
 hipError_t launch_geno_check(const void* X, int xt, int64_t n, int64_t p, int64_t ldx, int* bad, hipStream_t s);
 

@@ -38,7 +38,6 @@ typedef int v4i __attribute__((ext_vector_type(4)));
 constexpr int kT = 256;
 constexpr int kLimbs = 3;
 constexpr int kQBits = 22;       // |R| <= 2^22 keeps the top limb within int8
-constexpr int kQBits2 = 14;      // the same for two limbs (the residual's faster, coarser form)
 
 // Allele-count bytes -> int8 counts.  FP8 E4M3 codes of 0, 1, 2 are 0x00, 0x38,
 // 0x40, whose top three bits are the count itself (000, 001, 010); other codes
@@ -449,12 +448,13 @@ __device__ __forceinline__ void transpose4x4(const uint32_t (&d)[4], uint32_t (&
 // eta_b(i) += q_b tot(mt, v) for the 16 consecutive subjects i = i0 + 4 v + mt
 // that one lane of a compute wavefront owns in each b.  The values of eta are
 // read before any of them is written: a store could alias the next load, so one
-// by one each subject waits for memory in turn.
+// by one each subject waits for memory in turn.  16 adjacent lanes hold 16
+// adjacent vectors of a row.
 template <class F>
 __device__ __forceinline__ void add_eta(const MfmaEtaArgs& a, int b, int64_t i0, F&& tot)
 {
-    const int64_t n = a.n;
-    double* __restrict__ e = a.eta + (int64_t)b * n;
+    const int64_t n = a.n, bpad = a.bpad;
+    double* __restrict__ e = a.eta + b;
     const double q = a.dscale[b];
 #pragma unroll
     for (int h = 0; h < 4; h += 2) {  // eight values at a time: sixteen would not fit beside the accumulators
@@ -464,14 +464,14 @@ __device__ __forceinline__ void add_eta(const MfmaEtaArgs& a, int b, int64_t i0,
 #pragma unroll
             for (int mt = 0; mt < 4; ++mt) {
                 const int64_t i = i0 + 4 * (h + v) + mt;
-                old[v][mt] = i < n ? e[i] : 0.0;
+                old[v][mt] = i < n ? e[i * bpad] : 0.0;
             }
 #pragma unroll
         for (int v = 0; v < 2; ++v)
 #pragma unroll
             for (int mt = 0; mt < 4; ++mt) {
                 const int64_t i = i0 + 4 * (h + v) + mt;
-                if (i < n) e[i] = old[v][mt] + q * (double)tot(mt, h + v);
+                if (i < n) e[i * bpad] = old[v][mt] + q * (double)tot(mt, h + v);
             }
     }
 }
@@ -900,11 +900,11 @@ __global__ __launch_bounds__(64 * (CW + LW), (CW + LW) / 4) void mfma_eta_split_
                 if (slot < 0) {
                     add_eta(a, b, blk * SUB + r0, tot);
                 } else {
-                    long long* __restrict__ part = a.part + ((w * 2 + slot) * a.bpad + b) * SUB + r0;
+                    long long* __restrict__ part = a.part + ((w * 2 + slot) * SUB + r0) * a.bpad + b;
 #pragma unroll
                     for (int v = 0; v < 4; ++v)
 #pragma unroll
-                        for (int mt = 0; mt < 4; ++mt) part[4 * v + mt] = tot(mt, v);
+                        for (int mt = 0; mt < 4; ++mt) part[(4 * v + mt) * a.bpad] = tot(mt, v);
                 }
             }
 #pragma unroll
@@ -971,14 +971,13 @@ __global__ __launch_bounds__(64 * (CW + LW), (CW + LW) / 4) void mfma_eta_split_
 }
 
 // The left-over blocks of mfma_eta_split_kernel (those after the last round in
-// which every one of its `shares` workgroups had a whole block), one workgroup
-// per block and vector b (blockIdx.y), one thread per subject: eta += q_b *
-// (the sum of the partial sums of the shares that cover the block, in share
+// which every one of its `shares` workgroups had a whole block), bpad workgroups
+// (blockIdx.y) per block, one thread per subject and vector: eta += q_b * (the sum of the partial sums of the shares that cover the block, in share
 // order; a share covers at most two of them, its first in slot 0, its second
 // in slot 1).
 __global__ __launch_bounds__(kT) void eta_fixup_kernel(MfmaEtaArgs a, int shares)
 {
-    static_assert(kT == 256, "one thread per subject of a block");
+    static_assert(kT == 256, "bpad workgroups of 256 threads cover a block's 256 x bpad sums");
     const int nsel = *a.nsel;
     if (nsel == 0) return;
     constexpr int SUB = 256;
@@ -996,16 +995,16 @@ __global__ __launch_bounds__(kT) void eta_fixup_kernel(MfmaEtaArgs a, int shares
     };
     const int64_t wa = share_of(tb * nchunk), wb = share_of((tb + 1) * nchunk - 1);
     const int64_t blk = R * G + tb;
-    const int b = blockIdx.y, r = threadIdx.x;
+    const int e = blockIdx.y * kT + threadIdx.x, r = e / a.bpad, b = e % a.bpad;
     const int64_t i = blk * SUB + r;
-    if (i < n && (a.active == nullptr || a.active[b])) {
+    if (i < n && b < a.B && (a.active == nullptr || a.active[b])) {
         int64_t tot = 0;
         for (int64_t w = wa; w <= wb; ++w) {
             const int64_t first = (w * tbase + min(w, trem)) / nchunk;  // the first left-over block of w
             const int slot = first == tb ? 0 : 1;
-            tot += a.part[((w * 2 + slot) * a.bpad + b) * SUB + r];
+            tot += a.part[((w * 2 + slot) * SUB + r) * a.bpad + b];
         }
-        a.eta[(int64_t)b * n + i] += a.dscale[b] * (double)tot;
+        a.eta[i * a.bpad + b] += a.dscale[b] * (double)tot;
     }
 }
 
@@ -1058,76 +1057,6 @@ __global__ __launch_bounds__(kT) void dquant_kernel(const double* __restrict__ d
         dst[16 * bpad] = (int8_t)d1;
         dst[32 * bpad] = (int8_t)d2;
     }
-}
-
-// Largest |r| of each vector over a tile of 4096 subjects.
-__global__ __launch_bounds__(kT) void rmax_kernel(const double* __restrict__ r, int64_t n, double* __restrict__ part,
-                                                  int ntile)
-{
-    __shared__ double sh[kT / 64];
-    const int b = blockIdx.y;
-    double m = 0.0;
-    for (int64_t i = (int64_t)blockIdx.x * 4096 + threadIdx.x; i < min(n, (int64_t)(blockIdx.x + 1) * 4096);
-         i += kT)
-        m = fmax(m, fabs(r[(int64_t)b * n + i]));
-    m = wave_max(m);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
-    __syncthreads();
-    if (threadIdx.x == 0) part[(int64_t)b * ntile + blockIdx.x] = fmax(fmax(sh[0], sh[1]), fmax(sh[2], sh[3]));
-}
-
-// Quantise r to nlimb int8 limbs per vector (3: |R| <= 2^22; 2: |R| <= 2^14,
-// the top limb within int8 either way); exact partial sums of R.  Limb
-// layout: 16-subject chunks, [i / 16][limb * bpad + b][i % 16], so that a
-// stage's tile (all nlimb * bpad limb columns of KC subjects) is one
-// contiguous block.  Rows n .. round_up(n, 256) - 1 are written as zeros: the X~' R
-// kernel reads whole 64- or 128-subject stages, and the layout changes with
-// bpad, so stale limbs from an earlier batch size must not survive there.
-__global__ __launch_bounds__(kT) void quantize_kernel(const double* __restrict__ r, int64_t n,
-                                                      const double* __restrict__ rmaxp, int ntile,
-                                                      int8_t* __restrict__ limbs, int bpad, int nlimb,
-                                                      double* __restrict__ qscale, long long* __restrict__ rsump)
-{
-    __shared__ long long sh[kT / 64];
-    const int b = blockIdx.y;
-    double mx = 0.0;
-    for (int t = 0; t < ntile; ++t) mx = fmax(mx, rmaxp[(int64_t)b * ntile + t]);
-    const int bits = nlimb == 2 ? kQBits2 : kQBits;
-    const double q = mx > 0.0 ? mx / (double)(1 << bits) : 1.0;
-    if (blockIdx.x == 0 && threadIdx.x == 0) qscale[b] = q;
-    long long sum = 0;
-    const int64_t npad = (n + 255) / 256 * 256;
-    for (int64_t i = (int64_t)blockIdx.x * 4096 + threadIdx.x; i < min(npad, (int64_t)(blockIdx.x + 1) * 4096);
-         i += kT) {
-        const int R = i < n ? (int)llrint(r[(int64_t)b * n + i] / q) : 0;
-        const int d0 = ((R + 128) & 255) - 128;
-        const int R1 = (R - d0) >> 8;
-        int8_t* dst = limbs + ((i >> 4) * (nlimb * bpad) + b) * 16 + (i & 15);
-        dst[0] = (int8_t)d0;
-        if (nlimb == 2) {
-            dst[16 * bpad] = (int8_t)R1;  // |R1| <= 64 when |R| <= 2^14
-        } else {
-            const int d1 = ((R1 + 128) & 255) - 128;
-            dst[16 * bpad] = (int8_t)d1;
-            dst[32 * bpad] = (int8_t)((R1 - d1) >> 8);
-        }
-        sum += R;
-    }
-    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
-    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = sum;
-    __syncthreads();
-    if (threadIdx.x == 0) rsump[(int64_t)b * ntile + blockIdx.x] = sh[0] + sh[1] + sh[2] + sh[3];
-}
-
-// sumr_b = q_b * sum_i R_bi (the sum of the quantised residual, exact).
-__global__ void rsum_kernel(const long long* __restrict__ rsump, int ntile, const double* __restrict__ qscale,
-                            double* __restrict__ sumr, int B)
-{
-    const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b >= B) return;
-    long long s = 0;
-    for (int t = 0; t < ntile; ++t) s += rsump[(int64_t)b * ntile + t];
-    sumr[b] = qscale[b] * (double)s;
 }
 
 // bad[0] |= 1 if any byte of the n x p matrix is not the code of 0, 1 or 2
@@ -1186,7 +1115,8 @@ hipError_t launch_eta_split(const MfmaEtaArgs& a, hipStream_t s)
     hipLaunchKernelGGL((mfma_eta_split_kernel<XT, NG, CW, LW, LDF, NB, NTX>), dim3((unsigned)grid),
                        dim3(64 * (CW + LW)), 0, s, a);
     const int64_t left = nblk % grid;  // blocks after the last whole round
-    if (left > 0) hipLaunchKernelGGL(eta_fixup_kernel, dim3((unsigned)left, (unsigned)a.B), dim3(kT), 0, s, a, (int)grid);
+    if (left > 0) hipLaunchKernelGGL(eta_fixup_kernel, dim3((unsigned)left, (unsigned)a.bpad), dim3(kT), 0, s, a,
+                                     (int)grid);
     return hipGetLastError();
 }
 
@@ -1333,21 +1263,6 @@ hipError_t launch_xt(const MfmaArgs& a, hipStream_t s)
 }
 
 }  // namespace
-
-int mfma_ntile(int64_t n) { return (int)((n + 4095) / 4096); }
-
-hipError_t launch_quantize(const double* r64, int64_t n, int B, double* rmaxp, long long* rsump, int8_t* limbs,
-                           int64_t lstride, int bpad, int nlimb, double* qscale, double* sumr, hipStream_t s)
-{
-    if (lstride % 256 || lstride < n || bpad < B || bpad % 16 || (nlimb != 2 && nlimb != 3))
-        return hipErrorInvalidValue;
-    const int nt = mfma_ntile(n);
-    hipLaunchKernelGGL(rmax_kernel, dim3(nt, B), dim3(kT), 0, s, r64, n, rmaxp, nt);
-    hipLaunchKernelGGL(quantize_kernel, dim3(nt, B), dim3(kT), 0, s, r64, n, rmaxp, nt, limbs, bpad, nlimb, qscale,
-                       rsump);
-    hipLaunchKernelGGL(rsum_kernel, dim3(1), dim3(64), 0, s, rsump, nt, qscale, sumr, B);
-    return hipGetLastError();
-}
 
 hipError_t launch_quantize_d(const double* dcoef, int64_t p, const int32_t* sel, const int32_t* nsel, int B,
                              double* dmaxp, int8_t* dlimbs, int64_t dstride, int bpad, double* dscale,

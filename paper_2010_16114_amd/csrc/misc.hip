@@ -211,15 +211,6 @@ __global__ void nonfinite_kernel(const double* __restrict__ coef, int64_t p, int
     if (bad) flag[b] = 1;
 }
 
-// eta[b][i] = NaN for every i < n of each b whose flag is set
-__global__ void poison_eta_kernel(double* __restrict__ eta, int64_t n, const int32_t* __restrict__ flag)
-{
-    const int b = blockIdx.y;
-    if (!flag[b]) return;
-    for (int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x; i < n; i += (int64_t)gridDim.x * kT)
-        eta[(int64_t)b * n + i] = __builtin_nan("");
-}
-
 // dst[b][j] = src[b][j] - q_b R, R = llrint(src[b][j] / q_b): the integer the
 // eta update's quantiser takes for that entry at the same scale q_b.  One fma,
 // so the remainder carries at most one rounding of 2^-53 q_b.
@@ -329,13 +320,6 @@ hipError_t launch_nonfinite(const double* coef, int64_t p, int B, int32_t* flag,
     if (p < 1 || B < 1) return hipErrorInvalidValue;
     const unsigned gx = (unsigned)min((int64_t)256, (p + kT - 1) / kT);
     hipLaunchKernelGGL(nonfinite_kernel, dim3(gx, (unsigned)B), dim3(kT), 0, s, coef, p, flag);
-    return hipGetLastError();
-}
-hipError_t launch_poison_eta(double* eta, int64_t n, int B, const int32_t* flag, hipStream_t s)
-{
-    if (n < 1 || B < 1) return hipErrorInvalidValue;
-    const unsigned gx = (unsigned)min((int64_t)256, (n + kT - 1) / kT);
-    hipLaunchKernelGGL(poison_eta_kernel, dim3(gx, (unsigned)B), dim3(kT), 0, s, eta, n, flag);
     return hipGetLastError();
 }
 hipError_t launch_coef_remainder(const double* src, double* dst, int64_t p, int B, const double* dscale,

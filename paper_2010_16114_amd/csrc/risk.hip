@@ -43,6 +43,7 @@ __global__ __launch_bounds__(kT) void risk_finish_kernel(RiskArgs a)
 
 hipError_t launch_risk(const RiskArgs& a, hipStream_t s)
 {
+    if (a.bpad) return launch_risk_rows(a, s);
     if (a.ntile > kMaxTiles || a.ntile < 1 || a.nfin < 1) return hipErrorInvalidValue;
     hipLaunchKernelGGL(risk_eta_kernel, dim3(a.nfin, a.B), dim3(kT), 0, s, a);
     hipLaunchKernelGGL(risk_scan_w_kernel, dim3(a.ntile, a.B), dim3(kT), 0, s, a);

@@ -257,22 +257,10 @@ __device__ __forceinline__ void risk_resid_blk(const RiskArgs& a, int bx, int by
     if (threadIdx.x == 0) a.rpart[(int64_t)b * a.ntile + bx] = sr;
 }
 
-__device__ __forceinline__ void risk_finish_blk(const RiskArgs& a, int bx, double* sh)
+// The objective of b's step and its stopping rule, one workgroup (every thread
+// holds L).
+__device__ __forceinline__ void stop_rule(const RiskArgs& a, int b, double L, double* sh)
 {
-    const int b = bx;
-    if (skip_b(a, b)) return;
-    double L = 0.0, sr = 0.0;
-    for (int q = threadIdx.x; q < a.ntile; q += kT) {
-        L += a.Lpart[(int64_t)b * a.ntile + q];
-        sr += a.rpart[(int64_t)b * a.ntile + q];
-    }
-    L = block_sum(L, sh);
-    sr = block_sum(sr, sh);
-    if (threadIdx.x == 0) {
-        a.L[b] = L;
-        a.sumr[b] = sr;
-    }
-    if (!a.use_ctl) return;
     const FitCtl& c = a.ctl;
     double l1 = 0.0;
     for (int q = threadIdx.x; q < c.nblk; q += kT) l1 += c.l1[(int64_t)b * c.nblk + q];
@@ -300,6 +288,24 @@ __device__ __forceinline__ void risk_finish_blk(const RiskArgs& a, int bx, doubl
             c.kit[b] = k + 1;
         }
     }
+}
+
+__device__ __forceinline__ void risk_finish_blk(const RiskArgs& a, int bx, double* sh)
+{
+    const int b = bx;
+    if (skip_b(a, b)) return;
+    double L = 0.0, sr = 0.0;
+    for (int q = threadIdx.x; q < a.ntile; q += kT) {
+        L += a.Lpart[(int64_t)b * a.ntile + q];
+        sr += a.rpart[(int64_t)b * a.ntile + q];
+    }
+    L = block_sum(L, sh);
+    sr = block_sum(sr, sh);
+    if (threadIdx.x == 0) {
+        a.L[b] = L;
+        a.sumr[b] = sr;
+    }
+    if (a.use_ctl) stop_rule(a, b, L, sh);
 }
 
 }  // namespace riskdev

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 if not torch.cuda.is_available():
     pytest.skip("no GPU", allow_module_level=True)
-
+import paper_2010_16114_amd as P  # noqa: E402
 
 
 def _bits(a, b):
@@ -61,3 +61,46 @@ def test_small_matrix_core_splits(n, p, B, monkeypatch):
     for beta, obj in out[1:]:
         _bits(beta, out[0][0])
         _bits(obj, out[0][1])
+
+
+@pytest.mark.parametrize("n,B,ties", [(1, 9, "none"), (7, 16, "none"), (17, 17, "days"), (255, 33, "all"),
+                                      (257, 48, "none"), (4099, 64, "days"), (4113, 20, "long"), (9001, 40, "none")])
+def test_batched_risk_rows(n, B, ties):
+    """The batched risk-set passes (state in rows of 16, 32, 48 or 64 vectors, 32,
+    16, 10 or 8 tiles to a workgroup) at the edges of their tiles: fewer subjects
+    than a tile, tie groups inside a tile, over many tiles and workgroups, over all
+    subjects, and tied censored subjects.  Losses to the batched tests' 1e-12.  The
+    gradient differs from the oracle's by the residual's rounding to q = max|r| /
+    2^22 (at most q / 2 a subject) and the FP32 output: s_j sum_i |g_ij - mu_j| q / 2
+    + 2^-23 |g_j| for the SNPs, FP32 rounding alone for the covariates."""
+    p, q = 37, 3
+    d = coxsim.genotype_problem(max(n, 30), p, 3, 0.4, 4000 + n)
+    rng = np.random.Generator(np.random.PCG64(n))
+    G = d.G[:, :n].copy()
+    time = {"none": rng.random(n), "days": rng.integers(1, 40, n).astype(float), "all": np.ones(n),
+            "long": np.where(rng.random(n) < 0.7, 5.0, rng.random(n) * 10)}[ties]
+    event = (rng.random(n) < 0.5).astype(np.int32)
+    event[0] = 1
+    ldx = (n + 15) // 16 * 16
+    X = torch.zeros((p, ldx), dtype=torch.int8)
+    X[:, :n] = torch.from_numpy(G)
+    Z = rng.normal(size=(q, n)).astype(np.float32)
+    cox = P.Cox(X.cuda(), time, event, xtype=P.X_INT8, n=n, center=torch.from_numpy(d.mu).cuda(),
+                scale=torch.from_numpy(d.s).cuda(), max_batch=B)
+    cox.set_covariates(torch.from_numpy(Z).cuda())
+    beta = (rng.normal(0, 0.2, (B, p + q)) * (rng.random((B, p + q)) < 0.5)).astype(np.float32)
+    loss, grad = cox.loss_grad(torch.from_numpy(beta).cuda())
+    only, _ = cox.loss_grad(torch.from_numpy(beta).cuda(), want_grad=False)
+    _bits(loss, only)
+    grad = grad.cpu().numpy()
+    Xs = (G.astype(np.float64) - d.mu[:, None].astype(np.float64)) * d.s[:, None].astype(np.float64)
+    full = np.concatenate([Xs, Z.astype(np.float64)])
+    M = oracle.Matrix.dense(full)
+    for b in range(B):
+        negL, gl = oracle.loss_grad(M, time, event, beta[b].astype(np.float64))
+        go = -gl  # the oracle gives the gradient of L
+        assert loss[b] == pytest.approx(negL, rel=1e-12, abs=1e-12 * n), b
+        r = oracle.loglik(full.T @ beta[b].astype(np.float64), time, event)[1]
+        tol = 2.0**-23 * np.abs(go) + 1e-12 * n
+        tol[:p] += np.abs(Xs).sum(axis=1) * np.abs(r).max() * 2.0**-23
+        assert (np.abs(grad[b] - go) <= tol).all(), (b, np.abs(grad[b] - go).max())
