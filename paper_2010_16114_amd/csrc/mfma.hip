@@ -237,12 +237,25 @@ __global__ __launch_bounds__(64 * (CW + LW), (CW + LW) / 4) void mfma_xtr_split_
 // registers; CW compute wavefronts read both from LDS and run the matrix cores,
 // QC / 4 steps of 64 subjects per stage.  The loaders read a column's 16 QC
 // bytes of a stage with QC adjacent lanes, so that they go out as one request
-// with one address translation (QC = 8: one whole 128-byte line per column and
-// stage, where QC = 4 reads each line in two halves, a stage apart); in the
-// matrix-core layout that mfma_xtr_split_kernel loads directly those bytes sit
-// in lanes 16 apart and go out as separate 16-byte requests.  In LDS a column
-// takes 16 (QC + 1) bytes (16 of padding), so that the 16 lanes of a fragment
-// read (16 consecutive columns, one 16-byte chunk each) hit distinct banks.
+// with one address translation; in the matrix-core layout that
+// mfma_xtr_split_kernel loads directly those bytes sit in lanes 16 apart and go
+// out as separate 16-byte requests.  QC = 4 reads each 128-byte line in two
+// halves, a stage apart; in LDS a column then takes 80 bytes (16 of padding), so
+// that the 16 lanes of a fragment read (16 consecutive columns, one 16-byte chunk
+// each) hit distinct banks.
+//
+// QC = 8 loads whole 128-byte lines whatever the column's alignment: column j
+// starts m_j = (its address / 16) mod 8 chunks into a line, so line L of it holds
+// the chunks 8 L - m_j .. 8 L - m_j + 7, and the 128 subjects of stage t lie in
+// lines t and t + 1.  A ring of three lines per column is kept in LDS: while stage
+// t is computed the loaders store line t + 2.  With the loads cut at multiples of
+// 128 subjects instead, every line of a column that is not itself aligned to 128
+// bytes was read twice (streaming loads do not wait in L2 for the other half):
+// 100,003 x 20,001 x 16 (ldx 100,016) took 521 us, 3.8 TB/s, and takes 293 now, 6.8
+// TB/s; 200,000 x 50,000 x 64, every second column half a line off, 2,330 and
+// 1,912 us; 400,000 x 62,500 x 64, all aligned, 4.7 ms either way.  Chunk q of
+// column c stands at (q + c / 2) mod 8 of its line's slot, which again spreads
+// the 16 lanes of a fragment read over distinct banks, without padding.
 //
 // SPLIT: the last, partly filled round of workgroups is split.  Each block of
 // columns from a.nfull on is taken by a.ksplit workgroups, one run of consecutive
@@ -264,10 +277,12 @@ __global__ __launch_bounds__(64 * (CW + LW), (CW + LW) / 4) void mfma_xtr_lds_ke
     constexpr int XPT = (XCH + LT - 1) / LT;
     constexpr int RPT = (CHUNKS + LT - 1) / LT;
     constexpr int RS = NCOL + 8;         // LDS row stride of the limb tile (16-byte units)
-    constexpr int XS = QC + 1;           // LDS stride of a column of the X tile (16-byte units)
+    constexpr bool LINES = QC == 8;      // whole lines of X, whatever the column's alignment
+    constexpr int XS = LINES ? 8 : QC + 1;  // LDS stride of a column of the X tile (16-byte units)
+    constexpr int XB = LINES ? 3 : 2;    // X tiles in LDS
     constexpr bool XALL = XCH % LT == 0, RALL = CHUNKS % LT == 0;
     __shared__ v4i sR[2][QC * RS];
-    __shared__ v4i sX[2][WCOLS * XS];
+    __shared__ v4i sX[XB][WCOLS * XS];
 
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int64_t n = a.n, p = a.p, ldx = a.ldx;
@@ -286,6 +301,9 @@ __global__ __launch_bounds__(64 * (CW + LW), (CW + LW) / 4) void mfma_xtr_lds_ke
     const int64_t nst = t1 - t0;
     const int64_t nloop = (nst + LDF - 1) / LDF * LDF;
     const int64_t j0 = blk * WCOLS;
+    // chunks between the line that column j starts in and its start
+    const uint32_t base16 = (uint32_t)(reinterpret_cast<uintptr_t>(a.X) >> 4), ldx16 = (uint32_t)(ldx >> 4);
+    auto lead = [&](int64_t j) { return LINES ? (int)((base16 + (uint32_t)j * ldx16) & 7u) : 0; };
 
     if (wid >= CW) {
         // loaders.  X chunk c: column c / QC of the workgroup, subjects 16 (c % QC) .. + 15 of the
@@ -304,8 +322,9 @@ __global__ __launch_bounds__(64 * (CW + LW), (CW + LW) / 4) void mfma_xtr_lds_ke
             const int cc = xok[k] ? c : 0;
             const int64_t col = j0 + cc / QC;
             xbase[k] = col < p ? (uint64_t)col * (uint64_t)ldx : 0;
-            xrow[k] = 16 * (cc % QC);
-            xdst[k] = (cc / QC) * XS + cc % QC;
+            const int q = cc % QC - lead(col);  // the chunk of line 0 this lane loads (negative: before the column)
+            xrow[k] = 16 * q;
+            xdst[k] = LINES ? (cc / QC) * XS + ((q + (cc / QC >> 1)) & 7) : (cc / QC) * XS + cc % QC;
         }
         const int8_t* rsrc[RPT];
         int rdst[RPT];
@@ -320,11 +339,12 @@ __global__ __launch_bounds__(64 * (CW + LW), (CW + LW) / 4) void mfma_xtr_lds_ke
         }
         v4i xr[LDF][XPT];
         v4i rr[LDF][RPT];
-        auto fetch = [&](int64_t t, v4i (&xg)[XPT], v4i (&rg)[RPT]) {
+        auto fetch_x = [&](int64_t t, v4i (&xg)[XPT]) {
 #pragma unroll
             for (int k = 0; k < XPT; ++k) {
                 const int64_t row = (t0 + t) * SUBJ + xrow[k];
-                const v4i* src = reinterpret_cast<const v4i*>(X + (row < n ? xbase[k] + (uint64_t)row : 0));
+                const v4i* src =
+                    reinterpret_cast<const v4i*>(X + ((uint64_t)row < (uint64_t)n ? xbase[k] + (uint64_t)row : 0));
                 if (xok[k]) {
                     if constexpr (NTX)
                         xg[k] = __builtin_nontemporal_load(src);
@@ -332,30 +352,49 @@ __global__ __launch_bounds__(64 * (CW + LW), (CW + LW) / 4) void mfma_xtr_lds_ke
                         xg[k] = *src;
                 }
             }
+        };
+        auto fetch_r = [&](int64_t t, v4i (&rg)[RPT]) {
             const int64_t kr = min(t0 + t, nstage - 1) * (int64_t)(16 * CHUNKS);
 #pragma unroll
             for (int k = 0; k < RPT; ++k)
                 if (rok[k]) rg[k] = *reinterpret_cast<const v4i*>(rsrc[k] + kr);
         };
-        auto store = [&](int buf, const v4i (&xg)[XPT], const v4i (&rg)[RPT]) {
+        auto store_x = [&](int buf, const v4i (&xg)[XPT]) {
 #pragma unroll
             for (int k = 0; k < XPT; ++k)
                 if (xok[k]) sX[buf][xdst[k]] = decode_a<XT>(xg[k]);
+        };
+        auto store_r = [&](int buf, const v4i (&rg)[RPT]) {
 #pragma unroll
             for (int k = 0; k < RPT; ++k)
                 if (rok[k]) sR[buf][rdst[k]] = rg[k];
         };
+        // AH: the X tiles that step t = 0 needs before it starts; tile t + AH is stored during step t
+        constexpr int AH = LINES ? 2 : 1;
 #pragma unroll
-        for (int q = 0; q < LDF; ++q) fetch(q, xr[q], rr[q]);
-        store(0, xr[0], rr[0]);
+        for (int q = 0; q < LDF; ++q) {
+            fetch_x(q, xr[q]);
+            fetch_r(q, rr[q]);
+        }
+        if constexpr (LINES) {  // line 0 makes room for line LDF; slot q % LDF holds line q
+            store_x(0, xr[0]);
+            fetch_x(LDF, xr[0]);
+        }
+        store_x(AH - 1, xr[(AH - 1) % LDF]);
+        store_r(0, rr[0]);
         __syncthreads();
+        int xb = AH % XB;  // the LDS tile that X tile t + AH goes to
         for (int64_t s0 = 0; s0 < nloop; s0 += LDF) {
 #pragma unroll
             for (int q = 0; q < LDF; ++q) {
                 const int64_t t = s0 + q;
-                fetch(t + LDF, xr[q], rr[q]);  // slot q held stage t, stored before the last barrier
+                // the slots fetched into held tiles stored before the last barrier
+                fetch_x(t + LDF + AH - 1, xr[(q + AH - 1) % LDF]);
+                fetch_r(t + LDF, rr[q]);
                 __builtin_amdgcn_sched_barrier(0);  // keep the new loads ahead of the stores below
-                store((int)(t & 1) ^ 1, xr[(q + 1) % LDF], rr[(q + 1) % LDF]);
+                store_x(xb, xr[(q + AH) % LDF]);
+                store_r((int)(t & 1) ^ 1, rr[(q + 1) % LDF]);
+                xb = xb + 1 == XB ? 0 : xb + 1;
                 __syncthreads();
             }
         }
@@ -370,16 +409,26 @@ __global__ __launch_bounds__(64 * (CW + LW), (CW + LW) / 4) void mfma_xtr_lds_ke
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = v4i{0, 0, 0, 0};
+    // LINES: whether this lane's chunk 4 h + lane / 16 of a stage lies in the stage's second line
+    bool second[MT][QC / 4];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int h = 0; h < QC / 4; ++h) second[mt][h] = LINES && 4 * h + (lane >> 4) + lead(jw + mt * 16 + acol) >= 8;
+    const int skew = LINES ? acol >> 1 : 0;
+    int xa = 0;  // the LDS tile of stage t's (first) X tile
     __syncthreads();  // the loaders' first stage is in LDS
     for (int64_t t = 0; t < nloop; ++t) {
         const int buf = (int)(t & 1);
+        const int xn = xa + 1 == XB ? 0 : xa + 1;
         if (t < nst) {
 #pragma unroll
             for (int h = 0; h < QC / 4; ++h) {  // 64 subjects per matrix-core step
                 v4i A[MT];
+                const int at = LINES ? (4 * h + (lane >> 4) + skew) & 7 : 4 * h + (lane >> 4);
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt)
-                    A[mt] = sX[buf][(wid * MT * 16 + mt * 16 + acol) * XS + 4 * h + (lane >> 4)];
+                    A[mt] = sX[second[mt][h] ? xn : xa][(wid * MT * 16 + mt * 16 + acol) * XS + at];
                 const v4i* sb = &sR[buf][(4 * h + (lane >> 4)) * RS + acol];
                 v4i bcur = sb[0];
 #pragma unroll
@@ -393,6 +442,7 @@ __global__ __launch_bounds__(64 * (CW + LW), (CW + LW) / 4) void mfma_xtr_lds_ke
                 }
             }
         }
+        xa = xn;
         __syncthreads();
     }
 #pragma unroll
@@ -1175,8 +1225,8 @@ hipError_t launch_lds(const MfmaArgs& a, hipStream_t s)
 //     + the shares' partial sums, written and read once (a stage moves 32 KB of X
 //     per compute unit in about 1.5 us; the sums move at about 4 TB/s).
 // A part-filled round costs a whole one, so 196 blocks of 1,563 stages on 256
-// slots take 4 rounds of 313 stages in fifths (2.32 ms at 200,000 x 50,000 x 64;
-// 2.64 ms in thirds, 2.46 ms unsplit), and 3 blocks of 24 stages take 2 stages in
+// slots take 4 rounds of 313 stages in fifths (1.91 ms at 200,000 x 50,000 x 64;
+// 2.09 ms unsplit), and 3 blocks of 24 stages take 2 stages in
 // twelfths (15 us; 21 us in thirds).
 int pick_ksplit(int64_t ntail, int64_t nstage, int64_t slots, int64_t ptail, int B, int64_t room)
 {
@@ -1207,12 +1257,16 @@ hipError_t launch_lds_tail(const MfmaArgs& a, hipStream_t s)
     if (e != hipSuccess) return e;
     if (per_cu < 1) return hipErrorInvalidConfiguration;
     const int64_t nblk = (a.p + WCOLS - 1) / WCOLS, slots = (int64_t)a.ncu * per_cu;
-    const int64_t ntail = nblk % slots;
+    int64_t ntail = nblk % slots;
     MfmaArgs b = a;
     b.nfull = nblk - ntail;
     const int64_t j0 = b.nfull * WCOLS, ptail = a.p - j0;
     if (ntail > 0 && ptail > a.tail_cols) return hipErrorInvalidValue;
     b.ksplit = pick_ksplit(ntail, (a.n + 16 * QC - 1) / (16 * QC), slots, ptail, a.B, a.tail_cols);
+    if (b.ksplit == 1) {  // no split pays: a last round of whole blocks, no partial sums
+        b.nfull = nblk;
+        ntail = 0;
+    }
     b.tail_cols = ptail;  // the shares' sums stand close together
     hipLaunchKernelGGL((mfma_xtr_lds_kernel<XT, NG, RL, CW, LW, MT, LDF, NTX, QC, true>),
                        dim3((unsigned)(b.nfull + b.ksplit * ntail)), dim3(64 * (CW + LW)), 0, s, b);

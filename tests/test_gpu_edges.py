@@ -104,3 +104,35 @@ def test_batched_risk_rows(n, B, ties):
         tol = 2.0**-23 * np.abs(go) + 1e-12 * n
         tol[:p] += np.abs(Xs).sum(axis=1) * np.abs(r).max() * 2.0**-23
         assert (np.abs(grad[b] - go) <= tol).all(), (b, np.abs(grad[b] - go).max())
+
+
+@pytest.mark.parametrize("n,lead", [(1000, 0), (1009, 48), (2040, 112), (2040, 0), (40, 16), (130, 64)])
+def test_whole_line_loads(n, lead):
+    """The X~' R shapes that load whole 128-byte lines of X (13 to 15) agree bit for
+    bit with a shape that loads 64-byte pieces from the column's start (8), for
+    columns that start anywhere in a line: ldx 0, 16, 48, 112 bytes past a multiple
+    of 128, X itself `lead` bytes into a line, less than a stage of subjects."""
+    p, B = 530, 16
+    d = coxsim.genotype_problem(n, p, 4, 0.3, 7000 + n + lead, days=True)
+    ldx = (n + 15) // 16 * 16
+    buf = torch.full((p * ldx + 256,), 0x40, dtype=torch.uint8)  # the bytes around X and its padding are not zero
+    X = buf[lead:lead + p * ldx].view(p, ldx)
+    X[:, :n] = torch.from_numpy(coxsim.FP8_E4M3_CODE[d.G])
+    dev = buf.cuda()
+    X = dev[lead:lead + p * ldx].view(p, ldx)
+    assert X.data_ptr() % 128 == lead
+    cox = P.Cox(X, d.time, d.event, xtype=P.X_FP8_E4M3, n=n, center=torch.from_numpy(d.mu).cuda(),
+                scale=torch.from_numpy(d.s).cuda(), max_batch=B)
+    lams = coxsim.lambda_grid(0.8 * cox.lambda_max(), B, 0.05)
+    sigma = 1.0 / (2.0 * (np.sqrt(n) + np.sqrt(p)) ** 2)
+    out = []
+    for xv in (8, 13, 14, 15):
+        with pytest.MonkeyPatch.context() as mp:
+            mp.setenv("COXHIP_MFMA_VARIANT", str(xv))
+            mp.setenv("COXHIP_ETA_VARIANT", "2")
+            beta, _, obj, _ = cox.fit_path(lams, max_iter=6, tol=0.0, step=sigma)
+        out.append((beta.cpu().numpy(), obj))
+    assert (out[0][0] != 0).any()
+    for beta, obj in out[1:]:
+        _bits(beta, out[0][0])
+        _bits(obj, out[0][1])
