@@ -742,8 +742,8 @@ def bench_autograd_c2(args):
 
 def bench_dense_eta_c4(args):
     """Dense X~ beta for B = 64 vectors over 400,000 x 500,000 FP8 genotypes, the
-    pass behind cox_loss_grad, warm starts and the dense-eta ablation: three exact
-    limb passes of the matrix-core eta update (one FP64-accurate product), against
+    pass behind cox_loss_grad, warm starts and the dense-eta ablation: one exact
+    product in nine int8 limbs per coefficient, X read once per 32 vectors, against
     the FP64 vector passes of 8 vectors each (COXHIP_NO_MFMA=1).  Timed through
     cox_loss_grad without the gradient: the dense phase, its eta-update launches,
     and the losses of both forms."""
@@ -790,12 +790,10 @@ def bench_dense_eta_c4(args):
                      "eta_kernel_ms": ek_ms / ek_n if ek_n else None, "eta_kernel_launches": ek_n, "loss": loss}
         log(f"{mode}: {out[mode]['dense_ms']:.2f} ms per dense pass of {B} vectors ({wall:.2f} ms per call)")
     rel = float(np.max(np.abs(out["mfma"]["loss"] - out["vector"]["loss"]) / np.abs(out["vector"]["loss"])))
-    tuning = cox.mfma_tuning()
-    _, eta_kernel = mfma_kernel_names(0, tuning["eta_variant"])
     # algorithmic bytes of one dense product: X once, the FP64 coefficients read, eta written
     alg = n * p + 8 * B * p + 8 * B * n
-    # one of its three eta-update launches: X once, the D limbs, eta read and written
-    launch_bytes = n * p + 3 * ((B + 15) // 16 * 16) * ((p + 63) // 64 * 64) + 16 * B * n
+    # its launches, one per 32 vectors: X in each, the limbs, eta written
+    launch_bytes = (B + 31) // 32 * n * p + 9 * ((B + 15) // 16 * 16) * ((p + 63) // 64 * 64) + 8 * B * n
     kms = out["mfma"]["eta_kernel_ms"]
     dense = out["mfma"]["dense_ms"]
     for m in out.values():
@@ -806,18 +804,17 @@ def bench_dense_eta_c4(args):
         "ms_per_step": dense, "higher_is_better": False, "scaling": "weak", "vs_baseline": None,
         "dtype": "int8", "data": "synthetic",
         "config": {"workload": f"dense X~ beta, FP8 E4M3 genotype X n={n} p={p}, B={B} vectors 5% nonzero, "
-                               f"three exact 22-bit limb passes on the matrix cores", "n": n, "p": p, "B": B},
+                               f"exact products of nine int8 limbs on the matrix cores", "n": n, "p": p, "B": B},
         "modes": out,
         "speedup_vs_vector": out["vector"]["dense_ms"] / dense,
         "loss_max_rel_diff_vs_vector": rel,
         "hbm_probe": probe,
-        "roofline": {"bound": "hbm", "kernel": f"{eta_kernel} (one limb pass, every column selected)",
+        "roofline": {"bound": "hbm", "kernel": "mfma_dense_kernel+dense_sum_kernel (all launches of a product)",
                      "achieved": launch_bytes / (kms / 1e3) / 1e9 if kms else None, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": launch_bytes / (kms / 1e3) / 1e9 / HBM_PEAK_GBS if kms else None,
-                     "traffic": stored_traffic(f"mfma_eta_kernel_dense_geno_fp8_{n}x{p}_b{B}_traffic.md",
-                                               MFMA_SOURCES, f"shape{tuning['eta_variant']}"),
+                     "traffic": None,
                      "algorithmic_bytes_per_launch": launch_bytes, "kernel_ms": kms},
-        "roofline_pass": {"what": "one dense product (three launches) against a single read of X",
+        "roofline_pass": {"what": "one dense product against a single read of X",
                           "bytes": alg, "achieved": alg / (dense / 1e3) / 1e9,
                           "frac": alg / (dense / 1e3) / 1e9 / HBM_PEAK_GBS},
     }

@@ -121,9 +121,10 @@ cox_status cox_last_error(const cox_ctx *ctx, char *buf, size_t len);
  *   loss  host [B] double: -L(beta_b)
  *   grad  dev [B][ptot] float, or NULL for the loss only: -[X~ Z]' r_b
  * eta = X~ beta_b is formed to FP64 accuracy: by FP64 passes of up to 8 vectors,
- * or, for B > 8 over one-byte allele counts, by three exact 22-bit integer
- * passes on the matrix cores (whatever the first pass leaves of each vector is
- * taken by the next; at most 2^-69 max|beta_b| per coefficient is left over).
+ * or, for B > 8 over one-byte allele counts, by exact integer products on the
+ * matrix cores (each coefficient as three 22-bit integers, whatever the first
+ * leaves taken by the next; at most 2^-69 max|beta_b| per coefficient is left
+ * over).
  * NUMERIC if a loss is non-finite (e.g. NaN in beta). Synchronises. */
 cox_status cox_loss_grad(cox_ctx *ctx, const float *beta, int32_t B, double *loss, float *grad);
 
@@ -176,7 +177,7 @@ typedef struct {
                               computation; 1 documents the requirement. */
     int32_t eta_mode;   /* 0: eta updated from the columns whose beta changed (FP64 accumulator);
                            1: eta recomputed every step by a dense product (as in cox_loss_grad: FP64
-                           passes of up to 8 vectors, or three exact limb passes on the matrix cores
+                           passes of up to 8 vectors, or exact limb products on the matrix cores
                            for B > 8 over allele counts) */
     int32_t poll;       /* steps between host checks of the convergence flags; <= 0: 16 */
     int32_t residual_bits; /* batched matrix-core gradient pass only (allele counts, B > 8): the

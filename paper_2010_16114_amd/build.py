@@ -15,7 +15,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libcoxhip.so")
-SOURCES = ["api.cpp", "risk.hip", "riskb.hip", "gemv.hip", "gemvt.hip", "misc.hip", "mfma.hip", "covar.hip", "refit.hip", "nmf.hip",
+SOURCES = ["api.cpp", "risk.hip", "riskb.hip", "gemv.hip", "gemvt.hip", "misc.hip", "mfma.hip", "mfma_dense.hip", "covar.hip", "refit.hip", "nmf.hip",
            "persist.hip"]
 ARCH = os.environ.get("COXHIP_ARCH", "gfx950")
 FLAGS = [
@@ -28,7 +28,7 @@ FLAGS = [
 
 
 # sources of the tuned matrix-core kernels: their hash keys the autotuner's cache
-TUNED = ["mfma.hip", "mfma.h", "device_common.h"]
+TUNED = ["mfma.hip", "mfma.h", "mfma_dev.h", "device_common.h"]
 
 
 def source_hash() -> str:

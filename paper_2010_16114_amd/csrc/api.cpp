@@ -104,10 +104,10 @@ struct cox_ctx {
     double *rb_tot = nullptr, *rb_wg = nullptr;  // tile and workgroup totals of the risk-set passes
     unsigned long long* keys = nullptr;          // [3][kKeys]: max eta, max |r|, sums of R; then a counter
     int* geno_bad = nullptr;
-    int8_t* dlimbs = nullptr;    // [3][Bmax16][dstride] eta-update limbs
-    int32_t *sel_all = nullptr, *nsel_all = nullptr;  // 0 .. p - 1 and p: every column, for dense passes
+    int8_t* dlimbs = nullptr;    // [dstride][9 Bmax16] limbs of the dense product; the eta update uses 3
     int32_t* nonfin = nullptr;   // [max_batch] a dense pass's coefficient vector holds a NaN or infinity
-    long long* eta_part = nullptr;  // [ncu][2][Bmax16][256] partial sums of blocks two eta workgroups share
+    long long* eta_part = nullptr;  // partial sums of blocks several workgroups share: [ncu][2][256][Bmax16] of the eta
+    int64_t eta_words = 0;          // update; the dense product's split blocks take up to 12 M of the words
     long long* xtr_tail = nullptr;  // [Bmax16][tail_cols] X~' R sums of the split last round (shape 15)
     int64_t tail_cols = 0;       // its columns over all shares: up to 6 shares of a full round, 16 of a small one
     int ncu = 0;                 // compute units of the device
@@ -517,8 +517,8 @@ cox_status dense_eta_mfma(cox_ctx* c, const double* coef, int B);
 bool use_mfma(cox_ctx* c, int B);
 
 // eta[b] = X~ coef[b] (no centring) for b < B; coef is b-major [B][p].  More
-// than 8 vectors over one-byte allele counts go through the matrix cores (three
-// passes over X for any B, against one FP64 pass per 8 vectors) and leave eta in
+// than 8 vectors over one-byte allele counts go through the matrix cores (one
+// pass over X per 32 vectors, against one FP64 pass per 8) and leave eta in
 // rows (rows = use_mfma(c, B), from the caller).
 cox_status dense_eta(cox_ctx* c, const double* coef, int B, const double* shift, bool rows)
 {
@@ -715,32 +715,21 @@ cox_status pick_eta_variant(cox_ctx* c, MfmaEtaArgs* m)
 }
 
 // eta[b] = X coef[b] for b < B on the matrix cores (one-byte allele counts,
-// B > 8), to FP64 accuracy in three passes over X.  Each pass quantises what is
-// left of coef_b to integers of at most 22 bits on a per-vector scale q_b (the
-// eta update's D limbs, every column selected), adds q_b X R_b to eta with
-// exact integer sums, and leaves coef_b - q_b R_b (one fma) for the next pass.
-// What remains after three passes is at most 2^-69 max|coef_b|.  Integer limbs
-// cannot carry a NaN or an infinity, so a vector holding one gets eta = NaN,
-// as the FP64 passes would give it.
+// B > 8), to FP64 accuracy in one pass over X per 32 vectors with nine int8 limbs
+// per coefficient (mfma_dense.hip); at most 2^-69 max|coef_b| of a coefficient is left out.
+// Integer limbs cannot carry a NaN or an infinity, so a vector holding one gets
+// eta = NaN, as the FP64 passes would give it.
 cox_status dense_eta_mfma(cox_ctx* c, const double* coef, int B)
 {
     const int bpad = (int)round_up(B, 16);
     HIPCHK(launch_fill_i32(c->nonfin, 0, B, c->stream), "clear flags");
-    HIPCHK(launch_nonfinite(coef, c->p, B, c->nonfin, c->stream), "coefficient check");
-    HIPCHK(launch_fill_f64(c->eta, 0.0, bpad * c->n, c->stream), "clear eta");
-    MfmaEtaArgs m = mfma_eta_args(c, c->sel_all, c->nsel_all, B, nullptr);
-    for (int k = 0; k < 3; ++k) {
-        const double* src = k == 0 ? coef : c->dcoef;
-        HIPCHK(launch_quantize_d(src, c->p, c->sel_all, c->nsel_all, B, c->dmaxp, c->dlimbs, c->dstride, bpad,
-                                 c->dscale, c->stream),
-               "quantise coefficients");
-        if (k == 0) STCHK(pick_eta_variant(c, &m));
-        tmark(c, COX_PHASE_ETA_KERNEL);
-        HIPCHK(launch_mfma_eta(m, c->stream), "dense X beta on matrix cores");
-        tmark(c, COX_PHASE_ETA_KERNEL);
-        if (k < 2) HIPCHK(launch_coef_remainder(src, c->dcoef, c->p, B, c->dscale, c->stream), "coefficient remainder");
-    }
-    HIPCHK(launch_poison_rows(c->eta, c->n, B, bpad, c->nonfin, c->stream), "non-finite coefficients");
+    HIPCHK(launch_dense_quant(coef, c->p, B, c->dmaxp, c->dlimbs, c->dstride, bpad, c->dscale, c->nonfin, c->stream),
+           "quantise coefficients");
+    MfmaDenseArgs m{c->x.X, c->x.xt,   c->n,      c->p,   c->x.ldx,    c->dlimbs,    c->dstride, bpad,
+                    B,      c->dscale, c->nonfin, c->eta, c->eta_part, c->eta_words, c->ncu};
+    tmark(c, COX_PHASE_ETA_KERNEL);
+    HIPCHK(launch_mfma_dense(m, c->stream), "dense X beta on matrix cores");
+    tmark(c, COX_PHASE_ETA_KERNEL);
     return COX_OK;
 }
 
@@ -1144,16 +1133,18 @@ cox_status cox_setup(cox_ctx** out, const cox_matrix* X, const double* time, con
         ok = dalloc(c, &c->limbs, (size_t)3 * c->bpad_max * c->rstride) && dalloc(c, &c->qscale, max_batch) &&
              dalloc(c, &c->egrank, n + 1) && dalloc(c, &c->rb_tot, (size_t)32 * riskb_tiles()) &&
              dalloc(c, &c->rb_wg, (size_t)192 * riskb_wgs()) && dalloc(c, &c->keys, 3 * kKeys + 1) &&
-             dalloc(c, &c->geno_bad, 1) && dalloc(c, &c->dlimbs, (size_t)3 * c->bpad_max * c->dstride) &&
+             dalloc(c, &c->geno_bad, 1) && dalloc(c, &c->dlimbs, (size_t)9 * c->bpad_max * c->dstride) &&
              dalloc(c, &c->dscale, max_batch) && dalloc(c, &c->dmaxp, (size_t)max_batch * ((c->dstride + 4095) / 4096)) &&
-             dalloc(c, &c->sel_all, p) && dalloc(c, &c->nsel_all, 1) && dalloc(c, &c->nonfin, max_batch);
+             dalloc(c, &c->nonfin, max_batch);
         if (ok && hipDeviceGetAttribute(&c->ncu, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) {
             (void)hipGetLastError();
             c->ncu = 0;
         }
         if (ok && c->ncu > 0) {
             c->tail_cols = std::min((int64_t)6 * c->ncu * 256, 16 * p);
-            ok = dalloc(c, &c->eta_part, (size_t)c->ncu * 2 * c->bpad_max * 256) &&
+            c->eta_words = std::max((int64_t)c->ncu * 2 * c->bpad_max * 256,
+                                    std::min(int64_t(12) << 20, 16 * round_up(n, 512) * 3 * 32));
+            ok = dalloc(c, &c->eta_part, (size_t)c->eta_words) &&
                  dalloc(c, &c->xtr_tail, (size_t)c->bpad_max * c->tail_cols);
         }
     }
@@ -1194,10 +1185,6 @@ cox_status cox_setup(cox_ctx** out, const cox_matrix* X, const double* time, con
         chk(launch_fill_f64(reinterpret_cast<double*>(c->limbs), 0.0, (int64_t)3 * c->bpad_max * c->rstride / 8,
                             c->stream));
     if (c->keys) chk(launch_fill_f64(reinterpret_cast<double*>(c->keys), 0.0, 3 * kKeys + 1, c->stream));
-    if (c->sel_all) {
-        chk(launch_iota_i32(c->sel_all, p, c->stream));
-        chk(launch_fill_i32(c->nsel_all, (int32_t)p, 1, c->stream));
-    }
     if (st == COX_OK && hipStreamSynchronize(c->stream) != hipSuccess) st = COX_ERR_DEVICE;
     if (st != COX_OK) {
         (void)hipGetLastError();

@@ -174,8 +174,6 @@ hipError_t launch_risk(const RiskArgs& a, hipStream_t s);
 hipError_t launch_risk_rows(RiskArgs a, hipStream_t s);  // the batched form (a.bpad > 0)
 int64_t riskb_tiles();  // tiles of the batched form at 16 vectors, at most
 int riskb_wgs();        // its workgroups, at most
-// eta[i * bpad + b] = NaN for i < n, for each b < B with flag[b] set
-hipError_t launch_poison_rows(double* eta, int64_t n, int B, int bpad, const int32_t* flag, hipStream_t s);
 hipError_t launch_gemvt(const GemvtArgs& a, hipStream_t s);       // sums, then epilogue
 hipError_t launch_gemvt_sums(const GemvtArgs& a, hipStream_t s);  // the row-split column sums alone
 // the epilogue alone, on column sums already in a.part (nb may exceed 8)
@@ -229,15 +227,6 @@ hipError_t launch_resume(int32_t* status, int32_t* active, int32_t* kit, const i
 // acc[0] += v[0]
 hipError_t launch_count_add(const int32_t* v, long long* acc, hipStream_t s);
 hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t m, hipStream_t s);
-// p[i] = i for i < m
-hipError_t launch_iota_i32(int32_t* p, int64_t m, hipStream_t s);
-// flag[b] = 1 if coef[b*p + j] is not finite for some j < p (b < B; flags cleared beforehand)
-hipError_t launch_nonfinite(const double* coef, int64_t p, int B, int32_t* flag, hipStream_t s);
-// dst[b*p + j] = src[b*p + j] - dscale[b] * llrint(src[b*p + j] / dscale[b]) for b < B, j < p
-// (src == dst allowed): what the eta update's D quantisation leaves of each entry
-hipError_t launch_coef_remainder(const double* src, double* dst, int64_t p, int B, const double* dscale,
-                                 hipStream_t s);
-
 // ---- the dense covariate block Z beside X (covar.hip)
 struct CovArgs {
     const float* Z;        // column-major n x q, column k at Z + k * ldz

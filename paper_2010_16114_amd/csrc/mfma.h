@@ -86,6 +86,29 @@ hipError_t launch_quantize_rows(const double* r64, int64_t n, int B, const unsig
                                 int64_t lstride, int bpad, int nlimb, double* qscale, unsigned long long* rsum,
                                 unsigned* done, double* sumr, hipStream_t s);
 hipError_t launch_mfma_xtr(const MfmaArgs& a, hipStream_t s);
+
+// ---- dense products (mfma_dense.hip): eta_b(i) = sum_j g(i, j) c_b(j)
+struct MfmaDenseArgs {
+    const void* X;
+    int xt;
+    int64_t n, p, ldx;      // ldx % 16 == 0, X 16-byte aligned
+    const int8_t* dlimbs;   // dstride * 9 * bpad limbs as launch_dense_quant lays them out
+    int64_t dstride;        // a multiple of 64, >= p
+    int bpad, B;
+    const double* dscale;   // [B]
+    const int32_t* nonfin;  // [B] nonzero: eta_b = NaN (a coefficient was not finite)
+    double* eta;            // [n][bpad], written
+    long long* part;        // [part_room] partial sums of the split blocks
+    int64_t part_room;
+    int ncu;                // compute units of the device
+    int b0 = 0;                   // set by the launch: its first vector,
+    int64_t nblk = 0, nfull = 0;  // blocks of subjects, and those that run unsplit,
+    int ksplit = 1;               // shares of each of the others
+};
+// coef [B][p] -> dlimbs, dscale, nonfin (cleared by the caller); dmaxp [B][ceil(p / 4096)]
+hipError_t launch_dense_quant(const double* coef, int64_t p, int B, double* dmaxp, int8_t* dlimbs, int64_t dstride,
+                              int bpad, double* dscale, int32_t* nonfin, hipStream_t s);
+hipError_t launch_mfma_dense(const MfmaDenseArgs& a, hipStream_t s);
 hipError_t launch_geno_check(const void* X, int xt, int64_t n, int64_t p, int64_t ldx, int* bad, hipStream_t s);
 
 }  // namespace cox

@@ -195,34 +195,6 @@ __global__ void fill_i32_kernel(int32_t* __restrict__ p, int32_t v, int64_t m)
     for (int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x; i < m; i += (int64_t)gridDim.x * kT) p[i] = v;
 }
 
-__global__ void iota_i32_kernel(int32_t* __restrict__ p, int64_t m)
-{
-    for (int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x; i < m; i += (int64_t)gridDim.x * kT) p[i] = (int32_t)i;
-}
-
-// flag[b] = 1 when some coef[b][j], j < p, is not finite (the flags cleared by
-// the caller); one workgroup row per b (blockIdx.y), every writer stores 1
-__global__ void nonfinite_kernel(const double* __restrict__ coef, int64_t p, int32_t* __restrict__ flag)
-{
-    const int b = blockIdx.y;
-    bool bad = false;
-    for (int64_t j = (int64_t)blockIdx.x * kT + threadIdx.x; j < p; j += (int64_t)gridDim.x * kT)
-        bad |= !isfinite(coef[(int64_t)b * p + j]);
-    if (bad) flag[b] = 1;
-}
-
-// dst[b][j] = src[b][j] - q_b R, R = llrint(src[b][j] / q_b): the integer the
-// eta update's quantiser takes for that entry at the same scale q_b.  One fma,
-// so the remainder carries at most one rounding of 2^-53 q_b.
-__global__ void coef_remainder_kernel(const double* __restrict__ src, double* __restrict__ dst, int64_t p,
-                                      int64_t m, const double* __restrict__ dscale)
-{
-    for (int64_t k = (int64_t)blockIdx.x * kT + threadIdx.x; k < m; k += (int64_t)gridDim.x * kT) {
-        const double q = dscale[k / p], v = src[k];
-        dst[k] = fma(-q, (double)llrint(v / q), v);
-    }
-}
-
 }  // namespace
 
 #define COX_LAUNCH(kernel, grid, ...)                                        \
@@ -311,22 +283,4 @@ hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t m, hipStream_t s)
 {
     COX_LAUNCH(fill_i32_kernel, grid_for(m), p, v, m);
 }
-hipError_t launch_iota_i32(int32_t* p, int64_t m, hipStream_t s)
-{
-    COX_LAUNCH(iota_i32_kernel, grid_for(m), p, m);
-}
-hipError_t launch_nonfinite(const double* coef, int64_t p, int B, int32_t* flag, hipStream_t s)
-{
-    if (p < 1 || B < 1) return hipErrorInvalidValue;
-    const unsigned gx = (unsigned)min((int64_t)256, (p + kT - 1) / kT);
-    hipLaunchKernelGGL(nonfinite_kernel, dim3(gx, (unsigned)B), dim3(kT), 0, s, coef, p, flag);
-    return hipGetLastError();
-}
-hipError_t launch_coef_remainder(const double* src, double* dst, int64_t p, int B, const double* dscale,
-                                 hipStream_t s)
-{
-    if (p < 1 || B < 1) return hipErrorInvalidValue;
-    COX_LAUNCH(coef_remainder_kernel, grid_for((int64_t)B * p), src, dst, p, (int64_t)B * p, dscale);
-}
-
 }  // namespace cox

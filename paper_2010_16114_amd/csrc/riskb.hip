@@ -378,17 +378,6 @@ __global__ __launch_bounds__(kQT) void quantize_rows_kernel(const double* __rest
     if (threadIdx.x == 0) *done = 0;
 }
 
-// eta[i][b] = NaN for every i < n of each b whose flag is set
-__global__ __launch_bounds__(256) void poison_rows_kernel(double* __restrict__ eta, int64_t n, int B, int bpad,
-                                                          const int32_t* __restrict__ flag)
-{
-    const int64_t m = n * bpad;
-    for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < m; t += (int64_t)gridDim.x * 256) {
-        const int b = (int)(t % bpad);
-        if (b < B && flag[b]) eta[t] = __builtin_nan("");
-    }
-}
-
 }  // namespace
 
 void riskb_shape(int64_t n, int bpad, int64_t* tile, int* nwg)
@@ -427,14 +416,6 @@ hipError_t launch_quantize_rows(const double* r, int64_t n, int B, const unsigne
     const unsigned grid = (unsigned)min((int64_t)256, (nchunk + per - 1) / per);
     hipLaunchKernelGGL(quantize_rows_kernel, dim3(grid), dim3(kQT), 0, s, r, n, B, rkey, limbs, bpad, nlimb, qscale,
                        rsum, done, sumr);
-    return hipGetLastError();
-}
-
-hipError_t launch_poison_rows(double* eta, int64_t n, int B, int bpad, const int32_t* flag, hipStream_t s)
-{
-    if (n < 1 || B < 1 || bpad < B) return hipErrorInvalidValue;
-    const unsigned grid = (unsigned)min((int64_t)4096, (n * bpad + 255) / 256);
-    hipLaunchKernelGGL(poison_rows_kernel, dim3(grid), dim3(256), 0, s, eta, n, B, bpad, flag);
     return hipGetLastError();
 }
 

@@ -136,3 +136,26 @@ def test_whole_line_loads(n, lead):
     for beta, obj in out[1:]:
         _bits(beta, out[0][0])
         _bits(obj, out[0][1])
+
+
+@pytest.mark.parametrize("n,p,B", [(33000, 130, 64), (131100, 65, 9), (66000, 200, 20), (33000, 64, 40), (1000, 1000, 64),
+                                   (513, 63, 16), (129, 700, 33)])
+def test_dense_product_blocks(n, p, B, monkeypatch):
+    """The one-pass dense X~ beta of the matrix cores (512, 256 or 128 subjects per
+    block; whole rounds of blocks and a last one split over columns; odd and even
+    numbers of 64-column stages) against the FP64 vector passes: the losses agree to
+    the batched tests' 1e-12, and a vector with a NaN stays alone in its loss."""
+    d = coxsim.genotype_problem(n, p, 4, 0.5, 8100 + n, days=True)
+    cox, _ = device_problem(d, "int8", ldx=(n + 15) // 16 * 16, max_batch=B)
+    rng = np.random.Generator(np.random.PCG64(n + p))
+    scale = 10.0 ** rng.uniform(-6, 0, (B, 1))
+    beta = torch.from_numpy((0.2 * scale * rng.normal(size=(B, p))).astype(np.float32)).cuda()
+    beta[1] = 0.0
+    loss, _ = cox.loss_grad(beta, want_grad=False)
+    monkeypatch.setenv("COXHIP_NO_MFMA", "1")
+    ref, _ = cox.loss_grad(beta, want_grad=False)
+    monkeypatch.delenv("COXHIP_NO_MFMA")
+    np.testing.assert_allclose(loss, ref, rtol=1e-12)
+    beta[B // 2, p // 2] = float("nan")
+    with pytest.raises(P.CoxError):
+        cox.loss_grad(beta, want_grad=False)
