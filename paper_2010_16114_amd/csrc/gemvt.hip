@@ -7,11 +7,13 @@ namespace {
 
 using namespace gemvtdev;
 
-template <int XT, int NB, bool VEC>
+constexpr int64_t kFewWorkgroups = 512;
+
+template <int XT, int NB, bool VEC, int CPW>
 __global__ __launch_bounds__(kGemvtThreads) void gemvt_sums_kernel(GemvtArgs a)
 {
     __shared__ __attribute__((aligned(16))) float sr[NB * chunk_rows<NB>()];
-    gemvt_sums_blk<XT, NB, VEC>(a, blockIdx.x, blockIdx.y, sr);
+    gemvt_sums_blk<XT, NB, VEC, CPW>(a, blockIdx.x, blockIdx.y, sr);
 }
 
 template <int CB>
@@ -28,16 +30,25 @@ hipError_t launch_epilogue(const GemvtArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
+template <int XT, int NB, int CPW>
+hipError_t launch_cols(const GemvtArgs& a, hipStream_t s)
+{
+    const dim3 grid((unsigned)((a.x.p + 4 * CPW - 1) / (4 * CPW)), (unsigned)a.nsplit);
+    if (a.x.vec16)
+        hipLaunchKernelGGL((gemvt_sums_kernel<XT, NB, true, CPW>), grid, dim3(kGemvtThreads), 0, s, a);
+    else
+        hipLaunchKernelGGL((gemvt_sums_kernel<XT, NB, false, CPW>), grid, dim3(kGemvtThreads), 0, s, a);
+    return hipGetLastError();
+}
+
 template <int XT, int NB>
 hipError_t launch_t(const GemvtArgs& a, hipStream_t s)
 {
-    constexpr int cols_wg = 4 * cols_per_wave<XT, NB>();
-    const dim3 grid((unsigned)((a.x.p + cols_wg - 1) / cols_wg), (unsigned)a.nsplit);
-    if (a.x.vec16)
-        hipLaunchKernelGGL((gemvt_sums_kernel<XT, NB, true>), grid, dim3(kGemvtThreads), 0, s, a);
-    else
-        hipLaunchKernelGGL((gemvt_sums_kernel<XT, NB, false>), grid, dim3(kGemvtThreads), 0, s, a);
-    return hipGetLastError();
+    constexpr int CPW = cols_per_wave<XT, NB>();
+    // fewer than two workgroups per compute unit: four columns a wavefront shorten each one's work
+    const int64_t wgs = (a.x.p + 4 * CPW - 1) / (4 * CPW) * a.nsplit;
+    if (CPW > 4 && wgs < kFewWorkgroups) return launch_cols<XT, NB, 4>(a, s);
+    return launch_cols<XT, NB, CPW>(a, s);
 }
 
 template <int XT>

@@ -37,6 +37,9 @@ constexpr int kU = 2;  // row steps in flight per column
 template <int XT>
 constexpr int rows_per_load() { return XT == XT_F32 ? 4 : 16; }
 
+// Columns per wavefront where the columns fill the chip.  With fewer columns
+// every wavefront takes four (CPW = 4): a column's sums are one wavefront's
+// either way and in the same order.
 template <int XT, int NB>
 constexpr int cols_per_wave() { return XT == XT_F32 ? 4 : (NB == 1 ? 16 : (NB == 2 ? 8 : 4)); }
 
@@ -60,13 +63,12 @@ __device__ __forceinline__ int lds_pos(int row)
 
 // One workgroup of the column sums: column block bx, row split by.  sr: LDS
 // of NB * chunk_rows<NB>() floats (32 KB), 16-byte aligned.
-template <int XT, int NB, bool VEC>
+template <int XT, int NB, bool VEC, int CPW = cols_per_wave<XT, NB>()>
 __device__ __forceinline__ void gemvt_sums_blk(const GemvtArgs& a, int bx, int by, float* __restrict__ sr)
 {
     constexpr int RPL = rows_per_load<XT>();
     constexpr int WROWS = kWave * RPL;
     constexpr int RC = chunk_rows<NB>();
-    constexpr int CPW = cols_per_wave<XT, NB>();
     static_assert(RC % 1024 == 0 && kSplitRows % RC == 0, "chunk must hold whole wave steps");
 
     const int lane = threadIdx.x & (kWave - 1);
