@@ -185,7 +185,9 @@ __global__ __launch_bounds__(kT) void eta_update_kernel(XDesc x, const int32_t* 
                                                         double* __restrict__ part, int64_t cstride, int ncg,
                                                         const int32_t* __restrict__ active)
 {
-    eta_update_blk<XT, NB, VEC>(x, sel, nsel_p, dcoef, b0, nb, part, cstride, ncg, active, blockIdx.x, blockIdx.y);
+    __shared__ UpdLds<NB> lds;
+    eta_update_blk<XT, NB, VEC>(x, sel, nsel_p, dcoef, b0, nb, part, cstride, ncg, active, blockIdx.x, blockIdx.y,
+                                lds);
 }
 
 // One workgroup per chunk of 1024 blocks of columns.  Each adds up the counts

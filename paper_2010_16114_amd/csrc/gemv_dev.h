@@ -50,12 +50,25 @@ __device__ __forceinline__ int64_t row_of(int64_t slab0, int e)
     return VEC ? slab0 + (int64_t)threadIdx.x * 4 + e : slab0 + threadIdx.x + (int64_t)kT * e;
 }
 
+// Columns of the change list staged at a time, and LDS bytes of the stage.
+constexpr int kUpdStage = 128;
+constexpr int kUpdAhead = 8;  // columns of loads in flight
+template <int NB>
+struct UpdLds {
+    double d[NB][kUpdStage];
+    int32_t sel[kUpdStage];
+};
+
 // One workgroup of the eta update: row slab bx (kRows rows), column group cg.
+// The group's column indices and coefficients come into LDS first, so that the
+// loads of X hang on nothing but LDS and kUpdAhead of them are in flight (the
+// change list, then X and the coefficients, one after another for every four
+// columns took 17 us for a 1,000 x 2,000 problem).
 template <int XT, int NB, bool VEC>
 __device__ __forceinline__ void eta_update_blk(const XDesc& x, const int32_t* __restrict__ sel,
                                                const int32_t* __restrict__ nsel_p, const double* __restrict__ dcoef,
                                                int b0, int nb, double* __restrict__ part, int64_t cstride, int ncg,
-                                               const int32_t* __restrict__ active, int bx, int cg)
+                                               const int32_t* __restrict__ active, int bx, int cg, UpdLds<NB>& lds)
 {
     const int nsel = *nsel_p;
     if (nsel == 0) return;
@@ -75,33 +88,40 @@ __device__ __forceinline__ void eta_update_blk(const XDesc& x, const int32_t* __
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[b][e] = 0.0;
     const int64_t r0 = slab0 + (int64_t)threadIdx.x * 4;
-    for (int q = q0; q < q1; q += 4) {
-        float xv[4][4];
-        int64_t jj[4];
+    for (int qs = q0; qs < q1; qs += kUpdStage) {
+        const int m = min(kUpdStage, q1 - qs);
+        __syncthreads();
+        for (int t = threadIdx.x; t < m * NB; t += kT) {
+            const int b = t / m, q = t % m;
+            const int32_t j = sel[qs + q];
+            if (b == 0) lds.sel[q] = j;
+            lds.d[b][q] = b < nb ? dcoef[(int64_t)(b0 + b) * p + j] : 0.0;
+        }
+        __syncthreads();
+        for (int q = 0; q < m; q += kUpdAhead) {
+            float xv[kUpdAhead][4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            jj[u] = q + u < q1 ? sel[q + u] : -1;
-            if (jj[u] >= 0) {
+            for (int u = 0; u < kUpdAhead; ++u) {
+                const int64_t j = lds.sel[min(q + u, m - 1)];
                 if (VEC) {
-                    load_rows4<XT, true>(x, jj[u], r0, n, xv[u]);
+                    load_rows4<XT, true>(x, j, r0, n, xv[u]);
                 } else {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) {
                         const int64_t r = row_of<false>(slab0, e);
-                        xv[u][e] = r < n ? load_x1<XT>(x.X, jj[u] * x.ldx + r) : 0.f;
+                        xv[u][e] = r < n ? load_x1<XT>(x.X, j * x.ldx + r) : 0.f;
                     }
                 }
             }
-        }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            if (jj[u] < 0) break;
+            for (int u = 0; u < kUpdAhead; ++u) {
+                if (q + u >= m) break;
 #pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                if (b >= nb) break;
-                const double d = dcoef[(int64_t)(b0 + b) * p + jj[u]];
+                for (int b = 0; b < NB; ++b) {
+                    const double d = lds.d[b][q + u];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) acc[b][e] = fma((double)xv[u][e], d, acc[b][e]);
+                    for (int e = 0; e < 4; ++e) acc[b][e] = fma((double)xv[u][e], d, acc[b][e]);
+                }
             }
         }
     }

@@ -106,6 +106,7 @@ __global__ __launch_bounds__(kPT, (persist_waves<XT, NB>())) void fit_persistent
     __shared__ int ish[17], sstart[kPT], scnt[kPT];
     __shared__ int s_flag;
     static_assert(NB * gemvtdev::chunk_rows<NB>() * sizeof(float) <= sizeof(double) * kMaxTiles, "r chunk fits");
+    static_assert(sizeof(gemvdev::UpdLds<NB>) <= sizeof(double) * kMaxTiles, "the eta update's stage fits");
     float* const rchunk = reinterpret_cast<float*>(big);
 
     const RiskArgs& ra = a.ra;
@@ -123,7 +124,8 @@ __global__ __launch_bounds__(kPT, (persist_waves<XT, NB>())) void fit_persistent
             // eta partials of the columns that changed in the last step
             for (int64_t v = blockIdx.x; v < slabs * a.ncg; v += G) {
                 gemvdev::eta_update_blk<XT, NB, true>(g.x, a.sel, a.nsel, a.dcoef, 0, B, a.part_upd, a.cstride,
-                                                      a.ncg, ra.ctl.active, (int)(v % slabs), (int)(v / slabs));
+                                                      a.ncg, ra.ctl.active, (int)(v % slabs), (int)(v / slabs),
+                                                      *reinterpret_cast<gemvdev::UpdLds<NB>*>(big));
                 __syncthreads();
             }
             if (grid_barrier(br, nwg, &s_flag)) return;
