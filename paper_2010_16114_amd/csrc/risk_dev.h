@@ -17,7 +17,8 @@
 // request).  Inside cox_fit_path the last stage also forms f_k = -L +
 // lambda ||beta_k||_1 and applies the lag-k stopping rule of Section 6.
 //
-// Five phases, each spread over many workgroups (by = b):
+// Five phases, each spread over many workgroups (by = b); for few subjects risk.hip
+// has all five in one workgroup per b:
 //   1 eta     : add the partial updates (subject order, coalesced), block maxima
 //   2 scan_w  : w and its cumulative sum within each tile of sorted positions
 //   3 scan_q  : tile offsets of S (every workgroup scans the tile totals itself),
@@ -40,12 +41,16 @@ constexpr int kT = 256;  // threads per workgroup of every phase
 constexpr int kNW = kT / kWave;
 constexpr int kSub = 4 * kT;  // positions per sub-chunk of a tile (4 per thread)
 
+// A workgroup of the phases is kT threads; the small-problem launch runs several
+// tiles side by side in one workgroup, kT threads each.
+__device__ __forceinline__ int tid() { return threadIdx.x & (kT - 1); }
+
 __device__ __forceinline__ bool skip_b(const RiskArgs& a, int b) { return a.use_ctl && !a.ctl.active[b]; }
 
 // Block-wide exclusive scan of one double per thread; *total gets the block sum.
 __device__ inline double block_excl_scan(double v, double* sh, double* total)
 {
-    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    const int lane = threadIdx.x & (kWave - 1), wid = tid() / kWave;
     const double inc = wave_incl_scan(v, lane);
     if (lane == kWave - 1) sh[wid] = inc;
     __syncthreads();
@@ -62,7 +67,7 @@ __device__ inline double block_excl_scan(double v, double* sh, double* total)
 
 __device__ inline double block_sum(double v, double* sh)
 {
-    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    const int lane = threadIdx.x & (kWave - 1), wid = tid() / kWave;
     v = wave_sum(v);
     if (lane == 0) sh[wid] = v;
     __syncthreads();
@@ -75,7 +80,7 @@ __device__ inline double block_sum(double v, double* sh)
 
 __device__ inline double block_max(double v, double* sh)
 {
-    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    const int lane = threadIdx.x & (kWave - 1), wid = tid() / kWave;
     v = wave_max(v);
     if (lane == 0) sh[wid] = v;
     __syncthreads();
@@ -91,7 +96,7 @@ __device__ inline double block_max(double v, double* sh)
 __device__ inline void block_offsets(const double* __restrict__ v, int m, bool reverse, double* out, double* sh)
 {
     const int per = (m + kT - 1) / kT;
-    const int lo = threadIdx.x * per;
+    const int lo = tid() * per;
     double s = 0.0;
     for (int q = 0; q < per; ++q) {
         const int i = lo + q;
@@ -118,20 +123,22 @@ __device__ __forceinline__ void risk_eta_blk(const RiskArgs& a, int bx, int by, 
     const bool addp = a.part != nullptr && *a.nsel > 0;
     const bool copy = addp || a.eta_in_f32 || a.eta_in != a.eta;
     double m = -INFINITY;
-    const int64_t i0 = (int64_t)bx * kFinElems + threadIdx.x;
+    const int64_t i0 = (int64_t)bx * kFinElems + tid();
 #pragma unroll 4
     for (int e = 0; e < kFinElems / kT; ++e) {
         const int64_t i = i0 + (int64_t)e * kT;
         if (i >= n) break;
         double v = a.eta_in_f32 ? (double)static_cast<const float*>(a.eta_in)[bo + i]
                                 : static_cast<const double*>(a.eta_in)[bo + i];
-        if (addp)
+        if (addp) {
+#pragma unroll 8
             for (int c = 0; c < a.ncg; ++c) v += a.part[(int64_t)c * a.part_cstride + bo + i];
+        }
         if (copy) a.eta[bo + i] = v;
         m = fmax(m, v);
     }
     m = block_max(m, sh);
-    if (threadIdx.x == 0) a.bmax[(int64_t)b * a.nfin + bx] = m;
+    if (tid() == 0) a.bmax[(int64_t)b * a.nfin + bx] = m;
 }
 
 __device__ __forceinline__ void risk_scan_w_blk(const RiskArgs& a, int bx, int by, double* sh)
@@ -140,9 +147,9 @@ __device__ __forceinline__ void risk_scan_w_blk(const RiskArgs& a, int bx, int b
     if (skip_b(a, b)) return;
     const int64_t n = a.n, bo = (int64_t)b * n;
     double m = -INFINITY;
-    for (int q = threadIdx.x; q < a.nfin; q += kT) m = fmax(m, a.bmax[(int64_t)b * a.nfin + q]);
+    for (int q = tid(); q < a.nfin; q += kT) m = fmax(m, a.bmax[(int64_t)b * a.nfin + q]);
     m = block_max(m, sh);
-    if (bx == 0 && threadIdx.x == 0) a.mshift[b] = m;
+    if (bx == 0 && tid() == 0) a.mshift[b] = m;
     const int32_t* __restrict__ perm = a.ord.perm;
     const double* __restrict__ eta = a.eta + bo;
     double* __restrict__ w = a.w + bo;
@@ -151,7 +158,7 @@ __device__ __forceinline__ void risk_scan_w_blk(const RiskArgs& a, int bx, int b
     const int64_t t1 = min(n, t0 + a.tile);
     double carry = 0.0;
     for (int64_t base = t0; base < t1; base += kSub) {
-        const int64_t k0 = base + 4 * (int64_t)threadIdx.x;
+        const int64_t k0 = base + 4 * (int64_t)tid();
         double v[4];
         double ts = 0.0;
 #pragma unroll
@@ -171,7 +178,7 @@ __device__ __forceinline__ void risk_scan_w_blk(const RiskArgs& a, int bx, int b
         }
         carry += tot;
     }
-    if (threadIdx.x == 0) a.stot[(int64_t)b * a.ntile + bx] = carry;
+    if (tid() == 0) a.stot[(int64_t)b * a.ntile + bx] = carry;
 }
 
 __device__ __forceinline__ void risk_scan_q_blk(const RiskArgs& a, int bx, int by, double* sh, double* pre)
@@ -191,7 +198,7 @@ __device__ __forceinline__ void risk_scan_q_blk(const RiskArgs& a, int bx, int b
     const int64_t len = min(n, t0 + a.tile) - t0;
     double carry = 0.0, Lacc = 0.0;
     for (int64_t base = 0; base < len; base += kSub) {
-        const int64_t u0 = base + 4 * (int64_t)threadIdx.x;  // distance from the tile's last position
+        const int64_t u0 = base + 4 * (int64_t)tid();  // distance from the tile's last position
         double v[4];
         double ts = 0.0;
 #pragma unroll
@@ -218,7 +225,7 @@ __device__ __forceinline__ void risk_scan_q_blk(const RiskArgs& a, int bx, int b
         carry += tot;
     }
     Lacc = block_sum(Lacc, sh);
-    if (threadIdx.x == 0) {
+    if (tid() == 0) {
         a.qtot[(int64_t)b * a.ntile + bx] = carry;
         a.Lpart[(int64_t)b * a.ntile + bx] = Lacc;
     }
@@ -239,7 +246,7 @@ __device__ __forceinline__ void risk_resid_blk(const RiskArgs& a, int bx, int by
     const int64_t t0 = (int64_t)bx * a.tile;
     const int64_t t1 = min(n, t0 + a.tile);
     double sr = 0.0;
-    for (int64_t k = t0 + threadIdx.x; k < t1; k += kT) {
+    for (int64_t k = t0 + tid(); k < t1; k += kT) {
         const int64_t gs = gstart[k];
         const double c = T[gs] + suf[gs / a.tile];
         const double r = (ev[k] ? 1.0 : 0.0) - w[k] * c;
@@ -254,7 +261,7 @@ __device__ __forceinline__ void risk_resid_blk(const RiskArgs& a, int bx, int by
         if (a.r64) a.r64[bo + i] = r;
     }
     sr = block_sum(sr, sh);
-    if (threadIdx.x == 0) a.rpart[(int64_t)b * a.ntile + bx] = sr;
+    if (tid() == 0) a.rpart[(int64_t)b * a.ntile + bx] = sr;
 }
 
 // The objective of b's step and its stopping rule, one workgroup (every thread
@@ -263,9 +270,9 @@ __device__ __forceinline__ void stop_rule(const RiskArgs& a, int b, double L, do
 {
     const FitCtl& c = a.ctl;
     double l1 = 0.0;
-    for (int q = threadIdx.x; q < c.nblk; q += kT) l1 += c.l1[(int64_t)b * c.nblk + q];
+    for (int q = tid(); q < c.nblk; q += kT) l1 += c.l1[(int64_t)b * c.nblk + q];
     l1 = block_sum(l1, sh);
-    if (threadIdx.x == 0) {
+    if (tid() == 0) {
         if (c.l1cov) l1 += c.l1cov[b];
         const double f = -L + c.lam[b] * l1;
         const int k = c.kit[b];
@@ -295,13 +302,13 @@ __device__ __forceinline__ void risk_finish_blk(const RiskArgs& a, int bx, doubl
     const int b = bx;
     if (skip_b(a, b)) return;
     double L = 0.0, sr = 0.0;
-    for (int q = threadIdx.x; q < a.ntile; q += kT) {
+    for (int q = tid(); q < a.ntile; q += kT) {
         L += a.Lpart[(int64_t)b * a.ntile + q];
         sr += a.rpart[(int64_t)b * a.ntile + q];
     }
     L = block_sum(L, sh);
     sr = block_sum(sr, sh);
-    if (threadIdx.x == 0) {
+    if (tid() == 0) {
         a.L[b] = L;
         a.sumr[b] = sr;
     }

@@ -159,3 +159,44 @@ def test_dense_product_blocks(n, p, B, monkeypatch):
     beta[B // 2, p // 2] = float("nan")
     with pytest.raises(P.CoxError):
         cox.loss_grad(beta, want_grad=False)
+
+
+@pytest.mark.parametrize("n", [1, 2, 1023, 1024, 1025, 4095, 4096, 4097])
+@pytest.mark.parametrize("ties", [False, True])
+def test_small_risk_sets(n, ties):
+    """The risk-set phases in one launch (up to 4,096 subjects, four tiles of 1,024)
+    and just above in five: loss and adjoint in FP64 against the oracle's.  Both sum
+    at most n terms of one sign in FP64, so 1e-12 of the loss and of each residual's
+    parts (delta and w c, at most 1 + |r|) covers the rounding many times over."""
+    rng = np.random.Generator(np.random.PCG64(31 * n + ties))
+    time = rng.integers(1, 50, n).astype(float) if ties else rng.random(n)
+    event = (rng.random(n) < 0.6).astype(np.int32)
+    event[-1] = 1
+    eta = rng.normal(0, 1.5, (3, n))
+    cox = P.Cox(torch.zeros((1, (n + 15) // 16 * 16), device="cuda"), time, event, n=n, max_batch=3)
+    et = torch.from_numpy(eta).cuda().requires_grad_(True)
+    loss = P.BreslowNLL.apply(et, cox)
+    loss.sum().backward()
+    for b in range(3):
+        L, r = oracle.loglik(eta[b], time, event)
+        assert float(loss[b].detach()) == pytest.approx(-L, rel=1e-12, abs=1e-12 * n)
+        assert (np.abs(et.grad[b].cpu().numpy() + r) <= 1e-12 * (1 + np.abs(r))).all()
+
+
+@pytest.mark.parametrize("storage,p,B", [("f32", 40, 1), ("fp8", 127, 2), ("int8", 2100, 1), ("f32", 5000, 3),
+                                         ("fp8", 9000, 8)])
+def test_eta_update_stages(storage, p, B):
+    """The eta update's column groups staged through LDS, 128 columns at a time
+    with 8 loads in flight: lists of fewer columns than groups, of part stages and
+    of several stages per group, held to the parity tests' bars (1e-5 of max|beta|,
+    1e-6 in the objective) after steps that each hang on the one before."""
+    d = coxsim.genotype_problem(1500, p, 5, 0.3, 6000 + p, days=True)
+    cox, M = device_problem(d, storage, ldx=1504, max_batch=B)
+    lams = coxsim.lambda_grid(oracle.lambda_max(M, d.time, d.event), B + 1, 0.02)[1:]
+    sigma = 1.0 / (2.0 * (np.sqrt(d.n) + np.sqrt(d.p)) ** 2)
+    beta, _, obj, _ = cox.fit_path(lams, max_iter=20, tol=0.0, step=sigma)
+    beta = beta.cpu().numpy()
+    for b in range(B):
+        bo, tr, _, _ = oracle.fit(M, d.time, d.event, lams[b], sigma, max_iter=20)
+        assert np.abs(beta[b] - bo).max() <= 1e-5 * np.abs(bo).max()
+        assert obj[b] == pytest.approx(tr[-1], rel=1e-6)
