@@ -7,21 +7,20 @@
 // formed and summed in FP64, so the only rounding is in the order of the sums.
 //
 // One iteration (Section 5.1, the loop's order):
-//   W X'   (r x m)  nmf_wxt_kernel: workgroups over (256 rows of X, a split of
-//                   the columns); the 256 x 32 X tile and the r x 32 W tile of a
-//                   step pass through LDS into FP64 matrix-core tiles, the next
-//                   step's tiles loading into registers meanwhile (with aligned
-//                   rows, nmf_wxt_direct_kernel loads them straight into
-//                   registers).  The split partials are added by nmf_reduce_gram_kernel.
-//   W W'   (r x r)  the same launch, one workgroup per entry of the
-//                   upper triangle, fixed-order reduction.
+//   W X'   (r x m)  nmf_wxt_kernel: workgroups over (256 or 128 rows of X, a
+//                   split of the columns); a step's X tile of 32 columns and
+//                   r x 32 W tile pass through LDS into FP64 matrix-core
+//                   tiles, the next step's tiles loading into registers
+//                   meanwhile.  nmf_reduce_gram_kernel adds the split partials.
+//   W W'   (r x r)  the same launch, one workgroup per entry of the upper
+//                   triangle, fixed-order reduction.
 //   V' <- update    nmf_update_kernel, 4 threads per column of V': the r x r
 //                   product with W W', then the multiplicative update
 //                   V .* (X W') ./ (V W W' + eps) or the projected step
 //                   max(0, V - sigma (V W W' - X W')), sigma = 1/(2||W W'||_F^2 + eps).
-//   V' X   (r x n)  nmf_vtx_kernel: workgroups over (256 columns of X, a split
-//                   of the rows); a 32 x 256 X tile and the r x 32 V' tile, the
-//                   same way.
+//   V' X   (r x n)  nmf_vtx_kernel: workgroups over (256 or 128 columns of X, a
+//                   split of the rows); an X tile of 32 rows and the r x 32 V'
+//                   tile, the same way.
 //   V' V   (r x r), then the W update the same way with tau = 1/(2||V'V||_F^2 + eps).
 // Both passes over X read it once each; the r x r products and the updates
 // are O(r^2 (m + n)).
@@ -58,62 +57,90 @@ __device__ double block_sum256(double v, double* sh)
     return s;
 }
 
-typedef double v4d __attribute__((ext_vector_type(4)));
-
-// Both passes run on the FP64 matrix cores (v_mfma_f64_16x16x4f64: D = A B + C
-// with A 16 x 4, B 4 x 16, FP64 operands and accumulation).  Per lane: A holds
-// (row lane % 16, k lane / 16), B holds (k lane / 16, column lane % 16), and D
-// holds rows lane / 16 + 4 v, v < 4, of column lane % 16 (interleaved, unlike
-// the int8 instruction's 4 (lane / 16) + v; checked on the device).  The rank
-// is padded to MT tiles of 16; a wavefront owns 64 rows (or columns) of X, 4 N
-// tiles.
-__device__ __forceinline__ v4d mfma_f64(double a, double b, v4d c)
+// Both passes run on the FP64 matrix cores with v_mfma_f64_4x4x4f64, four
+// independent 4 x 4 x 4 products: per lane, block l / 4 mod 4 holds A (row l % 4,
+// k l / 16), B (k l / 16, column l % 4) and D (row l / 16, column l % 4).  Every
+// block takes the same four rows of the factor as A, so an instruction multiplies
+// 4 rank rows by 16 rows (or columns) of X, lane % 16, over 4 steps of the inner
+// dimension, and the rank is padded to QT quads of 4.  v_mfma_f64_16x16x4f64 does
+// 4 times the work an instruction, but sustained 44 TFLOP/s here, 31 with one
+// wavefront on a SIMD, against 72 and 67, and pads the rank to 16 (r = 20 did the
+// work of 32).  At 10,000 x 10,000, r = 20, W X' took 153 us and V' X 148 with it;
+// they take 127 and 120 (r = 5: 91 and 74; r = 60: 283 and 260).  Reading X alone
+// takes 82 us at the rate of a large copy and the products at r = 60 167 us at
+// 72 TFLOP/s: a pass is bound by X up to about r = 20 and by the matrix cores, fed
+// through LDS, above.
+__device__ __forceinline__ double mfma_f64(double a, double b, double c)
 {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
 }
 
+// N tiles of 16 rows (or columns) of X per wavefront: 4 up to rank 32, 2 above, where
+// 4 would take the accumulators past two wavefronts per SIMD (at 10,000 x 10,000, r = 60
+// one wavefront per SIMD made a pass 315 us).  A workgroup of 4 wavefronts owns 64
+// times as many.
+constexpr int n_tiles(int QT) { return QT <= 8 ? 4 : 2; }
+int rows_per_wg(int r) { return 64 * n_tiles((r + 3) / 4); }
+
+// LDS strides of the tiles.  A read of X takes 16 rows (or columns) by 4 inner
+// positions, one of a factor 4 rows by 4 positions for every block.  With rows of
+// 36 floats for the X tile of W X', 16 past a multiple of 64 floats for that of
+// V' X and 36 doubles for a factor tile, a read's addresses fall on distinct banks.
+constexpr int kXRow = kTJ + 4;
+template <int NT>
+constexpr int x_col() { return 64 * NT + 16; }
+constexpr int kFRow = 36;
+static_assert(kTJ <= kFRow && kTI <= kFRow, "a factor tile's row holds a step");
+
 // part[split][a][i] = sum over the split's columns j of W[a][j] X[i][j]:
-// M = a (the rank), N = i (256 rows of X per workgroup), K = j
-template <int MT>
-__global__ __launch_bounds__(kT) void nmf_wxt_kernel(const float* __restrict__ X, int64_t m, int64_t n, int64_t ldx,
+// M = a (the rank), N = i (64 NT rows of X per workgroup), K = j.  VEC: rows of X and
+// of W start 16-byte aligned (X aligned, ldx a multiple of 4; W aligned, n even),
+// and whole 16-byte pieces are loaded.
+template <int QT, bool VEC>
+__global__ __launch_bounds__(kT, 2) void nmf_wxt_kernel(const float* __restrict__ X, int64_t m, int64_t n, int64_t ldx,
                                                      int r, const double* __restrict__ W, int64_t cols,
                                                      double* __restrict__ part)
 {
-    constexpr int R = 16 * MT;
-    __shared__ float Xs[kT][kTJ + 1];
-    __shared__ double Ws[R][kTJ + 1];
+    constexpr int R = 4 * QT, NT = n_tiles(QT), ROWS = 64 * NT;
+    __shared__ __attribute__((aligned(16))) float Xs[ROWS][kXRow];
+    __shared__ __attribute__((aligned(16))) double Ws[R][kFRow];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const int64_t i0 = (int64_t)blockIdx.x * kT;
+    const int64_t i0 = (int64_t)blockIdx.x * ROWS;
     const int64_t j0 = (int64_t)blockIdx.y * cols, j1 = min(n, j0 + cols);
-    v4d acc[MT][4];
+    double acc[QT][NT];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt) acc[mt][nt] = v4d{0.0, 0.0, 0.0, 0.0};
+        for (int nt = 0; nt < NT; ++nt) acc[qt][nt] = 0.0;
     // the next step's tiles are loaded into registers while the current one is
     // multiplied out of LDS
-    constexpr int XE = kT * kTJ / (4 * kT);
-    constexpr int WE = (R * kTJ + kT - 1) / kT;
-    float xr[XE][4];
-    double wr[WE];
+    constexpr int XE = ROWS * kTJ / (4 * kT);
+    constexpr int WE = (R * kTJ / 2 + kT - 1) / kT;  // pairs of W
+    float4 xr[XE];
+    double2 wr[WE];
     auto fetch = [&](int64_t js) {
 #pragma unroll
         for (int e = 0; e < XE; ++e) {
             const int li = threadIdx.x + kT * e;
-            const int row = li / (kTJ / 4), c4 = (li % (kTJ / 4)) * 4;
-            const int64_t i = i0 + row;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int64_t j = js + c4 + q;
-                xr[e][q] = (i < m && j < j1) ? X[i * ldx + j] : 0.0f;
-            }
+            const int64_t i = i0 + li / (kTJ / 4), j = js + (li % (kTJ / 4)) * 4;
+            const float* x = X + i * ldx + j;
+            if (VEC && i < m && j + 4 <= j1)
+                xr[e] = *reinterpret_cast<const float4*>(x);
+            else
+                xr[e] = make_float4(i < m && j < j1 ? x[0] : 0.0f, i < m && j + 1 < j1 ? x[1] : 0.0f,
+                                    i < m && j + 2 < j1 ? x[2] : 0.0f, i < m && j + 3 < j1 ? x[3] : 0.0f);
         }
 #pragma unroll
         for (int e = 0; e < WE; ++e) {
             const int li = threadIdx.x + kT * e;
-            const int a = li / kTJ, jj = li % kTJ;
-            const int64_t j = js + jj;
-            wr[e] = (li < R * kTJ && a < r && j < j1) ? W[(int64_t)a * n + j] : 0.0;
+            const int a = li / (kTJ / 2);
+            const int64_t j = js + 2 * (li % (kTJ / 2));
+            const double* w = W + (int64_t)a * n + j;
+            const bool ok = li < R * kTJ / 2 && a < r;
+            if (VEC && ok && j + 2 <= j1)
+                wr[e] = *reinterpret_cast<const double2*>(w);
+            else
+                wr[e] = double2{ok && j < j1 ? w[0] : 0.0, ok && j + 1 < j1 ? w[1] : 0.0};
         }
     };
     if (j0 < j1) fetch(j0);
@@ -121,71 +148,68 @@ __global__ __launch_bounds__(kT) void nmf_wxt_kernel(const float* __restrict__ X
 #pragma unroll
         for (int e = 0; e < XE; ++e) {
             const int li = threadIdx.x + kT * e;
-            const int row = li / (kTJ / 4), c4 = (li % (kTJ / 4)) * 4;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) Xs[row][c4 + q] = xr[e][q];
+            *reinterpret_cast<float4*>(&Xs[li / (kTJ / 4)][(li % (kTJ / 4)) * 4]) = xr[e];
         }
 #pragma unroll
         for (int e = 0; e < WE; ++e) {
             const int li = threadIdx.x + kT * e;
-            if (li < R * kTJ) Ws[li / kTJ][li % kTJ] = wr[e];
+            if (li < R * kTJ / 2) *reinterpret_cast<double2*>(&Ws[li / (kTJ / 2)][2 * (li % (kTJ / 2))]) = wr[e];
         }
         __syncthreads();
         if (js + kTJ < j1) fetch(js + kTJ);
 #pragma unroll
         for (int kk = 0; kk < kTJ; kk += 4) {
             const int k = kk + (lane >> 4);
-            double av[MT], bv[4];
+            double av[QT], bv[NT];
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) av[mt] = Ws[mt * 16 + (lane & 15)][k];
+            for (int qt = 0; qt < QT; ++qt) av[qt] = Ws[qt * 4 + (lane & 3)][k];
 #pragma unroll
-            for (int nt = 0; nt < 4; ++nt) bv[nt] = (double)Xs[wid * 64 + nt * 16 + (lane & 15)][k];
+            for (int nt = 0; nt < NT; ++nt) bv[nt] = (double)Xs[wid * (16 * NT) + nt * 16 + (lane & 15)][k];
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
+            for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
-                for (int nt = 0; nt < 4; ++nt) acc[mt][nt] = mfma_f64(av[mt], bv[nt], acc[mt][nt]);
+                for (int nt = 0; nt < NT; ++nt) acc[qt][nt] = mfma_f64(av[qt], bv[nt], acc[qt][nt]);
         }
         __syncthreads();
     }
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int a = mt * 16 + (lane >> 4) + 4 * v;
-                const int64_t i = i0 + wid * 64 + nt * 16 + (lane & 15);
-                if (a < r && i < m) part[((int64_t)blockIdx.y * r + a) * m + i] = acc[mt][nt][v];
-            }
+        for (int nt = 0; nt < NT; ++nt) {
+            const int a = qt * 4 + (lane >> 4);
+            const int64_t i = i0 + wid * (16 * NT) + nt * 16 + (lane & 15);
+            if (a < r && i < m) part[((int64_t)blockIdx.y * r + a) * m + i] = acc[qt][nt];
+        }
 }
 
 // part[split][a][j] = sum over the split's rows i of Vt[a][i] X[i][j]:
-// M = a, N = j (256 columns of X per workgroup), K = i
-template <int MT>
-__global__ __launch_bounds__(kT) void nmf_vtx_kernel(const float* __restrict__ X, int64_t m, int64_t n, int64_t ldx,
+// M = a, N = j (64 NT columns of X per workgroup), K = i
+template <int QT>
+__global__ __launch_bounds__(kT, 2) void nmf_vtx_kernel(const float* __restrict__ X, int64_t m, int64_t n, int64_t ldx,
                                                      int r, const double* __restrict__ Vt, int64_t rows,
                                                      double* __restrict__ part)
 {
-    constexpr int R = 16 * MT;
-    __shared__ float Xs[kTI][kT + 4];
-    __shared__ double Vs[R][kTI + 1];
+    constexpr int R = 4 * QT, NT = n_tiles(QT), COLS = 64 * NT, RPT = kT / COLS;
+    __shared__ float Xs[kTI][x_col<NT>()];
+    __shared__ double Vs[R][kFRow];
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const int64_t jb = (int64_t)blockIdx.x * kT;
+    const int64_t jb = (int64_t)blockIdx.x * COLS;
     const int64_t i0 = (int64_t)blockIdx.y * rows, i1 = min(m, i0 + rows);
-    v4d acc[MT][4];
+    double acc[QT][NT];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt) acc[mt][nt] = v4d{0.0, 0.0, 0.0, 0.0};
-    // the next step's tiles (kTI rows x 256 columns of X, one column per thread,
+        for (int nt = 0; nt < NT; ++nt) acc[qt][nt] = 0.0;
+    // the next step's tiles (kTI rows x COLS columns of X, one column per thread,
     // and the r x kTI tile of V') are loaded into registers during this one
     constexpr int VE = (R * kTI + kT - 1) / kT;
-    float xr[kTI];
+    const int row0 = RPT == 1 ? 0 : threadIdx.x / COLS, col = RPT == 1 ? threadIdx.x : threadIdx.x % COLS;
+    float xr[kTI / RPT];
     double vr[VE];
     auto fetch = [&](int64_t is) {
 #pragma unroll
-        for (int ii = 0; ii < kTI; ++ii) {
-            const int64_t i = is + ii, j = jb + threadIdx.x;
+        for (int ii = 0; ii < kTI / RPT; ++ii) {
+            const int64_t i = is + RPT * ii + row0, j = jb + col;
             xr[ii] = (i < i1 && j < n) ? X[i * ldx + j] : 0.0f;
         }
 #pragma unroll
@@ -199,7 +223,7 @@ __global__ __launch_bounds__(kT) void nmf_vtx_kernel(const float* __restrict__ X
     if (i0 < i1) fetch(i0);
     for (int64_t is = i0; is < i1; is += kTI) {
 #pragma unroll
-        for (int ii = 0; ii < kTI; ++ii) Xs[ii][threadIdx.x] = xr[ii];
+        for (int ii = 0; ii < kTI / RPT; ++ii) Xs[RPT * ii + row0][col] = xr[ii];
 #pragma unroll
         for (int e = 0; e < VE; ++e) {
             const int li = threadIdx.x + kT * e;
@@ -210,133 +234,26 @@ __global__ __launch_bounds__(kT) void nmf_vtx_kernel(const float* __restrict__ X
 #pragma unroll
         for (int kk = 0; kk < kTI; kk += 4) {
             const int k = kk + (lane >> 4);
-            double av[MT], bv[4];
+            double av[QT], bv[NT];
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) av[mt] = Vs[mt * 16 + (lane & 15)][k];
+            for (int qt = 0; qt < QT; ++qt) av[qt] = Vs[qt * 4 + (lane & 3)][k];
 #pragma unroll
-            for (int nt = 0; nt < 4; ++nt) bv[nt] = (double)Xs[k][wid * 64 + nt * 16 + (lane & 15)];
+            for (int nt = 0; nt < NT; ++nt) bv[nt] = (double)Xs[k][wid * (16 * NT) + nt * 16 + (lane & 15)];
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
+            for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
-                for (int nt = 0; nt < 4; ++nt) acc[mt][nt] = mfma_f64(av[mt], bv[nt], acc[mt][nt]);
+                for (int nt = 0; nt < NT; ++nt) acc[qt][nt] = mfma_f64(av[qt], bv[nt], acc[qt][nt]);
         }
         __syncthreads();
     }
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int a = mt * 16 + (lane >> 4) + 4 * v;
-                const int64_t j = jb + wid * 64 + nt * 16 + (lane & 15);
-                if (a < r && j < n) part[((int64_t)blockIdx.y * r + a) * n + j] = acc[mt][nt][v];
-            }
-}
-
-// W X' with both operands loaded straight from memory into registers, no
-// LDS: used when the rows of X start 16-byte aligned (X aligned, ldx a
-// multiple of 4) and so do the rows of W (aligned, n even), as at the paper's
-// 10,000 x 10,000; otherwise the kernel above.  Each lane loads GL
-// consecutive columns, and the s-th product of a step puts column GL q + s of
-// the step in k-slot q (q = lane / 16) -- one permutation shared by both
-// operands, so the products pair up as in the plain sum.  The next step's
-// values load while the current ones are multiplied.  (The same form of V' X,
-// with 16-byte pieces of 4 columns per row, measured slower than the LDS
-// kernel: 0.19 against 0.15 ms at 10,000 x 10,000, r = 20.)
-
-// part[split][a][i] = sum over the split's columns j of W[a][j] X[i][j].  A
-// wavefront owns 64 rows of X (4 N tiles) and all MT rank tiles; a step covers
-// 4 GL columns; lane (c, q) reads columns js + GL q .. + GL - 1 of X row
-// ib + 16 nt + c and of W row 16 mt + c.  Rows of X past m are read from row
-// m - 1 (their outputs are not stored), W rows past r and columns past the
-// split give 0.
-template <int MT, int GL>
-__global__ __launch_bounds__(kT) void nmf_wxt_direct_kernel(const float* __restrict__ X, int64_t m, int64_t n,
-                                                            int64_t ldx, int r, const double* __restrict__ W,
-                                                            int64_t cols, double* __restrict__ part)
-{
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6, c = lane & 15, q = lane >> 4;
-    const int64_t ib = (int64_t)blockIdx.x * kT + wid * 64;
-    const int64_t j0 = (int64_t)blockIdx.y * cols, j1 = min(n, j0 + cols);
-    const float* xr[4];
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) xr[nt] = X + min(ib + nt * 16 + c, m - 1) * ldx;
-    const double* wr[MT];
-    bool wok[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        const int a = mt * 16 + c;
-        wok[mt] = a < r;
-        wr[mt] = W + (int64_t)min(a, r - 1) * n;
-    }
-    v4d acc[MT][4];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) acc[mt][nt] = v4d{0.0, 0.0, 0.0, 0.0};
-    float nx[4][GL];
-    double nw[MT][GL];
-    auto fetch = [&](int64_t js) {
-        const int64_t j = js + GL * q;
-        if (js + 4 * GL <= j1) {
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-                for (int e = 0; e < GL; e += 4) {
-                    const float4 v = *reinterpret_cast<const float4*>(xr[nt] + j + e);
-                    nx[nt][e] = v.x, nx[nt][e + 1] = v.y, nx[nt][e + 2] = v.z, nx[nt][e + 3] = v.w;
-                }
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                for (int e = 0; e < GL; e += 2) {
-                    const double2 v = wok[mt] ? *reinterpret_cast<const double2*>(wr[mt] + j + e) : double2{0.0, 0.0};
-                    nw[mt][e] = v.x, nw[mt][e + 1] = v.y;
-                }
-        } else {
-#pragma unroll
-            for (int e = 0; e < GL; ++e) {
-                const bool in = j + e < j1;
-                const int64_t jc = in ? j + e : j0;
-#pragma unroll
-                for (int nt = 0; nt < 4; ++nt) nx[nt][e] = xr[nt][jc];
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) nw[mt][e] = (in && wok[mt]) ? wr[mt][jc] : 0.0;
-            }
+        for (int nt = 0; nt < NT; ++nt) {
+            const int a = qt * 4 + (lane >> 4);
+            const int64_t j = jb + wid * (16 * NT) + nt * 16 + (lane & 15);
+            if (a < r && j < n) part[((int64_t)blockIdx.y * r + a) * n + j] = acc[qt][nt];
         }
-    };
-    if (j0 < j1) fetch(j0);
-    for (int64_t js = j0; js < j1; js += 4 * GL) {
-        float cx[4][GL];
-        double cw[MT][GL];
-#pragma unroll
-        for (int e = 0; e < GL; ++e) {
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) cx[nt][e] = nx[nt][e];
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) cw[mt][e] = nw[mt][e];
-        }
-        if (js + 4 * GL < j1) fetch(js + 4 * GL);
-#pragma unroll
-        for (int e = 0; e < GL; ++e)
-#pragma unroll
-            for (int nt = 0; nt < 4; ++nt) {
-                const double b = (double)cx[nt][e];
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) acc[mt][nt] = mfma_f64(cw[mt][e], b, acc[mt][nt]);
-            }
-    }
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int a = mt * 16 + q + 4 * v;
-                const int64_t i = ib + nt * 16 + c;
-                if (a < r && i < m) part[((int64_t)blockIdx.y * r + a) * m + i] = acc[mt][nt][v];
-            }
 }
 
 // num[t] = sum over splits of part[split][t], t < count, in split order: workgroup bx of nred
@@ -497,9 +414,6 @@ __global__ __launch_bounds__(kT) void nmf_objective_kernel(const double* __restr
     if (threadIdx.x == 0) f[0] = scal[0] - 2.0 * inner + c;
 }
 
-// The rank padded to whole 16-row matrix-core tiles.
-int rpad(int r) { return (r + 15) / 16 * 16; }
-
 inline unsigned grid_for(int64_t m) { return (unsigned)min((int64_t)8192, max((int64_t)1, (m + kT - 1) / kT)); }
 
 }  // namespace
@@ -573,16 +487,12 @@ void nmark(nmf_ctx* c, int ph)
     c->tev[ph].push_back(e);
 }
 
-// V'X split partials and V'V of the current V'
-// the rows of X and of W start 16-byte aligned: W X' loads straight from memory
-bool nmf_direct(const nmf_ctx* c, const double* W)
+// the rows of X and of W start 16-byte aligned: W X' loads whole 16-byte pieces
+bool nmf_aligned(const nmf_ctx* c, const double* W)
 {
     return reinterpret_cast<uintptr_t>(c->X) % 16 == 0 && c->ldx % 4 == 0 && c->n % 2 == 0 &&
            reinterpret_cast<uintptr_t>(W) % 16 == 0;
 }
-
-// columns per lane in a step of the direct W X' pass
-constexpr int direct_gl(int R) { return R <= 16 ? 8 : 4; }
 
 // num (r x len) from the split partials, G (r x r) from the factor F (r x flen)
 void nmf_reduce_gram(nmf_ctx* c, int nsplit, int64_t len, const double* F, int64_t flen, double* G)
@@ -593,62 +503,60 @@ void nmf_reduce_gram(nmf_ctx* c, int nsplit, int64_t len, const double* F, int64
                        c->num, (int)nred, F, c->r, flen, G);
 }
 
-template <int R>
+template <int QT>
 void nmf_vtx_gram(nmf_ctx* c, const double* Vt)
 {
-    const int r = c->r;
-    const unsigned gn = (unsigned)((c->n + kT - 1) / kT);
+    const unsigned gn = (unsigned)((c->n + 64 * n_tiles(QT) - 1) / (64 * n_tiles(QT)));
     nmark(c, 1);
-    hipLaunchKernelGGL((nmf_vtx_kernel<R / 16>), dim3(gn, c->ns_vtx), dim3(kT), 0, c->stream, c->X, c->m, c->n,
-                       c->ldx, r, Vt, c->rows, c->part);
+    hipLaunchKernelGGL(nmf_vtx_kernel<QT>, dim3(gn, c->ns_vtx), dim3(kT), 0, c->stream, c->X, c->m, c->n, c->ldx, c->r,
+                       Vt, c->rows, c->part);
     nmark(c, 1);
     nmf_reduce_gram(c, c->ns_vtx, c->n, Vt, c->m, c->VtV);
 }
 
 template <int R>
+void nmf_update(nmf_ctx* c, double* F, int64_t len, const double* G, int algo, double eps)
+{
+    hipLaunchKernelGGL(nmf_update_kernel<R>, dim3((unsigned)((len + kUC - 1) / kUC)), dim3(kT), 0, c->stream, F, c->r,
+                       len, c->num, G, algo, eps);
+}
+
+template <int QT>
 hipError_t nmf_iteration(nmf_ctx* c, int algo, double eps, double* Vt, double* W)
 {
-    const int r = c->r;
-    const unsigned gm = (unsigned)((c->m + kT - 1) / kT);
+    constexpr int R = (4 * QT + 15) / 16 * 16;  // the update's rank, padded to 16
+    const unsigned gm = (unsigned)((c->m + 64 * n_tiles(QT) - 1) / (64 * n_tiles(QT)));
     nmark(c, 0);
-    if (nmf_direct(c, W))
-        hipLaunchKernelGGL((nmf_wxt_direct_kernel<R / 16, direct_gl(R)>), dim3(gm, c->ns_wxt), dim3(kT), 0, c->stream,
-                           c->X, c->m, c->n, c->ldx, r, W, c->cols, c->part);
+    if (nmf_aligned(c, W))
+        hipLaunchKernelGGL((nmf_wxt_kernel<QT, true>), dim3(gm, c->ns_wxt), dim3(kT), 0, c->stream, c->X, c->m, c->n,
+                           c->ldx, c->r, W, c->cols, c->part);
     else
-        hipLaunchKernelGGL((nmf_wxt_kernel<R / 16>), dim3(gm, c->ns_wxt), dim3(kT), 0, c->stream, c->X, c->m, c->n,
-                           c->ldx, r, W, c->cols, c->part);
+        hipLaunchKernelGGL((nmf_wxt_kernel<QT, false>), dim3(gm, c->ns_wxt), dim3(kT), 0, c->stream, c->X, c->m, c->n,
+                           c->ldx, c->r, W, c->cols, c->part);
     nmark(c, 0);
     nmf_reduce_gram(c, c->ns_wxt, c->m, W, c->n, c->WWt);
-    hipLaunchKernelGGL((nmf_update_kernel<R>), dim3((unsigned)((c->m + kUC - 1) / kUC)), dim3(kT), 0, c->stream, Vt, r,
-                       c->m, c->num, c->WWt, algo, eps);
-    nmf_vtx_gram<R>(c, Vt);
-    hipLaunchKernelGGL((nmf_update_kernel<R>), dim3((unsigned)((c->n + kUC - 1) / kUC)), dim3(kT), 0, c->stream, W, r,
-                       c->n, c->num, c->VtV, algo, eps);
+    nmf_update<R>(c, Vt, c->m, c->WWt, algo, eps);
+    nmf_vtx_gram<QT>(c, Vt);
+    nmf_update<R>(c, W, c->n, c->VtV, algo, eps);
     return hipGetLastError();
 }
 
-template <int R>
+// iters iterations, or V'X and V'V alone, with the kernels of rank quads QT = ceil(r / 4) <= 16
+template <int QT = 1>
 hipError_t nmf_dispatch(nmf_ctx* c, int algo, double eps, double* Vt, double* W, int iters, bool vtx_only)
 {
+    if constexpr (QT < NMF_MAX_RANK / 4) {
+        if (c->r > 4 * QT) return nmf_dispatch<QT + 1>(c, algo, eps, Vt, W, iters, vtx_only);
+    }
     if (vtx_only) {
-        nmf_vtx_gram<R>(c, Vt);
+        nmf_vtx_gram<QT>(c, Vt);
         return hipGetLastError();
     }
     for (int k = 0; k < iters; ++k) {
-        const hipError_t e = nmf_iteration<R>(c, algo, eps, Vt, W);
+        const hipError_t e = nmf_iteration<QT>(c, algo, eps, Vt, W);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
-}
-
-hipError_t nmf_dispatch_r(nmf_ctx* c, int algo, double eps, double* Vt, double* W, int iters, bool vtx_only)
-{
-    switch (rpad(c->r)) {
-    case 16: return nmf_dispatch<16>(c, algo, eps, Vt, W, iters, vtx_only);
-    case 32: return nmf_dispatch<32>(c, algo, eps, Vt, W, iters, vtx_only);
-    case 48: return nmf_dispatch<48>(c, algo, eps, Vt, W, iters, vtx_only);
-    default: return nmf_dispatch<64>(c, algo, eps, Vt, W, iters, vtx_only);
-    }
 }
 
 }  // namespace
@@ -675,7 +583,7 @@ cox_status nmf_setup(nmf_ctx** out, const float* X, int64_t m, int64_t n, int64_
     c->ldx = ldx;
     c->r = r;
     // split the inner dimension so each pass has several workgroups per CU
-    const int64_t gm = (m + kT - 1) / kT, gn = (n + kT - 1) / kT;
+    const int64_t rw = rows_per_wg(r), gm = (m + rw - 1) / rw, gn = (n + rw - 1) / rw;
     c->ns_wxt = (int)std::max<int64_t>(1, std::min<int64_t>((n + kTJ - 1) / kTJ, (1024 + gm - 1) / gm));
     c->ns_vtx = (int)std::max<int64_t>(1, std::min<int64_t>((m + kTI - 1) / kTI, (1024 + gn - 1) / gn));
     c->cols = ((n + c->ns_wxt - 1) / c->ns_wxt + kTJ - 1) / kTJ * kTJ;
@@ -730,12 +638,12 @@ cox_status nmf_run(nmf_ctx* c, int32_t algo, int32_t iters, double eps, double* 
     if ((algo != NMF_MULTIPLICATIVE && algo != NMF_APG) || iters < 0 || !(eps >= 0) || !std::isfinite(eps) || !Vt ||
         !W)
         return nfail(c, COX_ERR_INVALID_ARG, "bad nmf_run arguments");
-    NCHK(nmf_dispatch_r(c, algo, eps, Vt, W, iters, false), "NMF iteration");
+    NCHK(nmf_dispatch(c, algo, eps, Vt, W, iters, false), "NMF iteration");
     if (obj) {
         const int r = c->r;
         // V'X and V'V of the final V are still in the workspace after an
         // iteration; with none, form them
-        if (iters == 0) NCHK(nmf_dispatch_r(c, algo, eps, Vt, W, 0, true), "V'X");
+        if (iters == 0) NCHK(nmf_dispatch(c, algo, eps, Vt, W, 0, true), "V'X");
         const int ninner = (int)std::min<int64_t>(kInner, ((int64_t)r * c->n + 1023) / 1024);
         hipLaunchKernelGGL(nmf_inner_gram_kernel, dim3((unsigned)(ninner + r * (r + 1) / 2)), dim3(kT), 0, c->stream, W,
                            r, c->n, c->num, c->ipart, ninner, c->WWt);

@@ -200,3 +200,24 @@ def test_eta_update_stages(storage, p, B):
         bo, tr, _, _ = oracle.fit(M, d.time, d.event, lams[b], sigma, max_iter=20)
         assert np.abs(beta[b] - bo).max() <= 1e-5 * np.abs(bo).max()
         assert obj[b] == pytest.approx(tr[-1], rel=1e-6)
+
+
+@pytest.mark.parametrize("r", [1, 4, 13, 21, 24, 29, 32, 33, 46, 51, 56, 64])
+@pytest.mark.parametrize("m,n,pad", [(65, 130, 2), (255, 513, 0), (1, 5, 0), (514, 256, 0)])
+def test_nmf_rank_quads(r, m, n, pad):
+    """Every instance of the NMF contractions (1 to 16 quads of the rank; 64, 128
+    or 256 rows or columns per workgroup with ragged ends; aligned rows and not).
+    The multiplicative update only adds and multiplies nonnegative FP64 numbers and
+    divides once, so three iterations from positive factors carry at most
+    3 (2 (m + n) + 2 r + 3) roundings of 1.2e-16, under 2e-12 here."""
+    rng = np.random.default_rng(100 * r + m)
+    X = rng.random((m, n)).astype(np.float32)
+    Xd = torch.zeros((m, n + pad), dtype=torch.float32)
+    Xd[:, :n] = torch.from_numpy(X)
+    Vt0, W0 = 0.1 + rng.random((r, m)), 0.1 + rng.random((r, n))
+    Vt, W = torch.from_numpy(Vt0).cuda(), torch.from_numpy(W0).cuda()
+    nmf = P.NMF(Xd.cuda(), r, n=n)
+    nmf.run(Vt, W, P.NMF_MULTIPLICATIVE, 3)
+    Vo, Wo, _ = oracle.nmf_run(X, Vt0, W0, P.NMF_MULTIPLICATIVE, 3)
+    np.testing.assert_allclose(Vt.cpu().numpy(), Vo, rtol=1e-11)
+    np.testing.assert_allclose(W.cpu().numpy(), Wo, rtol=1e-11)
