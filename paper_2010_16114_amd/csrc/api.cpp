@@ -1714,7 +1714,7 @@ cox_status cox_refit(cox_ctx* c, const int64_t* cols, int32_t m, const cox_refit
         if (!std::isfinite(coef[a])) return fail(c, COX_ERR_INVALID_ARG, "coef must be finite");
 
     const int64_t G = c->n_egroups, ldd = refit_ld(n), ldp = refit_ld(G);
-    const int nc1 = gram_chunks(n, M), nc2 = gram_chunks(G, M), nch = scan_chunks(n), nrb = refit_row_blocks(n);
+    const int nc1 = gram_chunks(n, M), nc2 = gram_chunks(G, M), nch = scan_chunks(n);
     const size_t MM = (size_t)M * M;
     Scratch w;
     float* D;
@@ -1724,7 +1724,7 @@ cox_status cox_refit(cox_ctx* c, const int64_t* cols, int32_t m, const cox_refit
     if (!(w.get(&D, (size_t)M * ldd) && w.get(&Pg, (size_t)(M + 1) * ldp) && w.get(&wg, ldp) && w.get(&wt, ldd) &&
           w.get(&rs, n) &&
           w.get(&csum, (size_t)(M + 1) * nch) && w.get(&p1, nc1 * MM) && w.get(&p2, nc2 * MM) && w.get(&H, MM) &&
-          w.get(&g, M) && w.get(&d, M) && w.get(&b, M) && w.get(&bt, M) && w.get(&gpart, (size_t)nrb * M) &&
+          w.get(&g, M) && w.get(&d, M) && w.get(&b, M) && w.get(&bt, M) && w.get(&gpart, (size_t)nch * M) &&
           w.get(&sed, M) && w.get(&pvd, M) && w.get(&colsd, std::max(m, 1)) && w.get(&okd, 1)))
         return fail(c, COX_ERR_OUT_OF_MEMORY, "refit workspace");
 
@@ -1766,7 +1766,7 @@ cox_status cox_refit(cox_ctx* c, const int64_t* cols, int32_t m, const cox_refit
     bool converged = false;
     int it = 0;
     for (;; ++it) {
-        HIPCHK(launch_refit_grad(D, ldd, n, M, c->perm, c->r64, rs, gpart, g, c->stream), "D' r");
+        HIPCHK(launch_refit_grad(D, ldd, n, M, c->perm, c->r64, c->w, rs, gpart, csum, g, c->stream), "D' r");
         STCHK(d2h(c, gh.data(), g, sizeof(double) * M));
         double gmax = 0.0;
         for (double v : gh) gmax = std::max(gmax, std::fabs(v));

@@ -21,7 +21,6 @@ constexpr int kMaxHist = 33;                        // lag <= 32
 constexpr int kCovRows = 8192;                      // rows per workgroup of Z' r
 constexpr int kMaxCov = 64;                         // covariates in the dense block beside X
 constexpr int kMaxRefit = 1024;                     // columns of an unpenalised refit
-constexpr int kRefitRows = 8192;                    // rows per workgroup of the refit's D' r
 constexpr int kGramChunks = 64;                     // most row chunks of a refit Gram term
 
 // Read-only description of X as the kernels see it.
@@ -287,11 +286,11 @@ hipError_t launch_gather_z(const float* Z, int64_t ldz, int64_t n, int q, const 
 // eta[perm[k]] = sum_a D[a][k] b[a] over M columns
 hipError_t launch_refit_eta(const float* D, int64_t ldd, int64_t n, int M, const int32_t* perm, const double* b,
                             double* eta, hipStream_t s);
-int refit_row_blocks(int64_t n);
-// g = D' r with r in subject order (rs [n]: r in sorted order, written;
-// part: [refit_row_blocks(n)][M] scratch)
+// g = D' r with r in subject order (rs [n]: r in sorted order, written; part:
+// [M][scan_chunks(n)] scratch), and csum [M + 1][scan_chunks(n)]: the chunk sums of
+// w D and w (w sorted) that the Hessian at this state starts its scans from
 hipError_t launch_refit_grad(const float* D, int64_t ldd, int64_t n, int M, const int32_t* perm, const double* r,
-                             double* rs, double* part, double* g, hipStream_t s);
+                             const double* w, double* rs, double* part, double* csum, double* g, hipStream_t s);
 // row chunks of a Gram term over `rows` rows and M columns; risk-set scan chunks
 int gram_chunks(int64_t rows, int M);
 int scan_chunks(int64_t n);
@@ -310,7 +309,7 @@ struct RefitHess {
     const int32_t* egcnt;
     int64_t G, ldp;
     double* wt;     // [ldd]
-    double* csum;   // [M + 1][scan_chunks(n)]
+    const double* csum;  // [M + 1][scan_chunks(n)], from launch_refit_grad at the same state
     double* P;      // [M + 1][ldp], ldp >= refit_ld(G)
     double* wg;     // [ldp]
     double* part1;  // [gram_chunks(n, M)][M][M]

@@ -82,16 +82,38 @@ __global__ __launch_bounds__(kT) void gather_z_kernel(const float* __restrict__ 
         D[(int64_t)a * ldd + k] = k < n ? Z[(int64_t)a * ldz + perm[k]] : 0.0f;
 }
 
-// eta[perm[k]] = sum_a D[a][k] b[a]  (eta in subject order)
+// eta[perm[k]] = sum_a D[a][k] b[a]  (eta in subject order).  A workgroup takes 256
+// positions, a lane 4 of them and a wavefront every fourth column, 8 16-byte loads
+// in flight; the four wavefronts' sums are added in order.  Bound by reading D:
+// with a position per lane and all columns in one chain of 4-byte loads it took
+// 182 us at 400,000 x 344, 111 now (5.0 TB/s).
 __global__ __launch_bounds__(kT) void refit_eta_kernel(const float* __restrict__ D, int64_t ldd, int64_t n, int M,
                                                        const int32_t* __restrict__ perm,
                                                        const double* __restrict__ b, double* __restrict__ eta)
 {
-    for (int64_t k = (int64_t)blockIdx.x * kT + threadIdx.x; k < n; k += (int64_t)gridDim.x * kT) {
-        double s = 0.0;
-        for (int a = 0; a < M; ++a) s += (double)D[(int64_t)a * ldd + k] * b[a];
-        eta[perm[k]] = s;
+    constexpr int NW = kT / kWave;
+    __shared__ double sh[NW][4][kWave];
+    const int lane = threadIdx.x & (kWave - 1), wid = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int64_t k0 = (int64_t)blockIdx.x * kT, k = k0 + 4 * lane;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    if (k < ldd) {
+        const float* Dk = D + k;
+#pragma unroll 8
+        for (int a = wid; a < M; a += NW) {
+            const float4 d = *reinterpret_cast<const float4*>(Dk + (int64_t)a * ldd);
+            const double ba = b[a];
+            s[0] += (double)d.x * ba, s[1] += (double)d.y * ba, s[2] += (double)d.z * ba, s[3] += (double)d.w * ba;
+        }
     }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sh[wid][e][lane] = s[e];
+    __syncthreads();
+    const int t = threadIdx.x;
+    if (k0 + t >= n) return;
+    double v = 0.0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) v += sh[q][t & 3][t >> 2];
+    eta[perm[k0 + t]] = v;
 }
 
 // rs[k] = r[perm[k]]: the residuals in the sorted order
@@ -99,30 +121,6 @@ __global__ void sort_r_kernel(const int32_t* __restrict__ perm, const double* __
                               double* __restrict__ rs)
 {
     for (int64_t k = (int64_t)blockIdx.x * kT + threadIdx.x; k < n; k += (int64_t)gridDim.x * kT) rs[k] = r[perm[k]];
-}
-
-// part[rb][a] = sum over row block rb of D[a][k] rs[k]
-__global__ __launch_bounds__(kT) void refit_xtr_kernel(const float* __restrict__ D, int64_t ldd, int64_t n, int M,
-                                                       const double* __restrict__ rs, int64_t rows,
-                                                       double* __restrict__ part)
-{
-    __shared__ double sh[kT / kWave];
-    const int a = blockIdx.y;
-    const int64_t i0 = (int64_t)blockIdx.x * rows, i1 = min(n, i0 + rows);
-    double s = 0.0;
-    for (int64_t i = i0 + threadIdx.x; i < i1; i += kT) s += (double)D[(int64_t)a * ldd + i] * rs[i];
-    s = block_sum256(s, sh);
-    if (threadIdx.x == 0) part[(int64_t)blockIdx.x * M + a] = s;
-}
-
-// g[a] = sum_rb part[rb][a], in row-block order
-__global__ void refit_sum_kernel(const double* __restrict__ part, int nrb, int M, double* __restrict__ g)
-{
-    const int a = blockIdx.x * kT + threadIdx.x;
-    if (a >= M) return;
-    double s = 0.0;
-    for (int rb = 0; rb < nrb; ++rb) s += part[(int64_t)rb * M + a];
-    g[a] = s;
 }
 
 // row weights of the first Hessian term in the sorted order: wt[k] = delta - r
@@ -136,13 +134,10 @@ __global__ void hess_weight_kernel(const int32_t* __restrict__ perm, const uint8
 
 constexpr int kScanJ = kScanChunk / (4 * kT);  // sub-blocks of 4 kT positions in a scan chunk
 
-// v[j][e] = w[k] D[a][k] (or w[k] with Dcol null) and g[j][e] = egidx[k]
-// (when egidx is given) at position k = k0 + 4 kT j + 4 t + e of thread t:
-// consecutive threads read consecutive 16-byte pieces.  0 (and g = -1) at or
-// past n.  k0 is a multiple of 4 kT, ldd of 8.
-__device__ __forceinline__ void scan_load(const float* __restrict__ Dcol, const double* __restrict__ w,
-                                          const int32_t* __restrict__ egidx, int64_t k0, int64_t n,
-                                          double (*v)[4], int32_t (*g)[4])
+// v[j][e] = w[k] at position k = k0 + 4 kT j + 4 t + e of thread t: consecutive
+// threads read consecutive 16-byte pieces.  0 at or past n.  k0 is a multiple of
+// 4 kT.
+__device__ __forceinline__ void scan_weights(const double* __restrict__ w, int64_t k0, int64_t n, double (*v)[4])
 {
 #pragma unroll
     for (int j = 0; j < kScanJ; ++j) {
@@ -151,89 +146,169 @@ __device__ __forceinline__ void scan_load(const float* __restrict__ Dcol, const 
             const double2 x0 = *reinterpret_cast<const double2*>(w + kb);
             const double2 x1 = *reinterpret_cast<const double2*>(w + kb + 2);
             v[j][0] = x0.x, v[j][1] = x0.y, v[j][2] = x1.x, v[j][3] = x1.y;
-            if (Dcol) {
-                const float4 d = *reinterpret_cast<const float4*>(Dcol + kb);
-                v[j][0] *= (double)d.x, v[j][1] *= (double)d.y, v[j][2] *= (double)d.z, v[j][3] *= (double)d.w;
-            }
-            if (egidx) {
-                const int4 q = *reinterpret_cast<const int4*>(egidx + kb);
-                g[j][0] = q.x, g[j][1] = q.y, g[j][2] = q.z, g[j][3] = q.w;
-            }
         } else {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int64_t k = kb + e;
-                v[j][e] = k < n ? (Dcol ? w[k] * (double)Dcol[k] : w[k]) : 0.0;
-                if (egidx) g[j][e] = k < n ? egidx[k] : -1;
-            }
+            for (int e = 0; e < 4; ++e) v[j][e] = kb + e < n ? w[kb + e] : 0.0;
         }
     }
 }
 
-// csum[a][ch] = sum over chunk ch's sorted positions k of w[k] D[a][k] (a < M)
-// or of w[k] (a == M)
-__global__ __launch_bounds__(kT) void chunk_sum_kernel(const float* __restrict__ D, int64_t ldd, int64_t n, int M,
-                                                       const double* __restrict__ w, int nch,
-                                                       double* __restrict__ csum)
+// the column's values at the same positions; 0 at or past ldd, as in its padding
+// (ldd a multiple of 8)
+__device__ __forceinline__ void scan_column(const float* __restrict__ Dcol, int64_t k0, int64_t ldd, float4* d)
 {
-    __shared__ double sh[kT / kWave];
-    const int ch = blockIdx.x, a = blockIdx.y;
-    double v[kScanJ][4];
-    scan_load(a < M ? D + (int64_t)a * ldd : nullptr, w, nullptr, (int64_t)ch * kScanChunk, n, v, nullptr);
+#pragma unroll
+    for (int j = 0; j < kScanJ; ++j) {
+        const int64_t kb = k0 + 4 * kT * j + 4 * (int64_t)threadIdx.x;
+        d[j] = kb < ldd ? *reinterpret_cast<const float4*>(Dcol + kb) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    }
+}
+
+// The two sums over D at one coefficient vector, in one pass: per chunk ch of
+// kScanChunk sorted positions gpart[a][ch] = sum_k D[a][k] rs[k] (the gradient) and
+// csum[a][ch] = sum_k D[a][k] w[k], csum[M][ch] = sum_k w[k] (the risk-set scans of
+// the Hessian).  A workgroup keeps the chunk's rs and w in registers over kSumCols
+// columns, the next column's loads under way.  Bound by reading D: 115 us at
+// 400,000 x 344 (4.8 TB/s), where one pass for each sum, reading rs or w again for
+// every column, took 170 and 127.
+constexpr int kSumCols = 8;
+__global__ __launch_bounds__(kT) void refit_sums_kernel(const float* __restrict__ D, int64_t ldd, int64_t n, int M,
+                                                        const double* __restrict__ rs, const double* __restrict__ w,
+                                                        int nch, double* __restrict__ gpart,
+                                                        double* __restrict__ csum)
+{
+    constexpr int NW = kT / kWave;
+    __shared__ double sh[kSumCols + 1][2][NW];
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    const int ch = blockIdx.x, a0 = blockIdx.y * kSumCols, na = min(kSumCols, M - a0);
+    const int64_t k0 = (int64_t)ch * kScanChunk;
+    float4 d[kScanJ], dn[kScanJ];
+    scan_column(D + (int64_t)a0 * ldd, k0, ldd, dn);
+    double rv[kScanJ][4], wv[kScanJ][4];
+    scan_weights(rs, k0, n, rv);
+    scan_weights(w, k0, n, wv);
+    for (int c = 0; c < na; ++c) {
+#pragma unroll
+        for (int j = 0; j < kScanJ; ++j) d[j] = dn[j];
+        if (c + 1 < na) scan_column(D + (int64_t)(a0 + c + 1) * ldd, k0, ldd, dn);
+        double sr = 0.0, sw = 0.0;
+#pragma unroll
+        for (int j = 0; j < kScanJ; ++j) {
+            const double v[4] = {(double)d[j].x, (double)d[j].y, (double)d[j].z, (double)d[j].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sr += v[e] * rv[j][e], sw += v[e] * wv[j][e];
+        }
+        sr = wave_sum(sr);
+        sw = wave_sum(sw);
+        if (lane == 0) sh[c][0][wid] = sr, sh[c][1][wid] = sw;
+    }
+    double sw = 0.0;
+    if (a0 == 0) {
+#pragma unroll
+        for (int j = 0; j < kScanJ; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sw += wv[j][e];
+        sw = wave_sum(sw);
+        if (lane == 0) sh[kSumCols][1][wid] = sw;
+    }
+    __syncthreads();
+    const int c = threadIdx.x >> 1, which = threadIdx.x & 1;
+    if (c < na || (c == kSumCols && which && a0 == 0)) {
+        double v = 0.0;
+#pragma unroll
+        for (int q = 0; q < NW; ++q) v += sh[c][which][q];
+        const int a = c == kSumCols ? M : a0 + c;
+        (which ? csum : gpart)[(int64_t)a * nch + ch] = v;
+    }
+}
+
+// g[a] = sum_ch gpart[a][ch], one wavefront per a, in a fixed order
+__global__ __launch_bounds__(kT) void refit_sum_kernel(const double* __restrict__ gpart, int nch, int M,
+                                                       double* __restrict__ g)
+{
+    const int lane = threadIdx.x & (kWave - 1), a = blockIdx.x * (kT / kWave) + threadIdx.x / kWave;
+    if (a >= M) return;
     double s = 0.0;
-#pragma unroll
-    for (int j = 0; j < kScanJ; ++j)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) s += v[j][e];
-    s = block_sum256(s, sh);
-    if (threadIdx.x == 0) csum[(int64_t)a * nch + ch] = s;
+    for (int ch = lane; ch < nch; ch += kWave) s += gpart[(int64_t)a * nch + ch];
+    s = wave_sum(s);
+    if (lane == 0) g[a] = s;
 }
 
 // The prefix sums at the event groups: with P_a(k) = sum_{k' <= k} w[k'] D[a][k']
 // (a < M) and P_M(k) = sum_{k' <= k} w[k'] in the sorted order, P[a][g] =
 // P_a(k) at the last position k of event group g (egidx[k] = g; -1 at every
-// other position).  Workgroup (ch, a) scans chunk ch of column a, starting
+// other position).  Workgroup (ch, y) scans chunk ch of kScanCols columns, starting
 // from the sums of the earlier chunks: each thread's 4 positions in each
 // sub-block are summed in place, every sub-block is scanned across the
-// wavefront, and one exchange of the wavefront totals places them.  Chunk 0
-// also clears P's padding rows G .. ldp - 1.
+// wavefront, and one exchange of the wavefront totals places them.  The chunk's
+// w and egidx stay in registers over the columns, the next column's loads are under
+// way meanwhile: read again for every column, three bytes of them to each of D, the
+// scan took 246 us at 400,000 x 344, now 213.  Chunk 0 also clears P's padding
+// rows G .. ldp - 1.
+constexpr int kScanCols = kT / kWave;  // a wavefront sums the earlier chunks of each
 __global__ __launch_bounds__(kT) void scan_p_kernel(const float* __restrict__ D, int64_t ldd, int64_t n, int M,
                                                     const double* __restrict__ w, const double* __restrict__ csum,
                                                     int nch, const int32_t* __restrict__ egidx, int64_t G,
                                                     int64_t ldp, double* __restrict__ P)
 {
     constexpr int NW = kT / kWave;
-    __shared__ double sv[kScanJ][NW], sh[NW];
-    const int ch = blockIdx.x, a = blockIdx.y;
+    __shared__ double sv[2][kScanJ][NW], scv[kScanCols];
+    const int ch = blockIdx.x, a0 = blockIdx.y * kScanCols, na = min(kScanCols, M + 1 - a0);
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
     const int64_t k0 = (int64_t)ch * kScanChunk;
-    double v[kScanJ][4];
+    float4 d[kScanJ], dn[kScanJ];
+    if (a0 < M) scan_column(D + (int64_t)a0 * ldd, k0, ldd, dn);
+    double wv[kScanJ][4];
     int32_t g[kScanJ][4];
-    scan_load(a < M ? D + (int64_t)a * ldd : nullptr, w, egidx, k0, n, v, g);
-    double cv = 0.0;
-    for (int c = threadIdx.x; c < ch; c += kT) cv += csum[(int64_t)a * nch + c];
-    cv = block_sum256(cv, sh);
-    double* Pa = P + (int64_t)a * ldp;
-    if (ch == 0 && threadIdx.x < ldp - G) Pa[G + threadIdx.x] = 0.0;
-    double iv[kScanJ];
+    scan_weights(w, k0, n, wv);
 #pragma unroll
     for (int j = 0; j < kScanJ; ++j) {
+        const int64_t kb = k0 + 4 * kT * j + 4 * (int64_t)threadIdx.x;
+        if (kb + 4 <= n) {
+            const int4 q = *reinterpret_cast<const int4*>(egidx + kb);
+            g[j][0] = q.x, g[j][1] = q.y, g[j][2] = q.z, g[j][3] = q.w;
+        } else {
 #pragma unroll
-        for (int e = 1; e < 4; ++e) v[j][e] += v[j][e - 1];
-        iv[j] = wave_incl_scan(v[j][3], lane);
-        if (lane == kWave - 1) sv[j][wid] = iv[j];
+            for (int e = 0; e < 4; ++e) g[j][e] = kb + e < n ? egidx[kb + e] : -1;
+        }
     }
-    __syncthreads();
-    double before = cv;  // the earlier chunks and sub-blocks
+    if (wid < na) {
+        double cv = 0.0;
+        for (int c = lane; c < ch; c += kWave) cv += csum[(int64_t)(a0 + wid) * nch + c];
+        cv = wave_sum(cv);
+        if (lane == 0) scv[wid] = cv;
+    }
+    for (int c = 0; c < na; ++c) {
+        const int a = a0 + c;
 #pragma unroll
-    for (int j = 0; j < kScanJ; ++j) {
-        // plus the earlier wavefronts of this sub-block and the earlier lanes
-        double bv = before + iv[j] - v[j][3];
-        for (int q = 0; q < wid; ++q) bv += sv[j][q];
+        for (int j = 0; j < kScanJ; ++j) d[j] = dn[j];
+        if (c + 1 < na && a + 1 < M) scan_column(D + (int64_t)(a + 1) * ldd, k0, ldd, dn);
+        double v[kScanJ][4], iv[kScanJ];
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (g[j][e] >= 0) Pa[g[j][e]] = bv + v[j][e];
-        for (int q = 0; q < NW; ++q) before += sv[j][q];
+        for (int j = 0; j < kScanJ; ++j) {
+            const float de[4] = {d[j].x, d[j].y, d[j].z, d[j].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                v[j][e] = a < M ? wv[j][e] * (double)de[e] : wv[j][e];
+                if (e) v[j][e] += v[j][e - 1];
+            }
+            iv[j] = wave_incl_scan(v[j][3], lane);
+            if (lane == kWave - 1) sv[c & 1][j][wid] = iv[j];
+        }
+        __syncthreads();
+        double* Pa = P + (int64_t)a * ldp;
+        if (ch == 0 && threadIdx.x < ldp - G) Pa[G + threadIdx.x] = 0.0;
+        double before = scv[c];  // the earlier chunks and sub-blocks
+#pragma unroll
+        for (int j = 0; j < kScanJ; ++j) {
+            // plus the earlier wavefronts of this sub-block and the earlier lanes
+            double bv = before + iv[j] - v[j][3];
+            for (int q = 0; q < wid; ++q) bv += sv[c & 1][j][q];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (g[j][e] >= 0) Pa[g[j][e]] = bv + v[j][e];
+            for (int q = 0; q < NW; ++q) before += sv[c & 1][j][q];
+        }
     }
 }
 
@@ -378,19 +453,22 @@ __global__ __launch_bounds__(256 / SW) void gram_kernel(const T* __restrict__ A,
     }
 }
 
-// H[a][b] = sum_c p1[c][a'][b'] - sum_c p2[c][a'][b'] with (a', b') = (min, max)
-// of (a, b): the Gram kernel writes every entry of the upper triangle.
+// H[a][b] = H[b][a] = sum_c p1[c][a][b] - sum_c p2[c][a][b], a <= b: the Gram
+// kernel writes every entry of the upper triangle.
 __global__ void gram_reduce_kernel(const double* __restrict__ p1, int nc1, const double* __restrict__ p2, int nc2,
                                    int M, double* __restrict__ H)
 {
     const int64_t mm = (int64_t)M * M;
     for (int64_t t = (int64_t)blockIdx.x * kT + threadIdx.x; t < mm; t += (int64_t)gridDim.x * kT) {
         const int a = (int)(t / M), b = (int)(t % M);
-        const int64_t at = a <= b ? (int64_t)a * M + b : (int64_t)b * M + a;
+        if (a > b) continue;
         double s = 0.0;
-        for (int c = 0; c < nc1; ++c) s += p1[c * mm + at];
-        for (int c = 0; c < nc2; ++c) s -= p2[c * mm + at];
+#pragma unroll 8
+        for (int c = 0; c < nc1; ++c) s += p1[c * mm + t];
+#pragma unroll 8
+        for (int c = 0; c < nc2; ++c) s -= p2[c * mm + t];
         H[t] = s;
+        H[(int64_t)b * M + a] = s;
     }
 }
 
@@ -678,19 +756,21 @@ hipError_t launch_gather_z(const float* Z, int64_t ldz, int64_t n, int q, const 
 hipError_t launch_refit_eta(const float* D, int64_t ldd, int64_t n, int M, const int32_t* perm, const double* b,
                             double* eta, hipStream_t s)
 {
-    hipLaunchKernelGGL(refit_eta_kernel, dim3(grid_for(n)), dim3(kT), 0, s, D, ldd, n, M, perm, b, eta);
+    if (ldd < refit_ld(n)) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(refit_eta_kernel, dim3((unsigned)((n + kT - 1) / kT)), dim3(kT), 0, s, D, ldd, n, M, perm, b,
+                       eta);
     return hipGetLastError();
 }
 
-int refit_row_blocks(int64_t n) { return (int)((n + kRefitRows - 1) / kRefitRows); }
-
 hipError_t launch_refit_grad(const float* D, int64_t ldd, int64_t n, int M, const int32_t* perm, const double* r,
-                             double* rs, double* part, double* g, hipStream_t s)
+                             const double* w, double* rs, double* part, double* csum, double* g, hipStream_t s)
 {
-    const int nrb = refit_row_blocks(n);
+    if (ldd < refit_ld(n)) return hipErrorInvalidValue;
+    const int nch = scan_chunks(n);
     hipLaunchKernelGGL(sort_r_kernel, dim3(grid_for(n)), dim3(kT), 0, s, perm, r, n, rs);
-    hipLaunchKernelGGL(refit_xtr_kernel, dim3(nrb, M), dim3(kT), 0, s, D, ldd, n, M, rs, (int64_t)kRefitRows, part);
-    hipLaunchKernelGGL(refit_sum_kernel, dim3((M + kT - 1) / kT), dim3(kT), 0, s, part, nrb, M, g);
+    hipLaunchKernelGGL(refit_sums_kernel, dim3(nch, (M + kSumCols - 1) / kSumCols), dim3(kT), 0, s, D, ldd, n, M, rs, w,
+                       nch, part, csum);
+    hipLaunchKernelGGL(refit_sum_kernel, dim3((M + kT / kWave - 1) / (kT / kWave)), dim3(kT), 0, s, part, nch, M, g);
     return hipGetLastError();
 }
 
@@ -718,8 +798,7 @@ hipError_t launch_refit_hessian(const RefitHess& h, hipStream_t s)
                        h.wt);
     hipLaunchKernelGGL((gram_kernel<float, 8, 4>), dim3(npair, nc1), dim3(kT / 4), 0, s, h.D, h.ldd, h.n, M, h.wt,
                        gram_rows(h.n, nc1), ntile, h.part1);
-    hipLaunchKernelGGL(chunk_sum_kernel, dim3(nch, M + 1), dim3(kT), 0, s, h.D, h.ldd, h.n, M, h.w, nch, h.csum);
-    hipLaunchKernelGGL(scan_p_kernel, dim3(nch, M + 1), dim3(kT), 0, s, h.D, h.ldd, h.n, M, h.w, h.csum, nch, h.egidx,
+    hipLaunchKernelGGL(scan_p_kernel, dim3(nch, M / kScanCols + 1), dim3(kT), 0, s, h.D, h.ldd, h.n, M, h.w, h.csum, nch, h.egidx,
                        h.G, h.ldp, h.P);
     hipLaunchKernelGGL(event_weight_kernel, dim3(grid_for(h.ldp)), dim3(kT), 0, s, h.P + (int64_t)M * h.ldp, h.egcnt,
                        h.G, h.ldp, h.wg);

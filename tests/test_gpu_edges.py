@@ -221,3 +221,30 @@ def test_nmf_rank_quads(r, m, n, pad):
     Vo, Wo, _ = oracle.nmf_run(X, Vt0, W0, P.NMF_MULTIPLICATIVE, 3)
     np.testing.assert_allclose(Vt.cpu().numpy(), Vo, rtol=1e-11)
     np.testing.assert_allclose(W.cpu().numpy(), Wo, rtol=1e-11)
+
+
+@pytest.mark.parametrize("n,M", [(257, 1), (1025, 8), (4095, 3), (4096, 32), (4097, 9), (8200, 33), (4099, 64), (4101, 65),
+                                 (12300, 129), (5000, 200)])
+def test_refit_blocks(n, M):
+    """The refit's passes over the design (chunks of 4,096 positions, columns in
+    groups of 4 and 8, eta in blocks of 256), the Gram tiles (16, 32 and 64 columns
+    and their ragged last ones) and the factor's blocks of 32: at the Newton solution
+    both sides solve the same FP64 equations, so coefficients, errors and likelihood
+    agree to the refit tests' 1e-8 (1e-12 for the likelihood)."""
+    rng = np.random.Generator(np.random.PCG64(17 * n + M))
+    X = rng.normal(size=(M, n)).astype(np.float32)
+    eta = 0.3 * X[:min(M, 5)].sum(axis=0)
+    time = np.ceil(200 * rng.exponential(np.exp(-eta)))
+    event = (rng.random(n) < 0.7).astype(np.int32)
+    ldx = (n + 15) // 16 * 16
+    Xd = torch.zeros((M, ldx), dtype=torch.float32)
+    Xd[:, :n] = torch.from_numpy(X)
+    cox = P.Cox(Xd.cuda(), time, event, n=n)
+    coef, se, pv, L, it, st = cox.refit(np.arange(M), gtol=1e-9)
+    assert st == P.OK
+    Mo = oracle.Matrix.dense(X.astype(np.float64))
+    b, cov, _, conv = oracle.newton(Mo, time, event, np.arange(M), gtol=1e-11, maxit=100)
+    assert conv
+    np.testing.assert_allclose(coef, b, rtol=1e-8, atol=1e-9)
+    np.testing.assert_allclose(se, np.sqrt(np.diag(cov)), rtol=1e-8)
+    assert L == pytest.approx(oracle.loglik(oracle.xbeta(Mo, b), time, event)[0], rel=1e-12)
