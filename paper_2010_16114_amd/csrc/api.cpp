@@ -1718,14 +1718,14 @@ cox_status cox_refit(cox_ctx* c, const int64_t* cols, int32_t m, const cox_refit
     const size_t MM = (size_t)M * M;
     Scratch w;
     float* D;
-    double *Pg, *wg, *wt, *rs, *csum, *p1, *p2, *H, *g, *d, *b, *bt, *gpart, *sed, *pvd;
+    double *Pg, *wg, *wt, *rs, *csum, *p1, *p2, *H, *g, *d, *b, *bt, *gpart, *sed, *pvd, *diag;
     int32_t* colsd;
     int* okd;
     if (!(w.get(&D, (size_t)M * ldd) && w.get(&Pg, (size_t)(M + 1) * ldp) && w.get(&wg, ldp) && w.get(&wt, ldd) &&
           w.get(&rs, n) &&
           w.get(&csum, (size_t)(M + 1) * nch) && w.get(&p1, nc1 * MM) && w.get(&p2, nc2 * MM) && w.get(&H, MM) &&
           w.get(&g, M) && w.get(&d, M) && w.get(&b, M) && w.get(&bt, M) && w.get(&gpart, (size_t)nch * M) &&
-          w.get(&sed, M) && w.get(&pvd, M) && w.get(&colsd, std::max(m, 1)) && w.get(&okd, 1)))
+          w.get(&sed, M) && w.get(&pvd, M) && w.get(&diag, kCholDiag) && w.get(&colsd, std::max(m, 1)) && w.get(&okd, 1)))
         return fail(c, COX_ERR_OUT_OF_MEMORY, "refit workspace");
 
     if (m > 0) {
@@ -1752,7 +1752,7 @@ cox_status cox_refit(cox_ctx* c, const int64_t* cols, int32_t m, const cox_refit
         HIPCHK(launch_refit_hessian(hs, c->stream), "Hessian");
         tmark(c, COX_PHASE_REFIT_HESSIAN);
         tmark(c, COX_PHASE_REFIT_SOLVE);
-        HIPCHK(launch_chol(H, M, okd, c->stream), "Cholesky");
+        HIPCHK(launch_chol(H, M, diag, okd, c->stream), "Cholesky");
         tmark(c, COX_PHASE_REFIT_SOLVE);
         int ok = 0;
         STCHK(d2h(c, &ok, okd, sizeof(int)));

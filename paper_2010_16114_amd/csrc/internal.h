@@ -317,8 +317,10 @@ struct RefitHess {
     double* H;      // [M][M]
 };
 hipError_t launch_refit_hessian(const RefitHess& h, hipStream_t s);
-// A = L L' in place (lower triangle), ok[0] = 1 if positive definite
-hipError_t launch_chol(double* A, int M, int* ok, hipStream_t s);
+// A = L L' in place (lower triangle), ok[0] = 1 if positive definite; diag: scratch of
+// kCholDiag doubles
+constexpr int kCholDiag = 32 * 32;
+hipError_t launch_chol(double* A, int M, double* diag, int* ok, hipStream_t s);
 hipError_t launch_chol_solve(const double* L, int M, const double* g, double* x, hipStream_t s);
 // se = sqrt(diag((L L')^{-1})), pval = erfc(|b / se| / sqrt 2)
 hipError_t launch_wald(const double* L, int M, const double* b, double* se, double* pval, hipStream_t s);

@@ -477,45 +477,77 @@ __global__ void gram_reduce_kernel(const double* __restrict__ p1, int nc1, const
 // left as it was), in blocks of kCB.  Step J runs chol_panel_kernel, then
 // chol_update_kernel on the trailing lower blocks.
 
-// Every workgroup factorises the diagonal block J in LDS (the same arithmetic
-// in each); workgroup 0 stores it and the flag, workgroup b > 0 solves block
-// row J + b of the panel, X L_JJ' = A_(J+b)J.  ok[0] = 1 after the first
-// step, set to 0 by any step that meets a pivot that is not positive (the
-// pivot is then taken as 1 and the factorisation runs on).
-__global__ __launch_bounds__(kT) void chol_panel_kernel(double* __restrict__ A, int M, int J, int* __restrict__ ok)
+// lane `src`'s v (src the same in every lane)
+__device__ __forceinline__ double bcast(double v, int src)
 {
-    __shared__ double Ld[kCB][kCB + 1];
-    __shared__ double P[kCB][kCB + 1];
-    __shared__ int good;
-    const int j0 = J * kCB, bs = min(kCB, M - j0);
-    for (int e = threadIdx.x; e < kCB * kCB; e += kT) {
-        const int r = e / kCB, c = e % kCB;
-        Ld[r][c] = (r < bs && c < bs) ? A[(int64_t)(j0 + r) * M + j0 + c] : 0.0;
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), src),
+                            __builtin_amdgcn_readlane(__double2loint(v), src));
+}
+
+// a / d from inv = 1 / d: the rounded product and one correction of its remainder, a
+// chain of three where the division's own is about ten
+__device__ __forceinline__ double quotient(double a, double d, double inv)
+{
+    const double q = a * inv;
+    return fma(fma(-d, q, a), inv, q);
+}
+
+// One wavefront per workgroup: lanes 0 .. kCB - 1 hold the rows of the diagonal
+// block J in registers (every workgroup factorises it, the same arithmetic in each),
+// lanes kCB .. 2 kCB - 1 those of block row J + b of the panel, b = blockIdx.x, which
+// the same column steps turn into X with X L_JJ' = A_(J+b)J.  Workgroup 0 stores the
+// factorised block, to `diag` (row-major, kCB wide) unless it is alone, because the
+// others may still have to read A's, and the flag; workgroup b > 0 its panel rows.
+// chol_update_kernel moves `diag` into A.  ok[0] = 1 after the
+// first step, set to 0 by any step that meets a pivot that is not positive (the
+// pivot is then taken as 1 and the factorisation runs on).  A chain of kCB square
+// roots, divisions and rank-1 updates: in LDS, with four barriers per column and
+// the panel solved afterwards, it took 28.5 us a step at M = 344, now 19.7.
+__global__ __launch_bounds__(kWave) void chol_panel_kernel(double* __restrict__ A, int M, int J,
+                                                            double* __restrict__ diag, int* __restrict__ ok)
+{
+    static_assert(2 * kCB == kWave && kCB * kCB == kCholDiag, "a lane per row of the two blocks");
+    __shared__ double T[2 * kCB][kCB + 1];
+    const int lane = threadIdx.x;
+    const int j0 = J * kCB, bs = min(kCB, M - j0), i0 = (J + blockIdx.x) * kCB;
+    // a panel block exists only below a full diagonal block (bs == kCB)
+    const int rs = blockIdx.x ? min(kCB, M - i0) : 0;
+#pragma unroll
+    for (int t = 0; t < kCB; ++t) {  // two rows of kCB at a time
+        const int r = 2 * t + lane / kCB, c = lane % kCB;
+        const bool top = r < kCB;
+        const int row = top ? j0 + r : i0 + r - kCB;
+        T[r][c] = c < bs && (top ? r < bs : r - kCB < rs) ? A[(int64_t)row * M + j0 + c] : 0.0;
     }
-    if (threadIdx.x == 0) good = 1;
     __syncthreads();
-    for (int j = 0; j < bs; ++j) {
-        const double d = Ld[j][j];
-        const double piv = d > 0.0 ? sqrt(d) : 1.0;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            if (!(d > 0.0)) good = 0;
-            Ld[j][j] = piv;
+    double x[kCB];
+#pragma unroll
+    for (int c = 0; c < kCB; ++c) x[c] = T[lane][c];
+    // entries right of the diagonal are carried along in lanes that no other reads
+    bool good = true;
+#pragma unroll
+    for (int j = 0; j < kCB; ++j) {
+        if (j < bs) {
+            const double d = bcast(x[j], j);
+            good = good && d > 0.0;
+            const double piv = d > 0.0 ? sqrt(d) : 1.0;
+            x[j] = lane == j ? piv : quotient(x[j], piv, 1.0 / piv);
+#pragma unroll
+            for (int k = j + 1; k < kCB; ++k) x[k] -= x[j] * bcast(x[j], k);
         }
-        if ((int)threadIdx.x > j && (int)threadIdx.x < bs) Ld[threadIdx.x][j] /= piv;
-        __syncthreads();
-        for (int e = threadIdx.x; e < kCB * kCB; e += kT) {
-            const int i = e / kCB, k = e % kCB;
-            if (k > j && k <= i && i < bs) Ld[i][k] -= Ld[i][j] * Ld[k][j];
-        }
-        __syncthreads();
     }
+#pragma unroll
+    for (int c = 0; c < kCB; ++c) T[lane][c] = x[c];
+    __syncthreads();
     if (blockIdx.x == 0) {
-        for (int e = threadIdx.x; e < kCB * kCB; e += kT) {
+        for (int e = lane; e < kCB * kCB; e += kWave) {
             const int r = e / kCB, c = e % kCB;
-            if (r < bs && c <= r) A[(int64_t)(j0 + r) * M + j0 + c] = Ld[r][c];
+            if (gridDim.x > 1)
+                diag[e] = T[r][c];
+            else if (r < bs && c <= r)
+                A[(int64_t)(j0 + r) * M + j0 + c] = T[r][c];
         }
-        if (threadIdx.x == 0) {
+        if (lane == 0) {
             if (J == 0)
                 ok[0] = good;
             else if (!good)
@@ -523,38 +555,26 @@ __global__ __launch_bounds__(kT) void chol_panel_kernel(double* __restrict__ A, 
         }
         return;
     }
-    // a panel block exists only below a full diagonal block (bs == kCB)
-    const int i0 = (J + blockIdx.x) * kCB, rs = min(kCB, M - i0);
-    for (int e = threadIdx.x; e < kCB * kCB; e += kT) {
+    for (int e = lane; e < kCB * kCB; e += kWave) {
         const int r = e / kCB, c = e % kCB;
-        P[r][c] = r < rs ? A[(int64_t)(i0 + r) * M + j0 + c] : 0.0;
-    }
-    __syncthreads();
-    if ((int)threadIdx.x < rs) {
-        const int r = threadIdx.x;
-        double x[kCB];
-#pragma unroll
-        for (int c = 0; c < kCB; ++c) {
-            double s = P[r][c];
-#pragma unroll
-            for (int c2 = 0; c2 < c; ++c2) s -= x[c2] * Ld[c][c2];
-            x[c] = s / Ld[c][c];
-        }
-#pragma unroll
-        for (int c = 0; c < kCB; ++c) P[r][c] = x[c];
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < kCB * kCB; e += kT) {
-        const int r = e / kCB, c = e % kCB;
-        if (r < rs) A[(int64_t)(i0 + r) * M + j0 + c] = P[r][c];
+        if (r < rs) A[(int64_t)(i0 + r) * M + j0 + c] = T[kCB + r][c];
     }
 }
 
 // A_IK -= L_IJ L_KJ' for the trailing lower blocks J < K <= I (in a diagonal
-// block only on and below the diagonal); one block per workgroup.
-__global__ __launch_bounds__(kT) void chol_update_kernel(double* __restrict__ A, int M, int J)
+// block only on and below the diagonal); one block per workgroup, and the last
+// workgroup stores step J's factorised diagonal block.
+__global__ __launch_bounds__(kT) void chol_update_kernel(double* __restrict__ A, int M, int J,
+                                                         const double* __restrict__ diag)
 {
     __shared__ double Pi[kCB][kCB + 1], Pk[kCB][kCB + 1];
+    if (blockIdx.x == gridDim.x - 1) {
+        for (int e = threadIdx.x; e < kCB * kCB; e += kT) {
+            const int r = e / kCB, c = e % kCB;
+            if (c <= r) A[(int64_t)(J * kCB + r) * M + J * kCB + c] = diag[e];
+        }
+        return;
+    }
     int64_t t = blockIdx.x;
     int ii = (int)((sqrt(8.0 * (double)t + 1.0) - 1.0) * 0.5);
     while ((int64_t)ii * (ii + 1) / 2 > t) --ii;
@@ -584,13 +604,14 @@ __global__ __launch_bounds__(kT) void chol_update_kernel(double* __restrict__ A,
     }
 }
 
-__device__ __forceinline__ double bcast(double v, int src) { return __shfl(v, src, kWave); }
-
 // Forward substitution L y = e on rows from block I0 on (L from the blocked
 // Cholesky, y in LDS ys[], whose entries below I0 kCB are not read); e is g
 // (rows i) or, with g null, the unit vector at row `unit`.  Per block: the
 // known part of each row's sum with 8 threads per row, then the kCB x kCB
-// diagonal block in one wavefront, lane r holding row r of it in registers.
+// diagonal block in one wavefront, lane r holding row r of it in registers, loaded
+// before the sums.  The chain over the rows is the time: with a division and a shuffle
+// through LDS per row the two solves took 146 us at M = 344, now 120 (the sums' loads
+// and barriers, 22 blocks one after the other).
 __device__ void lower_solve(const double* __restrict__ L, int M, int I0, const double* __restrict__ g, int unit,
                             double* ys, double* red)
 {
@@ -598,10 +619,17 @@ __device__ void lower_solve(const double* __restrict__ L, int M, int I0, const d
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     for (int I = I0; I < nb; ++I) {
         const int i0 = I * kCB, rb = min(kCB, M - i0);
+        double lr[kCB], ld = 1.0;
+        if (wid == 0) {
+#pragma unroll
+            for (int c = 0; c < kCB; ++c) lr[c] = (lane < rb && c <= lane) ? L[(int64_t)(i0 + lane) * M + i0 + c] : 0.0;
+            if (lane < rb) ld = L[(int64_t)(i0 + lane) * M + i0 + lane];
+        }
         {
             const int r = threadIdx.x >> 3, s = threadIdx.x & 7;
             double part = 0.0;
             if (r < rb)
+#pragma unroll 8
                 for (int k = I0 * kCB + s; k < i0; k += 8) part += L[(int64_t)(i0 + r) * M + k] * ys[k];
             part += __shfl_xor(part, 1, kWave);
             part += __shfl_xor(part, 2, kWave);
@@ -610,14 +638,13 @@ __device__ void lower_solve(const double* __restrict__ L, int M, int I0, const d
         }
         __syncthreads();
         if (wid == 0) {
-            double b = 0.0, lr[kCB];
-#pragma unroll
-            for (int c = 0; c < kCB; ++c) lr[c] = (lane < rb && c <= lane) ? L[(int64_t)(i0 + lane) * M + i0 + c] : 0.0;
+            double b = 0.0;
+            const double inv = 1.0 / ld;
             if (lane < rb) b = (g ? g[i0 + lane] : (i0 + lane == unit ? 1.0 : 0.0)) - red[lane];
 #pragma unroll
             for (int c = 0; c < kCB; ++c) {
                 if (c < rb) {
-                    const double yc = bcast(b / lr[c], c);
+                    const double yc = bcast(quotient(b, ld, inv), c);
                     if (lane > c) b -= lr[c] * yc;
                     if (lane == c) b = yc;
                 }
@@ -637,19 +664,25 @@ __device__ void upper_solve(const double* __restrict__ L, int M, double* ys, dou
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     for (int I = nb - 1; I >= 0; --I) {
         const int i0 = I * kCB, rb = min(kCB, M - i0), k0 = i0 + rb;
+        double lc[kCB], ld = 1.0;
+        if (wid == 0) {
+#pragma unroll
+            for (int c = 0; c < kCB; ++c)
+                lc[c] = (lane < rb && c >= lane && c < rb) ? L[(int64_t)(i0 + c) * M + i0 + lane] : 0.0;
+            if (lane < rb) ld = L[(int64_t)(i0 + lane) * M + i0 + lane];
+        }
         {
             const int r = threadIdx.x & (kCB - 1), s = threadIdx.x / kCB;
             double part = 0.0;
             if (r < rb)
+#pragma unroll 8
                 for (int k = k0 + s; k < M; k += kT / kCB) part += L[(int64_t)k * M + i0 + r] * ys[k];
             red8[s][r] = part;
         }
         __syncthreads();
         if (wid == 0) {
-            double b = 0.0, lc[kCB];
-#pragma unroll
-            for (int c = 0; c < kCB; ++c)
-                lc[c] = (lane < rb && c >= lane && c < rb) ? L[(int64_t)(i0 + c) * M + i0 + lane] : 0.0;
+            double b = 0.0;
+            const double inv = 1.0 / ld;
             if (lane < rb) {
                 b = ys[i0 + lane];
                 for (int s = 0; s < kT / kCB; ++s) b -= red8[s][lane];
@@ -657,7 +690,7 @@ __device__ void upper_solve(const double* __restrict__ L, int M, double* ys, dou
 #pragma unroll
             for (int c = kCB - 1; c >= 0; --c) {
                 if (c < rb) {
-                    const double xc = bcast(b / lc[c], c);
+                    const double xc = bcast(quotient(b, ld, inv), c);
                     if (lane < c) b -= lc[c] * xc;
                     if (lane == c) b = xc;
                 }
@@ -809,14 +842,15 @@ hipError_t launch_refit_hessian(const RefitHess& h, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_chol(double* A, int M, int* ok, hipStream_t s)
+hipError_t launch_chol(double* A, int M, double* diag, int* ok, hipStream_t s)
 {
     if (M < 1 || M > kMaxRefit) return hipErrorInvalidValue;
     const int nb = (M + kCB - 1) / kCB;
     for (int J = 0; J < nb; ++J) {
-        hipLaunchKernelGGL(chol_panel_kernel, dim3(nb - J), dim3(kT), 0, s, A, M, J, ok);
+        hipLaunchKernelGGL(chol_panel_kernel, dim3(nb - J), dim3(kWave), 0, s, A, M, J, diag, ok);
         const int nt = nb - J - 1;
-        if (nt > 0) hipLaunchKernelGGL(chol_update_kernel, dim3(nt * (nt + 1) / 2), dim3(kT), 0, s, A, M, J);
+        if (nt > 0)
+            hipLaunchKernelGGL(chol_update_kernel, dim3(nt * (nt + 1) / 2 + 1), dim3(kT), 0, s, A, M, J, diag);
     }
     return hipGetLastError();
 }
