@@ -1714,7 +1714,7 @@ cox_status cox_refit(cox_ctx* c, const int64_t* cols, int32_t m, const cox_refit
         if (!std::isfinite(coef[a])) return fail(c, COX_ERR_INVALID_ARG, "coef must be finite");
 
     const int64_t G = c->n_egroups, ldd = refit_ld(n), ldp = refit_ld(G);
-    const int nc1 = gram_chunks(n, M), nc2 = gram_chunks(G, M), nch = scan_chunks(n);
+    const int nch = scan_chunks(n);
     const size_t MM = (size_t)M * M;
     Scratch w;
     float* D;
@@ -1723,7 +1723,7 @@ cox_status cox_refit(cox_ctx* c, const int64_t* cols, int32_t m, const cox_refit
     int* okd;
     if (!(w.get(&D, (size_t)M * ldd) && w.get(&Pg, (size_t)(M + 1) * ldp) && w.get(&wg, ldp) && w.get(&wt, ldd) &&
           w.get(&rs, n) &&
-          w.get(&csum, (size_t)(M + 1) * nch) && w.get(&p1, nc1 * MM) && w.get(&p2, nc2 * MM) && w.get(&H, MM) &&
+          w.get(&csum, (size_t)(M + 1) * nch) && w.get(&p1, gram_part(n, M)) && w.get(&p2, gram_part(G, M)) && w.get(&H, MM) &&
           w.get(&g, M) && w.get(&d, M) && w.get(&b, M) && w.get(&bt, M) && w.get(&gpart, (size_t)nch * M) &&
           w.get(&sed, M) && w.get(&pvd, M) && w.get(&diag, kCholDiag) && w.get(&colsd, std::max(m, 1)) && w.get(&okd, 1)))
         return fail(c, COX_ERR_OUT_OF_MEMORY, "refit workspace");

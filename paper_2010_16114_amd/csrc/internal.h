@@ -21,7 +21,7 @@ constexpr int kMaxHist = 33;                        // lag <= 32
 constexpr int kCovRows = 8192;                      // rows per workgroup of Z' r
 constexpr int kMaxCov = 64;                         // covariates in the dense block beside X
 constexpr int kMaxRefit = 1024;                     // columns of an unpenalised refit
-constexpr int kGramChunks = 64;                     // most row chunks of a refit Gram term
+constexpr int kGramChunks = 256;                    // most row chunks of a refit Gram term
 
 // Read-only description of X as the kernels see it.
 struct XDesc {
@@ -291,8 +291,14 @@ hipError_t launch_refit_eta(const float* D, int64_t ldd, int64_t n, int M, const
 // w D and w (w sorted) that the Hessian at this state starts its scans from
 hipError_t launch_refit_grad(const float* D, int64_t ldd, int64_t n, int M, const int32_t* perm, const double* r,
                              const double* w, double* rs, double* part, double* csum, double* g, hipStream_t s);
-// row chunks of a Gram term over `rows` rows and M columns; risk-set scan chunks
-int gram_chunks(int64_t rows, int M);
+// row chunks of a Gram term's tiles over `rows` rows and M columns: the full ones
+// above the diagonal, those of the last column of tiles, those on the diagonal, the
+// last one; gram_part: doubles of its partial sums.  scan_chunks: risk-set scan chunks
+struct GramPlan {
+    int full, edge, diag, last;
+};
+GramPlan gram_plan(int64_t rows, int M);
+size_t gram_part(int64_t rows, int M);
 int scan_chunks(int64_t n);
 // H = -Hessian of L in the M coefficients (M x M, row-major) at the risk-set
 // state (w sorted, r in subject order).  egidx [n]: event group of each sorted
@@ -312,8 +318,8 @@ struct RefitHess {
     const double* csum;  // [M + 1][scan_chunks(n)], from launch_refit_grad at the same state
     double* P;      // [M + 1][ldp], ldp >= refit_ld(G)
     double* wg;     // [ldp]
-    double* part1;  // [gram_chunks(n, M)][M][M]
-    double* part2;  // [gram_chunks(G, M)][M][M]
+    double* part1;  // [gram_part(n, M)]
+    double* part2;  // [gram_part(G, M)]
     double* H;      // [M][M]
 };
 hipError_t launch_refit_hessian(const RefitHess& h, hipStream_t s);

@@ -26,12 +26,10 @@ namespace cox {
 namespace {
 
 constexpr int kT = 256;
-constexpr int kGT = 64;          // Gram output tile (kGT x kGT), one 16-row band per wavefront
+constexpr int kGT = 128;         // Gram output tile (kGT x kGT), 32 rows of it per wavefront
 constexpr int kGR = 32;          // row chunks of the Gram kernel start on multiples of this
 constexpr int kScanChunk = 4096; // sorted positions per workgroup of the risk-set scans
 constexpr int kCB = 32;          // block size of the Cholesky factorisation and the triangular solves
-
-typedef double v4d __attribute__((ext_vector_type(4)));
 
 __device__ double block_sum256(double v, double* sh)
 {
@@ -328,145 +326,227 @@ __global__ void event_weight_kernel(const double* __restrict__ PM, const int32_t
     }
 }
 
-__device__ __forceinline__ v4d mfma_f64(double a, double b, v4d c)
+// Gram terms: for a 128 x 128 output tile (ta, tb), ta <= tb, and a chunk of the rows
+// k, sum_k wt_k A[a][k] A[b][k], a <= b.  A is column-major (lda a multiple of 8, 0
+// past the rows, wt likewise); every chunk starts on a multiple of kGR rows.
+//
+// On the FP64 matrix cores with v_mfma_f64_4x4x4f64, four independent 4 x 4 x 4
+// products: per lane, block l / 4 mod 4 holds A (row l % 4, k l / 16), B (k l / 16,
+// column l % 4) and D (row l / 16, column l % 4).  Every block takes the same four
+// rows, so an instruction multiplies 4 rows by 16 columns.  It sustains 67 to 72
+// TFLOP/s here, v_mfma_f64_16x16x4f64 31 to 44 in the same loop.  Any vector
+// instruction between takes its issue slots from the matrix pipe, so the operands are
+// converted and weighted once per workgroup, on their way into LDS, not per
+// wavefront.
+//
+// A step is one 128-byte line of every column (32 FP32 rows, 16 FP64); 8 lanes load a
+// line.  The weighted columns of ta and the plain ones of tb lie in LDS as doubles,
+// with column strides that put a read of 16 columns on mostly distinct banks; the
+// next step's lines load into registers meanwhile.
+// Wavefront w takes the blocks of 16 rows w and 7 - w and leaves out the 16 x 16
+// blocks below the diagonal or past M (the reduction reads the upper triangle), so
+// that on the diagonal too the four have the same work: 9 blocks each.
+//
+// Bound by the matrix cores and the steps' latency.  At 400,000 x 344 the FP32 term
+// took 1360 us and the FP64 term (80,000 event groups) 366 with one wavefront per
+// 64 x 64 tile straight from memory on v_mfma_f64_16x16x4f64; now 1110 and 266
+// (its products alone take 660 us at the instruction's rate).  That form on the 4x4x4
+// instruction, its columns rotated across lanes, took 2030: the conversions and
+// rotations of every wavefront stood in the matrix pipe's way.
+
+// A tile's place in the list of workgroups: those of chunk ch of its kind start at
+// first + ch * count, its own is idx further on.
+struct GramTile {
+    int ta, tb, first, count, idx, chunks;
+};
+__device__ __forceinline__ int gram_tiles(int M) { return (M - 1) / kGT; }  // but the last
+__device__ __forceinline__ GramTile gram_find(const GramPlan& g, int M, int ta, int tb)
 {
-    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+    const int nt1 = gram_tiles(M), pairs = nt1 * (nt1 - 1) / 2;
+    const int edge = pairs * g.full, diag = edge + nt1 * g.edge, last = diag + nt1 * g.diag;
+    if (ta != tb) {
+        if (tb == nt1) return GramTile{ta, tb, edge, nt1, ta, g.edge};
+        return GramTile{ta, tb, 0, pairs, ta * (nt1 - 1) - ta * (ta - 1) / 2 + tb - ta - 1, g.full};
+    }
+    if (tb == nt1) return GramTile{ta, tb, last, 1, 0, g.last};
+    return GramTile{ta, tb, diag, nt1, ta, g.diag};
 }
 
-// GL consecutive values at p (16-byte aligned)
-template <int GL>
-__device__ __forceinline__ void load_seg(const float* p, float* o)
+template <class T>
+struct GramStep;
+template <>
+struct GramStep<float> {
+    static constexpr int K = 32, E = 4, S = 38;
+    using V = float4;
+};
+template <>
+struct GramStep<double> {
+    static constexpr int K = 16, E = 2, S = 18;
+    using V = double2;
+};
+__device__ __forceinline__ void unpack(const float4& v, double* o)
 {
-#pragma unroll
-    for (int e = 0; e < GL; e += 4) {
-        const float4 x = *reinterpret_cast<const float4*>(p + e);
-        o[e] = x.x, o[e + 1] = x.y, o[e + 2] = x.z, o[e + 3] = x.w;
-    }
+    o[0] = (double)v.x, o[1] = (double)v.y, o[2] = (double)v.z, o[3] = (double)v.w;
 }
-template <int GL>
-__device__ __forceinline__ void load_seg(const double* p, double* o)
+__device__ __forceinline__ void unpack(const double2& v, double* o) { o[0] = v.x, o[1] = v.y; }
+
+// one step's products of a wavefront: rows 16 of block h (as0, as1) by block t of 16
+// columns if bit 8 h + t of mask is set
+template <int K, int S>
+__device__ __forceinline__ void gram_step(const double (*__restrict__ as0)[S], const double (*__restrict__ as1)[S],
+                                          const double (*__restrict__ bs)[S], int lane, int mask, double (*acc)[8])
 {
+#pragma unroll 1
+    for (int kk = 0; kk < K; kk += 8) {
+        // a lane's k-slot l / 16 takes two neighbouring rows, in both operands
+        const int k = kk + 2 * (lane >> 4);
+        double2 av[8];
 #pragma unroll
-    for (int e = 0; e < GL; e += 2) {
-        const double2 x = *reinterpret_cast<const double2*>(p + e);
-        o[e] = x.x, o[e + 1] = x.y;
+        for (int q = 0; q < 4; ++q) {
+            av[q] = *reinterpret_cast<const double2*>(&as0[q * 4 + (lane & 3)][k]);
+            av[4 + q] = *reinterpret_cast<const double2*>(&as1[q * 4 + (lane & 3)][k]);
+        }
+#pragma unroll
+        for (int t = 0; t < 8; ++t) {
+            const double2 bv = *reinterpret_cast<const double2*>(&bs[t * 16 + (lane & 15)][k]);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                if (!((mask >> (8 * h + t)) & 1)) continue;
+#pragma unroll
+                for (int q = 4 * h; q < 4 * h + 4; ++q)
+                    acc[q][t] = __builtin_amdgcn_mfma_f64_4x4x4f64(av[q].x, bv.x, acc[q][t], 0, 0, 0);
+#pragma unroll
+                for (int q = 4 * h; q < 4 * h + 4; ++q)
+                    acc[q][t] = __builtin_amdgcn_mfma_f64_4x4x4f64(av[q].y, bv.y, acc[q][t], 0, 0, 0);
+            }
+        }
     }
 }
 
-// part[chunk][a][b] = sum over the chunk's rows k of wt_k A[a][k] A[b][k] (wt
-// nullable: 1) for the 64 x 64 output tile (ta, tb), ta <= tb, on the FP64
-// matrix cores (v_mfma_f64_16x16x4f64; per lane A holds (row lane % 16, k
-// lane / 16), B holds (k lane / 16, column lane % 16), D holds rows
-// lane / 16 + 4 v of column lane % 16).  Each of the 4 / SW wavefronts owns
-// SW bands of 16 rows of the tile and its 4 blocks of 16 columns, so a
-// loaded B row serves SW products; in a diagonal tile the blocks left of a
-// band are not stored (the reduction reads the upper triangle).  The rows are taken in steps of 4 GL: lane l loads
-// rows GL q .. GL q + GL - 1 (q = l / 16) of its column straight from
-// memory, and the s-th product of a step puts row GL q + s in k-slot q -- one
-// permutation of the rows, shared by both operands, so every product pairs up
-// as in the plain sum.  The next step's rows are loaded while the current
-// ones are multiplied.  A is column-major (lda a multiple of 8, 0 past the
-// rows, wt likewise); every chunk starts on a multiple of kGR (GL = 4 or 8).
-template <class T, int GL, int SW>
-__global__ __launch_bounds__(256 / SW) void gram_kernel(const T* __restrict__ A, int64_t lda, int64_t n, int M,
-                                                        const double* __restrict__ wt, int64_t rows, int ntile,
-                                                        double* __restrict__ part)
+template <class T>
+__global__ __launch_bounds__(kT, 2) void gram_kernel(const T* __restrict__ A, int64_t lda, int64_t n, int M,
+                                                     const double* __restrict__ wt, GramPlan g,
+                                                     double* __restrict__ part)
 {
-    int idx = blockIdx.x, ta = 0;
-    while (idx >= ntile - ta) {
-        idx -= ntile - ta;
-        ++ta;
+    using V = typename GramStep<T>::V;
+    constexpr int K = GramStep<T>::K, E = GramStep<T>::E, LS = GramStep<T>::S, P = kGT / 32;
+    __shared__ __attribute__((aligned(16))) double as[kGT][LS], bs[kGT][LS];
+    // workgroup -> (tile, chunk): the full tiles above the diagonal, those of the last
+    // column, those on the diagonal, the last one; within a kind the chunks outermost
+    const int nt1 = gram_tiles(M), pairs = nt1 * (nt1 - 1) / 2;
+    int idx = blockIdx.x, ta, tb, ch, nc;
+    if (idx < pairs * g.full) {
+        ch = idx / pairs, nc = g.full;
+        idx -= ch * pairs;
+        ta = 0;
+        while (idx >= nt1 - 1 - ta) {
+            idx -= nt1 - 1 - ta;
+            ++ta;
+        }
+        tb = ta + 1 + idx;
+    } else if ((idx -= pairs * g.full) < nt1 * g.edge) {
+        ch = idx / nt1, nc = g.edge, ta = idx - ch * nt1, tb = nt1;
+    } else if ((idx -= nt1 * g.edge) < nt1 * g.diag) {
+        ch = idx / nt1, nc = g.diag, ta = tb = idx - ch * nt1;
+    } else {
+        ch = idx - nt1 * g.diag, nc = g.last, ta = tb = nt1;
     }
-    const int tb = ta + idx;
     const bool diag = ta == tb;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, c = lane & 15, q = lane >> 4;
-    const int64_t r0 = (int64_t)blockIdx.y * rows, r1 = min(n, r0 + rows);
-    // columns past M are read from column M - 1: they only reach outputs that
-    // are not stored
-    const T* pa[SW];
+    // the wavefront's blocks of 16 rows, wid and 7 - wid, by 8 blocks of 16 columns:
+    // those with an entry on or above the diagonal, of rows and columns below M
+    const int lane = threadIdx.x & 63, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int u0 = wid * 16, u1 = (7 - wid) * 16;
+    int mask = 0;
 #pragma unroll
-    for (int u = 0; u < SW; ++u) pa[u] = A + (int64_t)min(ta * kGT + (wv * SW + u) * 16 + c, M - 1) * lda;
-    const T* pb[4];
+    for (int t = 0; t < 8; ++t) {
+        const int b = tb * kGT + t * 16;
+        mask |= (ta * kGT + u0 <= b && b < M) << t;
+        mask |= (ta * kGT + u1 <= b && b < M) << (8 + t);
+    }
+    const int64_t rows = ((n + nc - 1) / nc + kGR - 1) / kGR * kGR;
+    const int64_t r0 = ch * rows, r1 = min(n, r0 + rows);
+    double acc[8][8];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) pb[t] = A + (int64_t)min(tb * kGT + t * 16 + c, M - 1) * lda;
-    v4d acc[SW][4];
+    for (int u = 0; u < 8; ++u)
 #pragma unroll
-    for (int u = 0; u < SW; ++u)
-#pragma unroll
-        for (int t = 0; t < 4; ++t) acc[u][t] = v4d{0.0, 0.0, 0.0, 0.0};
-    T na[SW][GL], nb[4][GL];
-    double nw[GL];
-    // a lane's segment at or past r1 is read at r0 with weight 0 (a segment
-    // that starts before r1 ends before lda: r1 <= the rows, lda >= them
-    // rounded up to 8)
+        for (int t = 0; t < 8; ++t) acc[u][t] = 0.0;
+    // thread: rows E (tid % 8) .. of the step, columns tid / 8 + 32 p.  Columns past
+    // M are read from column M - 1: they only reach outputs that are not stored.  A
+    // piece at or past r1 is read at r0 with weight 0 (one that starts before r1
+    // ends before lda: r1 <= the rows, lda >= them rounded up to 8).
+    const int piece = threadIdx.x & 7, c0 = threadIdx.x >> 3;
+    V va[P], vb[P];
+    double vw[E];
+    bool in = false;
     auto fetch = [&](int64_t s0) {
-        const int64_t k = s0 + GL * q;
-        const bool in = k < r1;
+        const int64_t k = s0 + E * piece;
+        in = k < r1;
         const int64_t kl = in ? k : r0;
 #pragma unroll
-        for (int u = 0; u < SW; ++u) load_seg<GL>(pa[u] + kl, na[u]);
+        for (int p = 0; p < P; ++p)
+            va[p] = *reinterpret_cast<const V*>(A + (int64_t)min(ta * kGT + c0 + 32 * p, M - 1) * lda + kl);
+        if (!diag) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t) load_seg<GL>(pb[t] + kl, nb[t]);
-        if (wt)
-            load_seg<GL>(wt + kl, nw);
-        else
+            for (int p = 0; p < P; ++p)
+                vb[p] = *reinterpret_cast<const V*>(A + (int64_t)min(tb * kGT + c0 + 32 * p, M - 1) * lda + kl);
+        }
 #pragma unroll
-            for (int e = 0; e < GL; ++e) nw[e] = 1.0;
-#pragma unroll
-        for (int e = 0; e < GL; ++e) nw[e] = in ? nw[e] : 0.0;
+        for (int e = 0; e < E; e += 2) {
+            const double2 x = *reinterpret_cast<const double2*>(wt + kl + e);
+            vw[e] = x.x, vw[e + 1] = x.y;
+        }
     };
     if (r0 < r1) fetch(r0);
-    for (int64_t s0 = r0; s0 < r1; s0 += 4 * GL) {
-        T cak[SW][GL], cbk[4][GL];
-        double cwk[GL];
+    for (int64_t s0 = r0; s0 < r1; s0 += K) {
+        double w[E];
 #pragma unroll
-        for (int e = 0; e < GL; ++e) {
-            cwk[e] = nw[e];
+        for (int e = 0; e < E; ++e) w[e] = in ? vw[e] : 0.0;
 #pragma unroll
-            for (int u = 0; u < SW; ++u) cak[u][e] = na[u][e];
+        for (int p = 0; p < P; ++p) {
+            double x[E], y[E];
+            unpack(va[p], x);
+            unpack(diag ? va[p] : vb[p], y);
 #pragma unroll
-            for (int t = 0; t < 4; ++t) cbk[t][e] = nb[t][e];
-        }
-        if (s0 + 4 * GL < r1) fetch(s0 + 4 * GL);
-#pragma unroll
-        for (int e = 0; e < GL; ++e) {
-#pragma unroll
-            for (int u = 0; u < SW; ++u) {
-                const double av = (double)cak[u][e] * cwk[e];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) acc[u][t] = mfma_f64(av, (double)cbk[t][e], acc[u][t]);
+            for (int e = 0; e < E; e += 2) {
+                *reinterpret_cast<double2*>(&as[c0 + 32 * p][E * piece + e]) = double2{x[e] * w[e], x[e + 1] * w[e + 1]};
+                *reinterpret_cast<double2*>(&bs[c0 + 32 * p][E * piece + e]) = double2{y[e], y[e + 1]};
             }
         }
+        __syncthreads();
+        if (s0 + K < r1) fetch(s0 + K);
+        if (mask) gram_step<K, LS>(as + u0, as + u1, bs, lane, mask, acc);
+        __syncthreads();
     }
+    const int S = min(M, kGT);
+    part += (int64_t)blockIdx.x * S * S;
 #pragma unroll
-    for (int u = 0; u < SW; ++u) {
-        const int band = wv * SW + u;  // 16-row band of the tile
+    for (int u = 0; u < 8; ++u)
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            if (diag && t < band) continue;  // below the diagonal: the reduction reads the mirror
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int a = ta * kGT + band * 16 + q + 4 * v, b = tb * kGT + t * 16 + c;
-                if (a < M && b < M) part[((int64_t)blockIdx.y * M + a) * M + b] = acc[u][t][v];
-            }
+        for (int t = 0; t < 8; ++t) {
+            const int a = (u < 4 ? u0 : u1) + (u & 3) * 4 + (lane >> 4), b = t * 16 + (lane & 15);
+            const int ga = ta * kGT + a, gb = tb * kGT + b;
+            if (gb < M && ga <= gb) part[a * S + b] = acc[u][t];
         }
-    }
 }
 
-// H[a][b] = H[b][a] = sum_c p1[c][a][b] - sum_c p2[c][a][b], a <= b: the Gram
-// kernel writes every entry of the upper triangle.
-__global__ void gram_reduce_kernel(const double* __restrict__ p1, int nc1, const double* __restrict__ p2, int nc2,
-                                   int M, double* __restrict__ H)
+// H[a][b] = H[b][a] = sum_c p1[c][a][b] - sum_c p2[c][a][b], a <= b, over the chunks c
+// of the entry's tile: the Gram kernel writes every entry of the upper triangle.
+__global__ void gram_reduce_kernel(const double* __restrict__ p1, GramPlan g1, const double* __restrict__ p2,
+                                   GramPlan g2, int M, double* __restrict__ H)
 {
-    const int64_t mm = (int64_t)M * M;
-    for (int64_t t = (int64_t)blockIdx.x * kT + threadIdx.x; t < mm; t += (int64_t)gridDim.x * kT) {
+    const int S = min(M, kGT);
+    for (int64_t t = (int64_t)blockIdx.x * kT + threadIdx.x; t < (int64_t)M * M; t += (int64_t)gridDim.x * kT) {
         const int a = (int)(t / M), b = (int)(t % M);
         if (a > b) continue;
+        const int ta = a / kGT, tb = b / kGT;
+        const int64_t at = (a - ta * kGT) * S + b - tb * kGT;
+        const GramTile t1 = gram_find(g1, M, ta, tb), t2 = gram_find(g2, M, ta, tb);
+        const double *q1 = p1 + (int64_t)(t1.first + t1.idx) * S * S + at, *q2 = p2 + (int64_t)(t2.first + t2.idx) * S * S + at;
         double s = 0.0;
 #pragma unroll 8
-        for (int c = 0; c < nc1; ++c) s += p1[c * mm + t];
+        for (int c = 0; c < t1.chunks; ++c) s += q1[(int64_t)c * t1.count * S * S];
 #pragma unroll 8
-        for (int c = 0; c < nc2; ++c) s -= p2[c * mm + t];
+        for (int c = 0; c < t2.chunks; ++c) s -= q2[(int64_t)c * t2.count * S * S];
         H[t] = s;
         H[(int64_t)b * M + a] = s;
     }
@@ -807,17 +887,36 @@ hipError_t launch_refit_grad(const float* D, int64_t ldd, int64_t n, int M, cons
     return hipGetLastError();
 }
 
-int gram_chunks(int64_t rows, int M)
+// Chunks of each kind of tile in proportion to what a step of it costs, so that
+// every workgroup takes the same time, in all at most two workgroups of four
+// wavefronts per CU: one round.  A step costs its wavefronts' blocks (16 for a tile
+// above the diagonal, 9 for one on it) plus the loads, barriers and LDS writes,
+// about kGramStep blocks' time: the two terms at 400,000 x 344 took 1324 and 312 us
+// with as many chunks for every tile, 1379 and 308 in proportion to the blocks
+// alone, 1110 and 266 with 10 (1129 and 266 with 20, 1163 and 265 with 40).
+constexpr int kGramStep = 10;
+GramPlan gram_plan(int64_t rows, int M)
 {
-    const int ntile = (M + kGT - 1) / kGT, npair = ntile * (ntile + 1) / 2;
-    // at most 1024 workgroups, resident in one round: the FP32 term's are one
-    // wavefront at one per SIMD, the FP64 term's two at two per SIMD
-    const int want = max(1, 1024 / npair);
-    const int64_t cap = max((int64_t)1, rows / 1024);
-    return (int)max((int64_t)1, min((int64_t)min(want, kGramChunks), cap));
+    const int nt1 = (M - 1) / kGT, last = (M - nt1 * kGT + 15) / 16;
+    const int cf = 16 + kGramStep, ce = 2 * last + kGramStep, cd = 9 + kGramStep,
+              cl = (last * (last + 1) / 2 + 3) / 4 + kGramStep;
+    const int total = nt1 * (nt1 - 1) / 2 * cf + nt1 * (ce + cd) + cl;
+    const int64_t cap = max((int64_t)1, min((int64_t)kGramChunks, rows / 1024));
+    auto chunks = [&](int cost) { return (int)max((int64_t)1, min(cap, (int64_t)(512 * cost / total))); };
+    return GramPlan{chunks(cf), chunks(ce), chunks(cd), chunks(cl)};
 }
 
-static int64_t gram_rows(int64_t rows, int nc) { return ((rows + nc - 1) / nc + kGR - 1) / kGR * kGR; }
+static int gram_grid(const GramPlan& g, int M)
+{
+    const int nt1 = (M - 1) / kGT;
+    return nt1 * (nt1 - 1) / 2 * g.full + nt1 * (g.edge + g.diag) + g.last;
+}
+
+size_t gram_part(int64_t rows, int M)
+{
+    const size_t S = min(M, kGT);
+    return (size_t)gram_grid(gram_plan(rows, M), M) * S * S;
+}
 
 int scan_chunks(int64_t n) { return (int)max((int64_t)1, (n + kScanChunk - 1) / kScanChunk); }
 
@@ -825,20 +924,20 @@ hipError_t launch_refit_hessian(const RefitHess& h, hipStream_t s)
 {
     const int M = h.M;
     if (M < 1 || M > kMaxRefit || h.ldd < refit_ld(h.n) || h.ldp < refit_ld(h.G)) return hipErrorInvalidValue;
-    const int ntile = (M + kGT - 1) / kGT, npair = ntile * (ntile + 1) / 2;
-    const int nc1 = gram_chunks(h.n, M), nc2 = gram_chunks(h.G, M), nch = scan_chunks(h.n);
+    const GramPlan g1 = gram_plan(h.n, M), g2 = gram_plan(h.G, M);
+    const int nch = scan_chunks(h.n);
     hipLaunchKernelGGL(hess_weight_kernel, dim3(grid_for(h.ldd)), dim3(kT), 0, s, h.perm, h.ev, h.r, h.n, h.ldd,
                        h.wt);
-    hipLaunchKernelGGL((gram_kernel<float, 8, 4>), dim3(npair, nc1), dim3(kT / 4), 0, s, h.D, h.ldd, h.n, M, h.wt,
-                       gram_rows(h.n, nc1), ntile, h.part1);
+    hipLaunchKernelGGL((gram_kernel<float>), dim3(gram_grid(g1, M)), dim3(kT), 0, s, h.D, h.ldd, h.n, M, h.wt, g1,
+                       h.part1);
     hipLaunchKernelGGL(scan_p_kernel, dim3(nch, M / kScanCols + 1), dim3(kT), 0, s, h.D, h.ldd, h.n, M, h.w, h.csum, nch, h.egidx,
                        h.G, h.ldp, h.P);
     hipLaunchKernelGGL(event_weight_kernel, dim3(grid_for(h.ldp)), dim3(kT), 0, s, h.P + (int64_t)M * h.ldp, h.egcnt,
                        h.G, h.ldp, h.wg);
-    hipLaunchKernelGGL((gram_kernel<double, 4, 2>), dim3(npair, nc2), dim3(kT / 2), 0, s, h.P, h.ldp, h.G, M, h.wg,
-                       gram_rows(h.G, nc2), ntile, h.part2);
-    hipLaunchKernelGGL(gram_reduce_kernel, dim3(grid_for((int64_t)M * M)), dim3(kT), 0, s, h.part1, nc1, h.part2,
-                       nc2, M, h.H);
+    hipLaunchKernelGGL((gram_kernel<double>), dim3(gram_grid(g2, M)), dim3(kT), 0, s, h.P, h.ldp, h.G, M, h.wg, g2,
+                       h.part2);
+    hipLaunchKernelGGL(gram_reduce_kernel, dim3(grid_for((int64_t)M * M)), dim3(kT), 0, s, h.part1, g1, h.part2,
+                       g2, M, h.H);
     return hipGetLastError();
 }
 
