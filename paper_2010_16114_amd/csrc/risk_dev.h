@@ -266,7 +266,7 @@ __device__ __forceinline__ void risk_resid_blk(const RiskArgs& a, int bx, int by
 
 // The objective of b's step and its stopping rule, one workgroup (every thread
 // holds L).
-__device__ __forceinline__ void stop_rule(const RiskArgs& a, int b, double L, double* sh)
+__device__ __forceinline__ void stop_rule(const RiskArgs& a, int b, double L, double* sh, double Llo = 0.0)
 {
     const FitCtl& c = a.ctl;
     double l1 = 0.0;
@@ -274,7 +274,10 @@ __device__ __forceinline__ void stop_rule(const RiskArgs& a, int b, double L, do
     l1 = block_sum(l1, sh);
     if (tid() == 0) {
         if (c.l1cov) l1 += c.l1cov[b];
-        const double f = -L + c.lam[b] * l1;
+        // -(L + Llo) + lam |beta|_1, rounded once: the sum's own error goes in with Llo
+        const double pen = c.lam[b] * l1, f0 = pen - L, z = f0 + L;
+        double f = f0;
+        if (Llo != 0.0) f += ((pen - z) - (L + (f0 - z))) - Llo;
         const int k = c.kit[b];
         double* h = c.hist + (int64_t)b * kMaxHist;
         h[k % kMaxHist] = f;

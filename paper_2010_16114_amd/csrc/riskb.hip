@@ -130,13 +130,27 @@ __global__ __launch_bounds__(kBT) void riskb_max_kernel(RiskArgs a)
     }
 }
 
+// A tile's w and the tiles' and workgroups' L terms are added with their rounding
+// errors kept (two sums), and the objective adds lambda |beta|_1 before its last
+// rounding.  Near the top of a path the w of a step are a few values just below 1,
+// whose additions all round the same way, and -L and the penalty change by 1e3 units
+// in the last place of L, their sum by none: with plain sums the objective of the
+// first step at 400,000 x 500,000 came out one unit above the start's.  The adds hide
+// behind the loads.
+__device__ __forceinline__ void add2(double& hi, double& lo, double v, double vlo)
+{
+    const double t = hi + v, z = t - hi;
+    lo += (hi - (t - z)) + (v - z) + vlo;
+    hi = t;
+}
+
 __global__ __launch_bounds__(kBT) void riskb_w_kernel(RiskArgs a)
 {
     __shared__ double st[kUnits * 16], sl[kUnits * 16];
     const Unit x = unit_of(a);
     const int bpad = a.bpad;
     if (blockIdx.x == 0) a.rkey[threadIdx.x] = 0;  // for the r pass of this step
-    double run = 0.0, l1 = 0.0;
+    double run = 0.0, rlo = 0.0, l1 = 0.0;
     if (x.on) {
         const double m = of_key(top_key(a.mkey, x.b));
         const int32_t* __restrict__ perm = a.ord.perm;
@@ -161,11 +175,11 @@ __global__ __launch_bounds__(kBT) void riskb_w_kernel(RiskArgs a)
             for (int q = 0; q < kPf; ++q) {
                 if (k0 + q >= x.t1) break;
                 const double v = e[q] - m, wk = exp(v);
-                run += wk;
+                add2(run, rlo, wk, 0.0);
                 if (d[q]) l1 += v;
                 w[(k0 + q) * bpad] = wk;
                 if (rk[q] != g) {  // an event group ends here
-                    sg[(int64_t)g * bpad] = run;
+                    sg[(int64_t)g * bpad] = run + rlo;
                     g = rk[q];
                 }
             }
@@ -173,6 +187,7 @@ __global__ __launch_bounds__(kBT) void riskb_w_kernel(RiskArgs a)
     }
     const int ng = bpad / 16, tpw = kUnits / ng;
     if (x.tl < tpw) {
+        run += rlo;
         st[x.tl * bpad + x.b] = run;
         sl[x.tl * bpad + x.b] = l1;
         a.stot[((int64_t)blockIdx.x * tpw + x.tl) * bpad + x.b] = run;
@@ -198,8 +213,9 @@ __global__ __launch_bounds__(kBT) void riskb_q_kernel(RiskArgs a)
     outer_sum(a.wgS, bpad, false, slice, off);
     double q = 0.0, l = 0.0;
     if (x.on) {
-        double before = off[x.b];
+        double before = 0.0;
         for (int t = 0; t < x.tl; ++t) before += a.stot[((int64_t)blockIdx.x * tpw + t) * bpad + x.b];
+        before += off[x.b];
         double* __restrict__ sg = a.S + x.b;
         const int32_t* __restrict__ cnt = a.egcnt;
         const int32_t g1 = a.egrank[x.t1];
@@ -229,11 +245,12 @@ __global__ __launch_bounds__(kBT) void riskb_q_kernel(RiskArgs a)
     }
     __syncthreads();
     if ((int)threadIdx.x < bpad) {
-        double s = 0.0, t = 0.0;
+        double s = 0.0, t = 0.0, lo = 0.0;
         for (int u = 0; u < tpw; ++u) {
             s += sq[u * bpad + threadIdx.x];
-            t += sl[u * bpad + threadIdx.x];
+            add2(t, lo, sl[u * bpad + threadIdx.x], 0.0);
         }
+        if (isfinite(t)) t += lo;
         a.wgQ[(int64_t)blockIdx.x * bpad + threadIdx.x] = s;
         a.Lpart[(int64_t)blockIdx.x * bpad + threadIdx.x] -= t;
     }
@@ -293,14 +310,23 @@ __global__ __launch_bounds__(kBT) void riskb_r_kernel(RiskArgs a)
 
 __global__ __launch_bounds__(riskdev::kT) void riskb_finish_kernel(RiskArgs a)
 {
-    __shared__ double sh[riskdev::kNW];
+    __shared__ double sh[riskdev::kNW], sl[riskdev::kNW];
     const int b = blockIdx.x;
     if (riskdev::skip_b(a, b)) return;
-    double L = 0.0;
-    for (int q = threadIdx.x; q < a.ntile; q += riskdev::kT) L += a.Lpart[(int64_t)q * a.bpad + b];
-    L = riskdev::block_sum(L, sh);
-    if (threadIdx.x == 0) a.L[b] = L;
-    if (a.use_ctl) riskdev::stop_rule(a, b, L, sh);
+    double L = 0.0, lo = 0.0;
+    for (int q = threadIdx.x; q < a.ntile; q += riskdev::kT) add2(L, lo, a.Lpart[(int64_t)q * a.bpad + b], 0.0);
+#pragma unroll
+    for (int o = kWave / 2; o > 0; o >>= 1) add2(L, lo, __shfl_xor(L, o, kWave), __shfl_xor(lo, o, kWave));
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    if (lane == 0) sh[wid] = L, sl[wid] = lo;
+    __syncthreads();
+    L = 0.0, lo = 0.0;
+#pragma unroll
+    for (int q = 0; q < riskdev::kNW; ++q) add2(L, lo, sh[q], sl[q]);
+    __syncthreads();
+    if (!isfinite(L)) lo = 0.0;
+    if (threadIdx.x == 0) a.L[b] = L + lo;
+    if (a.use_ctl) riskdev::stop_rule(a, b, L, sh, lo);
 }
 
 // The residual limbs of 16 subjects and one vector per thread, 16 adjacent lanes
