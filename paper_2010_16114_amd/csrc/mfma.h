@@ -98,9 +98,9 @@ struct MfmaDenseArgs {
     const double* dscale;   // [B]
     const int32_t* nonfin;  // [B] nonzero: eta_b = NaN (a coefficient was not finite)
     double* eta;            // [n][bpad], written
-    long long* part;        // [part_room] partial sums of the split blocks
+    long long* part;        // [part_room] partial sums of the split blocks (none: null, 0)
     int64_t part_room;
-    int ncu;                // compute units of the device
+    int ncu;                // compute units of the device, or 0
     int b0 = 0;                   // set by the launch: its first vector,
     int64_t nblk = 0, nfull = 0;  // blocks of subjects, and those that run unsplit,
     int ksplit = 1;               // shares of each of the others

@@ -30,6 +30,7 @@
 #include "device_common.h"
 #include "mfma.h"
 #include "mfma_dev.h"
+#include "mfma_plan.h"
 
 namespace cox {
 namespace {
@@ -306,22 +307,11 @@ template <int XT, int NG, int SUB>
 hipError_t launch_ng(MfmaDenseArgs a, hipStream_t s)
 {
     a.nblk = (a.n + SUB - 1) / SUB;
-    const int64_t slots = a.ncu, nstage = (a.p + 63) / 64, ntail = a.nblk % slots;
-    a.nfull = a.nblk - ntail;
-    // the last, partly filled round split over columns where that saves time (one workgroup per compute unit): rounds
-    // of shares x (their stages + the fill and flush of a workgroup, about 6 stages), and the room for the sums
-    a.ksplit = 1;
-    int64_t best = nstage + 6;
-    for (int64_t k = 2; k <= 16 && k <= nstage && ntail > 0; ++k) {
-        if (k * ntail * SUB * kSets * 16 * NG > a.part_room) break;
-        const int64_t c = (ntail * k + slots - 1) / slots * ((nstage + k - 1) / k + 6);
-        if (c < best) {
-            best = c;
-            a.ksplit = (int)k;
-        }
-    }
-    hipLaunchKernelGGL((mfma_dense_kernel<XT, NG, SUB>), dim3((unsigned)(a.nfull + ntail * a.ksplit)), dim3(kDT), 0, s,
-                       a);
+    const DensePlan d = dense_plan(a.nblk, (a.p + 63) / 64, a.ncu, (int64_t)SUB * kSets * 16 * NG, a.part_room);
+    a.nfull = d.nfull;
+    a.ksplit = d.ksplit;
+    hipLaunchKernelGGL((mfma_dense_kernel<XT, NG, SUB>), dim3((unsigned)(a.nfull + (a.nblk - a.nfull) * a.ksplit)),
+                       dim3(kDT), 0, s, a);
     if (a.ksplit > 1) {
         const int64_t m = (a.n - a.nfull * SUB) * 16 * NG;
         hipLaunchKernelGGL(dense_sum_kernel, dim3((unsigned)((m + kT - 1) / kT)), dim3(kT), 0, s, a, SUB, 16 * NG);
@@ -357,7 +347,8 @@ hipError_t launch_dense_quant(const double* coef, int64_t p, int B, double* dmax
 
 hipError_t launch_mfma_dense(const MfmaDenseArgs& a, hipStream_t s)
 {
-    if (a.bpad < 16 || a.bpad > 64 || a.bpad % 16 || a.B > a.bpad || a.ncu < 1 || !a.part) return hipErrorInvalidValue;
+    if (a.bpad < 16 || a.bpad > 64 || a.bpad % 16 || a.B > a.bpad || (a.part_room > 0 && !a.part))
+        return hipErrorInvalidValue;
     return a.xt == XT_FP8 ? launch_xt<XT_FP8>(a, s) : launch_xt<XT_I8>(a, s);
 }
 
