@@ -28,7 +28,7 @@ FLAGS = [
 
 
 # sources of the tuned matrix-core kernels: their hash keys the autotuner's cache
-TUNED = ["mfma.hip", "mfma.h", "mfma_dev.h", "device_common.h"]
+TUNED = ["mfma.hip", "mfma.h", "mfma_dev.h", "mfma_plan.h", "device_common.h"]
 
 
 def source_hash() -> str:

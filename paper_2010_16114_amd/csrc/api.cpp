@@ -1098,14 +1098,21 @@ cox_status cox_setup(cox_ctx** out, const cox_matrix* X, const double* time, con
         }
     }
     c->n_egroups = (int64_t)egc.size();
+    // the matrix-core passes can serve batches of more than kGroup vectors (use_mfma);
+    // sums that int32 does not hold whole are split for the compute units
+    bool mfma_able = X->xtype != COX_X_F32 && c->x.vec16 && max_batch > kGroup;
+    if (mfma_able && hipDeviceGetAttribute(&c->ncu, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) {
+        (void)hipGetLastError();
+        c->ncu = 0;
+    }
+    if (c->ncu <= 0 && std::max(n, p) > kMfmaMaxSum) mfma_able = false;
     std::vector<int32_t> egr;  // event groups that end before position k
-    if (X->xtype != COX_X_F32 && c->x.vec16 && max_batch > kGroup) {
+    if (mfma_able) {
         egr.resize(n + 1);
         egr[0] = 0;
         for (int64_t k = 0; k < n; ++k) egr[k + 1] = egr[k] + (egi[k] >= 0);
     }
 
-    const bool mfma_able = X->xtype != COX_X_F32 && c->x.vec16 && max_batch > kGroup;
     const int64_t Bn = (mfma_able ? round_up(max_batch, 16) : max_batch) * n, Bp = (int64_t)max_batch * p;
     bool ok = dalloc(c, &c->perm, n) && dalloc(c, &c->gstart, n) && dalloc(c, &c->gend, n) && dalloc(c, &c->ev, n) &&
               dalloc(c, &c->egidx, n) && dalloc(c, &c->egcnt, std::max<size_t>(1, egc.size())) &&
@@ -1140,14 +1147,13 @@ cox_status cox_setup(cox_ctx** out, const cox_matrix* X, const double* time, con
              dalloc(c, &c->geno_bad, 1) && dalloc(c, &c->dlimbs, (size_t)9 * c->bpad_max * c->dstride) &&
              dalloc(c, &c->dscale, max_batch) && dalloc(c, &c->dmaxp, (size_t)max_batch * ((c->dstride + 4095) / 4096)) &&
              dalloc(c, &c->nonfin, max_batch);
-        if (ok && hipDeviceGetAttribute(&c->ncu, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) {
-            (void)hipGetLastError();
-            c->ncu = 0;
-        }
         if (ok && c->ncu > 0) {
-            c->tail_cols = std::min((int64_t)6 * c->ncu * 256, 16 * p);
-            c->eta_words = std::max((int64_t)c->ncu * 2 * c->bpad_max * 256,
-                                    std::min(int64_t(12) << 20, 16 * round_up(n, 512) * 3 * 32));
+            // at least the shares that int32 sums need
+            const int64_t kn = min_shares((n + 127) / 128, 128), kp = min_shares((p + 63) / 64, 64);
+            c->tail_cols = std::max(std::min((int64_t)6 * c->ncu * 256, kMaxSplit * p), kn > 1 ? kn * p : 0);
+            c->eta_words = std::max({(int64_t)c->ncu * 2 * c->bpad_max * 256,
+                                     std::min(int64_t(12) << 20, kMaxSplit * round_up(n, 512) * 3 * 32),
+                                     kp > 1 ? kp * round_up(n, 512) * 3 * 32 : 0});
             ok = dalloc(c, &c->eta_part, (size_t)c->eta_words) &&
                  dalloc(c, &c->xtr_tail, (size_t)c->bpad_max * c->tail_cols);
         }

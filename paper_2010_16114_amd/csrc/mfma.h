@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "mfma_plan.h"
+
 namespace cox {
 
 // Row of the 16x16 accumulator tile held by vector register v of lane `lane`
@@ -32,7 +34,8 @@ struct MfmaArgs {
                             // 9 = 4+4, 4, 4; 10 = 4+4, 4, 5; 11 = 8+4, 2, 4; 12 = 8+4, 2, 3; with
                             // stages of 128 subjects (a whole 128-byte line per column): 13 = 4+4, 4, 2;
                             // 14 = 13 with streaming (non-temporal) loads of X; 15 = 14 with the
-                            // last, partly filled round of workgroups split over subjects
+                            // last, partly filled round of workgroups split over subjects (the one taken
+                            // whatever is asked for from kMfmaMaxSum subjects on)
     long long* tail = nullptr;  // shape 15: [ksplit][B][columns] exact sums of the split blocks
     int64_t tail_cols = 0;      // columns tail holds over all shares, per b: >= the split blocks' columns
     int ncu = 0;                // shape 15: compute units of the device
@@ -69,6 +72,7 @@ struct MfmaEtaArgs {
                             // with streaming loads; 12 = 5 with streaming loads
     long long* part;        // [sk_grid][2][256][bpad] partial sums of shared blocks (variants 8..12), or null
     int sk_grid;            // workgroups of variants 8..12: the compute units (0: one per block)
+    int64_t u0 = 0;         // set by the launch: positions of the change list before this run of it
 };
 
 // D_b(u) = dcoef[b][sel[u]] -> dlimbs, dscale (per-b step max|D_b| / 2^22)

@@ -5,8 +5,8 @@
 // g in {0, 1, 2} are exact in int8.  Each residual vector r_b is quantised to
 // integers R_b = round(r_b / q_b) with q_b = max_i |r_bi| / 2^22 and split into
 // three signed 8-bit limbs, R = d0 + 256 d1 + 65536 d2.  Every limb product is
-// then exact on v_mfma_i32_16x16x64_i8 with int32 accumulation (|sum| <=
-// 2 * 128 * n < 2^31 for n < 2^22), and
+// then exact on v_mfma_i32_16x16x64_i8 with int32 accumulation over up to
+// kMfmaMaxSum subjects (mfma_plan.h; more are taken in shares), and
 //     sum_i g_ij R_bi = acc0 + 256 acc1 + 65536 acc2      (exact, int64)
 // so the only rounding is that of r to 23 significant bits relative to its
 // largest entry.  The raw sums q_b * sum_i g_ij R_bi go to the same epilogue
@@ -525,8 +525,8 @@ __global__ __launch_bounds__(256 * NSPLIT, NSPLIT) void mfma_eta_kernel(MfmaEtaA
     using dchunk = typename std::conditional<D8, uint2, v4i>::type;
     __shared__ uint32_t sG[2][64 * SW];
     __shared__ v4i sD[2][4 * DS];
-    const int nsel = *a.nsel;
-    if (nsel == 0) return;
+    const int nsel = (int)min(*a.nsel - a.u0, kMfmaMaxSum);
+    if (nsel <= 0) return;
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int wsub = wid & 3, half = wid >> 2;
     const int64_t n = a.n, p = a.p, ldx = a.ldx;
@@ -721,8 +721,8 @@ __global__ __launch_bounds__(64 * (CW + LW), (CW + LW) / 4) void mfma_eta_split_
     constexpr bool DALL = DCH % LT == 0;  // every loader thread moves DPT chunks of D
     __shared__ uint32_t sG[NB][64 * SW];
     __shared__ v4i sD[NB][4 * DS];
-    const int nsel = *a.nsel;
-    if (nsel == 0) return;
+    const int nsel = (int)min(*a.nsel - a.u0, kMfmaMaxSum);
+    if (nsel <= 0) return;
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
     const int64_t n = a.n, ldx = a.ldx;
     const int nchunk = (nsel + 63) / 64;
@@ -988,8 +988,8 @@ __global__ __launch_bounds__(64 * (CW + LW), (CW + LW) / 4) void mfma_eta_split_
 __global__ __launch_bounds__(kT) void eta_fixup_kernel(MfmaEtaArgs a, int shares)
 {
     static_assert(kT == 256, "bpad workgroups of 256 threads cover a block's 256 x bpad sums");
-    const int nsel = *a.nsel;
-    if (nsel == 0) return;
+    const int nsel = (int)min(*a.nsel - a.u0, kMfmaMaxSum);
+    if (nsel <= 0) return;
     constexpr int SUB = 256;
     const int64_t n = a.n, G = shares;
     const int64_t nchunk = (nsel + 63) / 64;
@@ -1179,33 +1179,9 @@ hipError_t launch_lds(const MfmaArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
-// Shares each block of the last round's `ntail` blocks is split into, of nstage
-// stages each, on `slots` resident workgroups: the split with the least
-//     rounds of shares x (stages of a share + the fill and flush of a workgroup)
-//     + the shares' partial sums, written and read once (a stage moves 32 KB of X
-//     per compute unit in about 1.5 us; the sums move at about 4 TB/s).
-// A part-filled round costs a whole one, so 196 blocks of 1,563 stages on 256
-// slots take 4 rounds of 313 stages in fifths (1.91 ms at 200,000 x 50,000 x 64;
-// 2.09 ms unsplit), and 3 blocks of 24 stages take 2 stages in
-// twelfths (15 us; 21 us in thirds).
-int pick_ksplit(int64_t ntail, int64_t nstage, int64_t slots, int64_t ptail, int B, int64_t room)
-{
-    constexpr int64_t kFill = 6;
-    int best = 1;
-    double cost = 1e300;
-    for (int64_t k = 1; k <= 16 && k <= nstage && k * ptail <= room; ++k) {
-        const double c = (double)((ntail * k + slots - 1) / slots * ((nstage + k - 1) / k + kFill)) +
-                         (k > 1 ? 16.0 * (double)(k * ptail) * B / 6e6 : 0.0);
-        if (c < cost) {
-            cost = c;
-            best = (int)k;
-        }
-    }
-    return best;
-}
-
 // Shape 15's launch: the blocks of columns that fill whole rounds of resident
-// workgroups run unsplit, and the rest (the last round's) are split.
+// workgroups run unsplit, and the rest (the last round's) are split; with more subjects
+// than one int32 sum takes (kMfmaMaxSum) every block is.
 template <int XT, int NG, int RL, int CW, int LW, int MT, int LDF, bool NTX, int QC>
 hipError_t launch_lds_tail(const MfmaArgs& a, hipStream_t s)
 {
@@ -1217,12 +1193,14 @@ hipError_t launch_lds_tail(const MfmaArgs& a, hipStream_t s)
     if (e != hipSuccess) return e;
     if (per_cu < 1) return hipErrorInvalidConfiguration;
     const int64_t nblk = (a.p + WCOLS - 1) / WCOLS, slots = (int64_t)a.ncu * per_cu;
-    int64_t ntail = nblk % slots;
+    static_assert(QC == 8, "stages of 128 subjects");
+    const int64_t nstage = (a.n + 127) / 128;
+    int64_t ntail = min_shares(nstage, 128) > 1 ? nblk : nblk % slots;
     MfmaArgs b = a;
     b.nfull = nblk - ntail;
     const int64_t j0 = b.nfull * WCOLS, ptail = a.p - j0;
-    if (ntail > 0 && ptail > a.tail_cols) return hipErrorInvalidValue;
-    b.ksplit = pick_ksplit(ntail, (a.n + 16 * QC - 1) / (16 * QC), slots, ptail, a.B, a.tail_cols);
+    b.ksplit = xtr_split(ntail, nstage, slots, ptail, a.B, a.tail_cols);
+    if (b.ksplit < 1) return hipErrorInvalidValue;
     if (b.ksplit == 1) {  // no split pays: a last round of whole blocks, no partial sums
         b.nfull = nblk;
         ntail = 0;
@@ -1239,7 +1217,8 @@ hipError_t launch_lds_tail(const MfmaArgs& a, hipStream_t s)
 template <int XT, int NG, int RL>
 hipError_t launch_ng(const MfmaArgs& a, hipStream_t s)
 {
-    switch (a.variant) {
+    // only shape 15 splits the sums over more subjects than int32 takes
+    switch (a.n > kMfmaMaxSum ? 15 : a.variant) {
     case 5: return launch_split<XT, NG, RL, 7, 1, 3, 1, 6, 3>(a, s);
     case 6: return launch_split<XT, NG, RL, 7, 1, 3, 1, 4, 4>(a, s);
     case 7: return launch_split<XT, NG, RL, 6, 2, 3, 1, 6, 3>(a, s);
@@ -1283,7 +1262,7 @@ hipError_t launch_quantize_d(const double* dcoef, int64_t p, const int32_t* sel,
                              hipStream_t s)
 {
     if (dstride % 64 || dstride < p || bpad < B || bpad % 16) return hipErrorInvalidValue;
-    const int nt = (int)((p + 63) / 64 * 64 + 4095) / 4096;
+    const int nt = (int)(((p + 63) / 64 * 64 + 4095) / 4096);
     hipLaunchKernelGGL(dmax_kernel, dim3(nt, B), dim3(kT), 0, s, dcoef, p, sel, nsel, dmaxp, nt);
     hipLaunchKernelGGL(dquant_kernel, dim3(nt, B), dim3(kT), 0, s, dcoef, p, sel, nsel, dmaxp, nt, dlimbs, bpad,
                        dscale);
@@ -1294,7 +1273,15 @@ hipError_t launch_mfma_eta(const MfmaEtaArgs& a, hipStream_t s)
 {
     if (a.bpad < 16 || a.bpad > 64 || a.bpad % 16 || a.B > a.bpad || a.dstride % 64 || a.dstride < a.p)
         return hipErrorInvalidValue;
-    return a.xt == XT_FP8 ? launch_eta_xt<XT_FP8>(a, s) : launch_eta_xt<XT_I8>(a, s);
+    // runs of the change list of at most kMfmaMaxSum columns, one for all but huge p
+    MfmaEtaArgs b = a;
+    hipError_t e = hipSuccess;
+    for (b.u0 = 0; b.u0 < a.p && e == hipSuccess; b.u0 += kMfmaMaxSum) {
+        b.sel = a.sel + b.u0;
+        b.dlimbs = a.dlimbs + b.u0 * (kLimbs * a.bpad);
+        e = a.xt == XT_FP8 ? launch_eta_xt<XT_FP8>(b, s) : launch_eta_xt<XT_I8>(b, s);
+    }
+    return e;
 }
 
 hipError_t launch_mfma_xtr(const MfmaArgs& a, hipStream_t s)

@@ -5,7 +5,8 @@
 // |R| <= 2^22 (R1 is what R0's rounding leaves, on a scale 2^23 times finer, and so
 // on): q0_b = max_j |c_bj| / 2^22, q1 = 2^-23 q0, q2 = 2^-46 q0, rest at most
 // 2^-69 max|c_b|.  Every R goes as three signed int8 limbs (mfma.hip), so one
-// read of X meets nine limb columns per vector; the integer sums are exact, and
+// read of X meets nine limb columns per vector; the integer sums are exact (over more
+// than kMfmaMaxSum columns they are taken in shares, mfma_plan.h), and
 // eta = q0 S0 + q1 S1 + q2 S2 is three roundings.
 //
 // Up to 32 vectors go in one launch (48 and 64 in two, each reading X).  A
@@ -30,7 +31,6 @@
 #include "device_common.h"
 #include "mfma.h"
 #include "mfma_dev.h"
-#include "mfma_plan.h"
 
 namespace cox {
 namespace {
@@ -308,6 +308,7 @@ hipError_t launch_ng(MfmaDenseArgs a, hipStream_t s)
 {
     a.nblk = (a.n + SUB - 1) / SUB;
     const DensePlan d = dense_plan(a.nblk, (a.p + 63) / 64, a.ncu, (int64_t)SUB * kSets * 16 * NG, a.part_room);
+    if (d.ksplit < 1) return hipErrorInvalidValue;
     a.nfull = d.nfull;
     a.ksplit = d.ksplit;
     hipLaunchKernelGGL((mfma_dense_kernel<XT, NG, SUB>), dim3((unsigned)(a.nfull + (a.nblk - a.nfull) * a.ksplit)),

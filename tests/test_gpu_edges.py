@@ -248,3 +248,51 @@ def test_refit_blocks(n, M):
     np.testing.assert_allclose(coef, b, rtol=1e-8, atol=1e-9)
     np.testing.assert_allclose(se, np.sqrt(np.diag(cov)), rtol=1e-8)
     assert L == pytest.approx(oracle.loglik(oracle.xbeta(Mo, b), time, event)[0], rel=1e-12)
+
+
+def test_sums_longer_than_int32_holds(monkeypatch):
+    """From 2^23 subjects (columns) on the int8 limbs' int32 sums could wrap: they are
+    taken in shares, in the shapes too that do not split otherwise (X~' R 14, eta update
+    2).  2^23 + 512 tied subjects, 256 of them events: every censored residual is -256/n,
+    held as -128 q (lowest limb -128), against a column of twos.  2^24 + 64 equal columns,
+    whose equal steps have the top limb 64: one ISTA step moves them all, and a warm
+    start takes the dense product over them.  The gradient is off by at most q / 2 a
+    subject (q = max|r| / 2^22) and the FP32 output; the step and with it eta by 2^-22 of
+    themselves, the objective (at most 4 in size of its derivative's terms) by 1e-6."""
+    monkeypatch.setenv("COXHIP_MFMA_VARIANT", "14")
+    monkeypatch.setenv("COXHIP_ETA_VARIANT", "2")
+    B, ev = 9, 256
+    n = 2**23 + 512
+    X = torch.zeros((2, n), dtype=torch.int8, device="cuda")
+    X[0, ev:] = 2
+    event = np.zeros(n, np.int32)
+    event[:ev] = 1
+    cox = P.Cox(X, np.ones(n), event, xtype=P.X_INT8, max_batch=B)
+    loss, grad = cox.loss_grad(torch.zeros((B, 2), device="cuda"))
+    np.testing.assert_allclose(loss, ev * np.log(n), rtol=1e-12)
+    want = 2.0 * (n - ev) * ev / n
+    np.testing.assert_allclose(grad[:, 0].cpu().numpy(), want, rtol=2.0**-23, atol=2.0 * (n - ev) * 2.0**-23)
+    np.testing.assert_array_equal(grad[:, 1].cpu().numpy(), 0.0)
+    cox.close()
+    del cox, X, grad
+    n, p = 16, 2**24 + 64
+    X = torch.zeros((p, n), dtype=torch.int8, device="cuda")
+    X[:, 0] = 2
+    time = np.arange(n, 0, -1.0)  # subject 0 leaves last: it is in every risk set
+    cox = P.Cox(X, time, np.ones(n, np.int32), xtype=P.X_INT8, max_batch=B)
+
+    def negL(eta0):
+        e = np.exp(np.r_[eta0, np.zeros(n - 1)])
+        return np.log(np.cumsum(e)).sum() - eta0
+
+    g = 2.0 * (1.0 - (1.0 / np.arange(1, n + 1)).sum())
+    lams = np.linspace(0.5, 0.1, B) * abs(g)
+    step = 1.0 / (2.0 * p * abs(g))
+    beta, _, obj, _ = cox.fit_path(lams, max_iter=1, tol=0.0, step=step)
+    want = np.sign(g) * step * (abs(g) - lams)
+    f1 = np.array([negL(2.0 * p * b) + l * p * abs(b) for b, l in zip(want, lams)])
+    assert (np.abs(f1 - negL(0.0)) > 0.1).all()  # the step matters
+    np.testing.assert_allclose(beta[:, ::p - 1].cpu().numpy(), np.repeat(want[:, None], 2, 1), rtol=1e-6)
+    np.testing.assert_allclose(obj, f1, rtol=1e-6)
+    _, _, warm, _ = cox.fit_path(lams, max_iter=0, tol=0.0, step=step, beta=beta)
+    np.testing.assert_allclose(warm, f1, rtol=1e-6)
