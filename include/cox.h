@@ -370,8 +370,10 @@ typedef enum {
 /* The batched matrix-core passes (X~' R and the eta update, used when X holds
  * allele counts and B > 8) come in several pipeline shapes: COX_MFMA_VARIANTS
  * for X~' R, COX_MFMA_ETA_VARIANTS for the eta update.  The first batched call
- * times every shape on the live data (one untimed and three timed launches,
- * the median kept) and keeps the fastest (the
+ * times every shape of X~' R on the live data (one untimed and three timed
+ * launches, the median kept) and keeps the fastest; the eta update's are timed
+ * the same way on the first change list seen with 1,024 columns or half of X's
+ * (looked at in a fit's first update and every `poll` steps).  (The
  * environment variable COXHIP_TUNE_CACHE names a file that caches the choice;
  * COXHIP_MFMA_VARIANT and COXHIP_ETA_VARIANT force one; COXHIP_ETA_SHARES sets
  * how many workgroups the eta shapes that share blocks between workgroups use,

@@ -694,17 +694,29 @@ MfmaEtaArgs mfma_eta_args(cox_ctx* c, const int32_t* sel, const int32_t* nsel, i
     return m;
 }
 
+// Changed columns from which a change list tells the eta update's shapes apart (16
+// stages of 64, or half of a smaller X).  A fit's early lists, above all a warm
+// start's, can be empty, and every shape then returns at once.
+int64_t eta_tune_columns(const cox_ctx* c) { return std::min<int64_t>(1024, (c->p + 1) / 2); }
+
 // The eta update's pipeline shape: forced, cached, or timed once per context on
-// these arguments (writing into scratch, since the update is in place).
-cox_status pick_eta_variant(cox_ctx* c, MfmaEtaArgs* m)
+// these arguments (writing into scratch, since the update is in place) when the
+// change list is long enough.  The list is looked at where `look` is set (each look
+// waits for the stream); until then a shape that needs no timing serves: 10, the
+// fastest at 400,000 x 500,000 x 64 (23.1 ms; the others 23.3 to 33.6), or 0
+// where its 32-bit column offsets do not reach.
+cox_status pick_eta_variant(cox_ctx* c, MfmaEtaArgs* m, bool look)
 {
     const int forced = forced_variant("COXHIP_ETA_VARIANT", kMfmaEtaVariants);
     if (forced >= 0) {
         c->eta_variant = forced;
-    } else if (c->eta_variant < 0) {
-        const std::string key = tune_key(c, "eta", m->bpad);
-        c->eta_variant = tune_cache_lookup(key, kMfmaEtaVariants);
-        if (c->eta_variant < 0) {
+    } else if (c->eta_variant < 0 && look) {
+        int32_t nsel = 0;
+        STCHK(d2h(c, &nsel, m->nsel, sizeof(nsel)));
+        const bool filled = nsel >= eta_tune_columns(c);
+        const std::string key = filled ? tune_key(c, "eta", m->bpad) : std::string();
+        if (filled) c->eta_variant = tune_cache_lookup(key, kMfmaEtaVariants);
+        if (filled && c->eta_variant < 0) {
             MfmaEtaArgs t = *m;
             t.eta = c->w;
             c->eta_variant = autotune(
@@ -714,7 +726,7 @@ cox_status pick_eta_variant(cox_ctx* c, MfmaEtaArgs* m)
             tune_cache_store(key, c->eta_variant, c->eta_tune_ms, kMfmaEtaVariants);
         }
     }
-    m->variant = c->eta_variant;
+    m->variant = c->eta_variant >= 0 ? c->eta_variant : (m->ldx < (int64_t(1) << 32) ? 10 : 0);
     return COX_OK;
 }
 
@@ -1535,7 +1547,8 @@ cox_status cox_fit_path(cox_ctx* c, const double* lambdas, int32_t B, const cox_
                                          c->dscale, c->stream),
                        "quantise eta update");
                 MfmaEtaArgs m = mfma_eta_args(c, c->sel, c->nsel, B, c->active);
-                STCHK(pick_eta_variant(c, &m));
+                // looked at in a call's first update and where the last step's poll waited already
+                STCHK(pick_eta_variant(c, &m, it == it0 + 1 || it % poll == 0));
                 tmark(c, COX_PHASE_ETA_KERNEL);
                 HIPCHK(launch_mfma_eta(m, c->stream), "eta update on matrix cores");
                 tmark(c, COX_PHASE_ETA_KERNEL);

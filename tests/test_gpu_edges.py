@@ -296,3 +296,31 @@ def test_sums_longer_than_int32_holds(monkeypatch):
     np.testing.assert_allclose(obj, f1, rtol=1e-6)
     _, _, warm, _ = cox.fit_path(lams, max_iter=0, tol=0.0, step=step, beta=beta)
     np.testing.assert_allclose(warm, f1, rtol=1e-6)
+
+
+def test_eta_shapes_are_timed_on_a_filled_list(tmp_path, monkeypatch):
+    """A batch warm-started where nothing moves (lambda above lambda_max, beta 0) has an
+    empty change list, on which every shape of the eta update takes no time: none is
+    kept or stored.  The next fit, whose first steps move most columns, is timed."""
+    cache = tmp_path / "tune.json"
+    monkeypatch.setenv("COXHIP_TUNE_CACHE", str(cache))
+    for v in ("COXHIP_MFMA_VARIANT", "COXHIP_ETA_VARIANT"):
+        monkeypatch.delenv(v, raising=False)
+    B = 16
+    d = coxsim.genotype_problem(1000, 600, 4, 0.3, 77, days=True)
+    cox, _ = device_problem(d, "int8", ldx=1008, max_batch=B)
+    lm = cox.lambda_max()
+    sigma = 1.0 / (2.0 * cox.opnorm2()[0])
+    beta, _, _, _ = cox.fit_path(lm * np.linspace(3.0, 2.0, B), max_iter=20, tol=0.0, step=sigma,
+                                 beta=torch.zeros((B, 600), device="cuda"))
+    assert not beta.any()
+    assert cox.mfma_tuning()["eta_variant"] == -1 and '"eta|' not in cache.read_text()
+    lams = coxsim.lambda_grid(lm, B, 0.01)
+    beta, _, obj, _ = cox.fit_path(lams, max_iter=5, tol=0.0, step=sigma)
+    t = cox.mfma_tuning()
+    assert t["eta_variant"] >= 0 and all(m > 0 for m in t["eta_ms"][:P.ETA_VARIANTS])
+    assert '"eta|' in cache.read_text()
+    monkeypatch.setenv("COXHIP_ETA_VARIANT", "10")  # the shape that serves meanwhile: the same integer sums
+    again, _, oagain, _ = cox.fit_path(lams, max_iter=5, tol=0.0, step=sigma)
+    _bits(again.cpu().numpy(), beta.cpu().numpy())
+    _bits(oagain, obj)
