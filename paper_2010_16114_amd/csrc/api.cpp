@@ -547,8 +547,8 @@ cox_status dense_eta(cox_ctx* c, const double* coef, int B, const double* shift,
 // median of kTuneReps timed launches; a shape whose launch fails is never
 // chosen) and written to that file.  The cache is one JSON object whose keys
 // name the pass, the device, its architecture, the source of the kernels
-// (COXHIP_SRC_HASH, set by the build) and the problem's shape; each value holds
-// the chosen shape and the medians.  Entries that do not parse, name a shape
+// (COXHIP_SRC_HASH, set by the build) with how X's columns lie in 128-byte lines,
+// and the problem's shape; each value holds the chosen shape and the medians.  Entries that do not parse, name a shape
 // out of range or carry another key are ignored, so an old or corrupt file
 // leads to a fresh tuning, never to a wrong shape.
 #ifndef COXHIP_SRC_HASH
@@ -579,7 +579,11 @@ std::string tune_key(const cox_ctx* c, const char* kernel, int bpad)
     for (char& ch : arch)
         if (ch == '"' || ch == '\\' || (unsigned char)ch < 0x20) ch = '_';
     std::ostringstream os;
-    os << kernel << "|" << dev << "|" << arch << "|src:" << COXHIP_SRC_HASH << "|xt" << c->x.xt << "|n" << c->n
+    // 16-byte chunks into a line that X and its second column start, from the first: a shape
+    // that loads whole lines and one that does not differ by it (521 and 293 us at 100,003 x
+    // 20,001 x 16 for columns 3 chunks apart)
+    os << kernel << "|" << dev << "|" << arch << "|src:" << COXHIP_SRC_HASH << "+lines"
+       << reinterpret_cast<uintptr_t>(c->x.X) % 128 / 16 << "." << c->x.ldx % 128 / 16 << "|xt" << c->x.xt << "|n" << c->n
        << "|p" << c->p << "|b" << bpad;
     return os.str();
 }

@@ -324,3 +324,24 @@ def test_eta_shapes_are_timed_on_a_filled_list(tmp_path, monkeypatch):
     again, _, oagain, _ = cox.fit_path(lams, max_iter=5, tol=0.0, step=sigma)
     _bits(again.cpu().numpy(), beta.cpu().numpy())
     _bits(oagain, obj)
+
+
+def test_tune_cache_keeps_layouts_apart(tmp_path, monkeypatch):
+    """A shape timed for columns on whole 128-byte lines is not taken from the cache for
+    columns that are not, nor for an X that starts inside a line, and is for its own."""
+    cache = tmp_path / "tune.json"
+    monkeypatch.setenv("COXHIP_TUNE_CACHE", str(cache))
+    for v in ("COXHIP_MFMA_VARIANT", "COXHIP_ETA_VARIANT"):
+        monkeypatch.delenv(v, raising=False)
+    B, n, p = 16, 500, 130
+    d = coxsim.genotype_problem(n, p, 4, 0.3, 78, days=True)
+    timed = []
+    for ldx, lead in ((512, 0), (528, 0), (512, 16), (512, 0)):
+        buf = torch.zeros(p * ldx + 256, dtype=torch.uint8)
+        buf[lead:lead + p * ldx].view(p, ldx)[:, :n] = torch.from_numpy(coxsim.FP8_E4M3_CODE[d.G])
+        X = buf.cuda()[lead:lead + p * ldx].view(p, ldx)
+        cox = P.Cox(X, d.time, d.event, xtype=P.X_FP8_E4M3, n=n, max_batch=B)
+        cox.loss_grad(torch.zeros((B, p), device="cuda"))
+        timed.append(any(cox.mfma_tuning()["xtr_ms"]))
+    assert timed == [True, True, True, False]
+    assert cache.read_text().count('"xtr|') == 3
