@@ -45,8 +45,10 @@ namespace {
 constexpr int kMaxBatch = 64;
 // Column groups of the eta update, at most: up to about four workgroups per compute
 // unit over (1,024 rows, column group), their partial sums added by the risk-set pass
-// (at 20,000 rows 16 groups 8.7 us, four 17; at 1,000 rows 6.3 and 11.9)
+// (at 20,000 rows 16 groups 8.7 us, four 17; at 1,000 rows 6.3 and 11.9).  Batches of
+// more than kGroup vectors take fewer where the sums outgrow the workspace (upd_groups).
 constexpr int kUpdGroups = 16;
+constexpr int64_t kUpdRoom = int64_t(8) << 20;  // doubles that the groups of any batch may take
 constexpr int kGroup = 8;  // coefficient vectors per VALU pass over X
 constexpr int kFreeCovMaxIter = 100000;  // steps of the unpenalised covariate fit inside cox_lambda_max
 constexpr double kFreeCovGtol = 1e-10;   // its stop: max |g_k| below this fraction of its value at zero
@@ -93,9 +95,15 @@ struct cox_ctx {
     // g-th such group (-1 elsewhere), egcnt[g] = its events
     int32_t *egidx = nullptr, *egcnt = nullptr;
     int64_t n_egroups = 0;
-    double *eta = nullptr, *w = nullptr, *S = nullptr, *T = nullptr, *r64 = nullptr;
+    // state of the subjects: [Bmax][n] each; in the batched form rows of Bmax16, where
+    // r64 takes T's room too and w and S_rows share another split of w's and S's
+    double *eta = nullptr, *w = nullptr, *S = nullptr, *T = nullptr, *r64 = nullptr, *S_rows = nullptr;
     float* r32 = nullptr;
-    double *part_upd = nullptr, *part_gemv = nullptr;
+    // partial sums that live from one launch to the next, in one buffer: the eta update's
+    // column groups, the dense X beta's column blocks, and the split blocks of the
+    // matrix-core passes (eta update, dense product, the last round of X~' R)
+    double* part = nullptr;
+    int64_t part_words = 0;
     int64_t tile = 0;
     int ntile = 0, nfin = 0;
     double* part_xtr = nullptr;  // [nsplit][Bmax][p] split partials of X' r
@@ -108,12 +116,9 @@ struct cox_ctx {
     double *rb_tot = nullptr, *rb_wg = nullptr;  // tile and workgroup totals of the risk-set passes
     unsigned long long* keys = nullptr;          // [3][kKeys]: max eta, max |r|, sums of R; then a counter
     int* geno_bad = nullptr;
-    int8_t* dlimbs = nullptr;    // [dstride][9 Bmax16] limbs of the dense product; the eta update uses 3
+    int8_t* dlimbs = nullptr;    // [dstride][3 Bmax16] limbs of the eta update, behind dcoef
+    int8_t* climbs = nullptr;    // [dstride][9 Bmax16] limbs of the dense product, over dcoef and dlimbs
     int32_t* nonfin = nullptr;   // [max_batch] a dense pass's coefficient vector holds a NaN or infinity
-    long long* eta_part = nullptr;  // partial sums of blocks several workgroups share: [ncu][2][256][Bmax16] of the eta
-    int64_t eta_words = 0;          // update; the dense product's split blocks take up to 12 M of the words
-    long long* xtr_tail = nullptr;  // [Bmax16][tail_cols] X~' R sums of the split last round (shape 15)
-    int64_t tail_cols = 0;       // its columns over all shares: up to 6 shares of a full round, 16 of a small one
     int ncu = 0;                 // compute units of the device
     int64_t dstride = 0;
     double *dscale = nullptr, *dmaxp = nullptr;
@@ -534,7 +539,7 @@ cox_status dense_eta(cox_ctx* c, const double* coef, int B, const double* shift,
     }
     for (int b0 = 0; b0 < B; b0 += kGroup) {
         const int nb = std::min(kGroup, B - b0);
-        HIPCHK(launch_gemv(c->x, coef, b0, nb, c->part_gemv, c->ncb, c->eta, shift, c->stream), "dense X beta");
+        HIPCHK(launch_gemv(c->x, coef, b0, nb, c->part, c->ncb, c->eta, shift, c->stream), "dense X beta");
     }
     tmark(c, COX_PHASE_ETA);
     return COX_OK;
@@ -690,7 +695,8 @@ int autotune(cox_ctx* c, int count, F&& launch, float* ms_out)
 MfmaEtaArgs mfma_eta_args(cox_ctx* c, const int32_t* sel, const int32_t* nsel, int B, const int32_t* active)
 {
     MfmaEtaArgs m{c->x.X, c->x.xt, c->n, c->p, c->x.ldx, sel, nsel, c->dlimbs, c->dstride,
-                  (int)round_up(B, 16), B, c->dscale, c->eta, active, 0, c->eta_part, c->ncu};
+                  (int)round_up(B, 16), B, c->dscale, c->eta, active, 0,
+                  c->ncu > 0 ? reinterpret_cast<long long*>(c->part) : nullptr, c->ncu};
     if (const char* e = std::getenv("COXHIP_ETA_SHARES")) {
         const int v = std::atoi(e);
         if (v > 0 && v <= c->ncu) m.sk_grid = v;
@@ -743,10 +749,11 @@ cox_status dense_eta_mfma(cox_ctx* c, const double* coef, int B)
 {
     const int bpad = (int)round_up(B, 16);
     HIPCHK(launch_fill_i32(c->nonfin, 0, B, c->stream), "clear flags");
-    HIPCHK(launch_dense_quant(coef, c->p, B, c->dmaxp, c->dlimbs, c->dstride, bpad, c->dscale, c->nonfin, c->stream),
+    HIPCHK(launch_dense_quant(coef, c->p, B, c->dmaxp, c->climbs, c->dstride, bpad, c->dscale, c->nonfin, c->stream),
            "quantise coefficients");
-    MfmaDenseArgs m{c->x.X, c->x.xt,   c->n,      c->p,   c->x.ldx,    c->dlimbs,    c->dstride, bpad,
-                    B,      c->dscale, c->nonfin, c->eta, c->eta_part, c->eta_words, c->ncu};
+    MfmaDenseArgs m{c->x.X,    c->x.xt,   c->n,   c->p, c->x.ldx,  c->climbs,
+                    c->dstride, bpad,     B,      c->dscale, c->nonfin, c->eta,
+                    reinterpret_cast<long long*>(c->part), c->part_words, c->ncu};
     tmark(c, COX_PHASE_ETA_KERNEL);
     HIPCHK(launch_mfma_dense(m, c->stream), "dense X beta on matrix cores");
     tmark(c, COX_PHASE_ETA_KERNEL);
@@ -775,6 +782,13 @@ bool use_mfma(cox_ctx* c, int B)
     return c->geno_state == 0;
 }
 
+// Column groups of the vector form's eta update for B vectors: as many as their sums
+// find room for, kUpdGroups' rule at the most.
+int upd_groups(const cox_ctx* c, int B)
+{
+    return (int)std::max<int64_t>(1, std::min<int64_t>(c->ncg, c->part_words / ((int64_t)B * c->n)));
+}
+
 // rows: the batched form, its state in rows (use_mfma(c, B), or false)
 RiskArgs risk_args(cox_ctx* c, int B, bool rows)
 {
@@ -786,8 +800,8 @@ RiskArgs risk_args(cox_ctx* c, int B, bool rows)
     a.eta_in_f32 = 0;
     a.eta = c->eta;
     a.part = nullptr;
-    a.ncg = c->ncg;
-    a.part_cstride = (int64_t)c->Bmax * c->n;
+    a.ncg = upd_groups(c, B);
+    a.part_cstride = (int64_t)B * c->n;
     a.nsel = c->nsel;
     a.w = c->w;
     a.S = c->S;
@@ -810,6 +824,8 @@ RiskArgs risk_args(cox_ctx* c, int B, bool rows)
     if (rows) {  // the matrix-core pass quantises the FP64 residual itself
         a.r32 = nullptr;
         a.r64 = c->r64;
+        a.S = c->S_rows;
+        a.T = nullptr;
         a.bpad = (int)round_up(B, 16);
         a.egrank = c->egrank;
         a.egcnt = c->egcnt;
@@ -861,8 +877,8 @@ cox_status run_gemvt(cox_ctx* c, GemvtArgs g, int B, bool rows, int rlimbs = 3)
                "quantise r");
         MfmaArgs m{c->x.X,   c->x.xt, c->n, c->p,      c->x.ldx,     c->limbs, c->rstride,
                    bpad,     rlimbs,  B,    c->qscale, c->part_xtr, 0};
-        m.tail = c->xtr_tail;
-        m.tail_cols = c->tail_cols;
+        m.tail = reinterpret_cast<long long*>(c->part);
+        m.tail_cols = c->part_words / B;
         m.ncu = c->ncu;
         int& chosen = c->xtr_by_limbs[rlimbs];
         const int forced = forced_variant("COXHIP_MFMA_VARIANT", kMfmaVariants);
@@ -1129,13 +1145,38 @@ cox_status cox_setup(cox_ctx** out, const cox_matrix* X, const double* time, con
         for (int64_t k = 0; k < n; ++k) egr[k + 1] = egr[k] + (egi[k] >= 0);
     }
 
-    const int64_t Bn = (mfma_able ? round_up(max_batch, 16) : max_batch) * n, Bp = (int64_t)max_batch * p;
+    // the state of the subjects in both forms (cox_ctx)
+    const int64_t Bn = (int64_t)max_batch * n, Bp = (int64_t)max_batch * p, vec = round_up(Bn, 32);
+    const int64_t rowsn = mfma_able ? round_up(round_up(max_batch, 16) * n, 32) : 0;
+    const int64_t ws = std::max(2 * vec, rowsn + (mfma_able ? round_up(max_batch, 16) * c->n_egroups : 0));
+    // partial sums: the dense X beta's; the eta update's column groups, all of them for up
+    // to kGroup vectors and, for more, as many as fit kUpdRoom or the dense X beta's and
+    // four (fewer from 128 x 1,024 rows on); the matrix-core passes' split blocks
+    const int64_t gemv_words = std::max<int64_t>((int64_t)c->ncb * kGroup, (int64_t)gemv16_blocks(n, p) * 4) * n;
+    const int64_t few = std::max<int64_t>(1, std::min<int64_t>(4, 512 / nslab));
+    c->part_words = std::max({gemv_words, (int64_t)c->ncg * std::min(max_batch, kGroup) * n,
+                              std::min(c->ncg * Bn, std::max(few * Bn + gemv_words, kUpdRoom))});
+    if (mfma_able && c->ncu > 0) {
+        // the eta update's: [ncu][2][256][Bmax16]; the dense product's: up to 12 M words; X~' R's:
+        // up to 6 shares of a full round of columns, 16 of a small one; at least the shares
+        // that int32 sums need
+        const int64_t kn = min_shares((n + 127) / 128, 128), kp = min_shares((p + 63) / 64, 64);
+        const int64_t bp = round_up(max_batch, 16), rows = round_up(n, 512) * 3 * 32;
+        const int64_t tail = std::max(std::min((int64_t)6 * c->ncu * 256, kMaxSplit * p), kn > 1 ? kn * p : 0);
+        c->part_words = std::max({c->part_words, (int64_t)c->ncu * 2 * bp * 256, max_batch * tail,
+                                  std::min(int64_t(12) << 20, kMaxSplit * rows), kp > 1 ? kp * rows : 0});
+    }
+    // the eta update's limbs stand behind dcoef, the dense product's over both (no call
+    // needs the change of its last step after one)
+    const int64_t dcoef_bytes = round_up(8 * Bp, 256), dl = mfma_able ? round_up(max_batch, 16) * round_up(p, 64) : 0;
+    int8_t* changes = nullptr;
     bool ok = dalloc(c, &c->perm, n) && dalloc(c, &c->gstart, n) && dalloc(c, &c->gend, n) && dalloc(c, &c->ev, n) &&
               dalloc(c, &c->egidx, n) && dalloc(c, &c->egcnt, std::max<size_t>(1, egc.size())) &&
-              dalloc(c, &c->eta, Bn) && dalloc(c, &c->w, Bn) && dalloc(c, &c->S, Bn) && dalloc(c, &c->T, Bn) &&
-              dalloc(c, &c->r64, Bn) && dalloc(c, &c->r32, (size_t)max_batch * c->rstride) &&
-              dalloc(c, &c->part_upd, (size_t)c->ncg * Bn) && dalloc(c, &c->part_gemv, (size_t)std::max<int64_t>((int64_t)c->ncb * kGroup, (int64_t)gemv16_blocks(n, p) * 4) * n) &&
-              dalloc(c, &c->beta64, Bp) && dalloc(c, &c->coef, Bp) && dalloc(c, &c->dcoef, Bp) &&
+              dalloc(c, &c->eta, std::max(vec, rowsn)) && dalloc(c, &c->w, ws) &&
+              dalloc(c, &c->r64, std::max(2 * vec, rowsn)) &&
+              dalloc(c, &c->r32, (size_t)max_batch * c->rstride) && dalloc(c, &c->part, c->part_words) &&
+              dalloc(c, &c->beta64, Bp) && dalloc(c, &c->coef, Bp) &&
+              dalloc(c, &changes, std::max(dcoef_bytes + 3 * dl, 9 * dl)) &&
               dalloc(c, &c->g64, Bp) && dalloc(c, &c->chg_flag, p) && dalloc(c, &c->chg_cnt, c->nblk) &&
               dalloc(c, &c->chg_idx, (size_t)c->nblk * kGemvtCols) && dalloc(c, &c->sel, p) &&
               dalloc(c, &c->nsel, 1) && dalloc(c, &c->l1old, (size_t)max_batch * c->nblk) &&
@@ -1154,25 +1195,23 @@ cox_status cox_setup(cox_ctx** out, const cox_matrix* X, const double* time, con
               dalloc(c, &c->l1c_new, max_batch) && dalloc(c, &c->pf, p + kMaxCov) &&
               dalloc(c, &c->bar_words, persist_barrier_words()) && dalloc(c, &c->col_count, 1) &&
               dalloc(c, &c->red_part, kRedParts);
+    if (ok) {
+        c->S = c->w + vec;
+        c->T = c->r64 + vec;
+        c->S_rows = c->w + rowsn;
+        c->dcoef = reinterpret_cast<double*>(changes);
+        c->dlimbs = changes + dcoef_bytes;
+        c->climbs = changes;
+    }
     if (ok && mfma_able) {
         c->bpad_max = (int)round_up(max_batch, 16);
         c->dstride = round_up(p, 64);
         ok = dalloc(c, &c->limbs, (size_t)3 * c->bpad_max * c->rstride) && dalloc(c, &c->qscale, max_batch) &&
              dalloc(c, &c->egrank, n + 1) && dalloc(c, &c->rb_tot, (size_t)32 * riskb_tiles()) &&
              dalloc(c, &c->rb_wg, (size_t)192 * riskb_wgs()) && dalloc(c, &c->keys, 3 * kKeys + 1) &&
-             dalloc(c, &c->geno_bad, 1) && dalloc(c, &c->dlimbs, (size_t)9 * c->bpad_max * c->dstride) &&
-             dalloc(c, &c->dscale, max_batch) && dalloc(c, &c->dmaxp, (size_t)max_batch * ((c->dstride + 4095) / 4096)) &&
+             dalloc(c, &c->geno_bad, 1) && dalloc(c, &c->dscale, max_batch) &&
+             dalloc(c, &c->dmaxp, (size_t)max_batch * ((c->dstride + 4095) / 4096)) &&
              dalloc(c, &c->nonfin, max_batch);
-        if (ok && c->ncu > 0) {
-            // at least the shares that int32 sums need
-            const int64_t kn = min_shares((n + 127) / 128, 128), kp = min_shares((p + 63) / 64, 64);
-            c->tail_cols = std::max(std::min((int64_t)6 * c->ncu * 256, kMaxSplit * p), kn > 1 ? kn * p : 0);
-            c->eta_words = std::max({(int64_t)c->ncu * 2 * c->bpad_max * 256,
-                                     std::min(int64_t(12) << 20, kMaxSplit * round_up(n, 512) * 3 * 32),
-                                     kp > 1 ? kp * round_up(n, 512) * 3 * 32 : 0});
-            ok = dalloc(c, &c->eta_part, (size_t)c->eta_words) &&
-                 dalloc(c, &c->xtr_tail, (size_t)c->bpad_max * c->tail_cols);
-        }
     }
     if (ok) {
         c->pinned_bytes = 64 * 1024;
@@ -1204,7 +1243,7 @@ cox_status cox_setup(cox_ctx** out, const cox_matrix* X, const double* time, con
     chk(launch_fill_f64(reinterpret_cast<double*>(c->r32), 0.0, (int64_t)max_batch * c->rstride / 2, c->stream));
     chk(launch_fill_i32(c->chg_flag, 0, p, c->stream));
     chk(launch_fill_i32(c->nsel, 0, 1, c->stream));
-    chk(launch_fill_f64(c->eta, 0.0, Bn, c->stream));
+    chk(launch_fill_f64(c->eta, 0.0, std::max(vec, rowsn), c->stream));
     chk(launch_fill_f64(c->pf, 1.0, p, c->stream));
     chk(launch_fill_f64(c->pf + p, 0.0, kMaxCov, c->stream));
     if (c->limbs)
@@ -1501,7 +1540,7 @@ cox_status cox_fit_path(cox_ctx* c, const double* lambdas, int32_t B, const cox_
     }
 
     RiskArgs ra = risk_args(c, B, mfma);
-    ra.part = (o.eta_mode == 0 && !mfma) ? c->part_upd : nullptr;
+    ra.part = (o.eta_mode == 0 && !mfma) ? c->part : nullptr;
     ra.use_ctl = 1;
     ra.ctl = FitCtl{c->lam, c->l1new, c->nblk, c->hist, c->kit, c->active, c->iters, c->status, c->fobj,
                     q ? c->l1c_new : nullptr, o.max_iter, o.lag, o.tol, nullptr, 0};
@@ -1520,10 +1559,10 @@ cox_status cox_fit_path(cox_ctx* c, const double* lambdas, int32_t B, const cox_
     g.lam = c->lam;
     g.step = step;
     g.active = c->active;
-    const int64_t cstride = (int64_t)c->Bmax * c->n;
+    const int64_t cstride = ra.part_cstride;
 
     if (o.persistent) {
-        PersistArgs pa{ra, g, c->sel, c->sel, c->nsel, c->dcoef, c->part_upd, cstride, c->ncg, o.max_iter, B};
+        PersistArgs pa{ra, g, c->sel, c->sel, c->nsel, c->dcoef, c->part, cstride, ra.ncg, o.max_iter, B};
         pa.g.b0 = 0;
         pa.g.nb = B;
         pa.g.first_group = 1;
@@ -1561,7 +1600,7 @@ cox_status cox_fit_path(cox_ctx* c, const double* lambdas, int32_t B, const cox_
                 tmark(c, COX_PHASE_ETA);
                 for (int b0 = 0; b0 < B; b0 += kGroup)
                     HIPCHK(launch_eta_update(c->x, c->sel, c->nsel, c->dcoef, b0, std::min(kGroup, B - b0),
-                                             c->part_upd, cstride, c->ncg, c->active, c->stream),
+                                             c->part, cstride, ra.ncg, c->active, c->stream),
                            "eta update");
                 tmark(c, COX_PHASE_ETA);
             } else {

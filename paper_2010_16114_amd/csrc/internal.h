@@ -152,8 +152,8 @@ struct PersistArgs {
     int32_t* sel_w;        // the same buffer, written by the compaction
     int32_t* nsel;
     const double* dcoef;   // [B][p] coefficient changes times the genotype scale
-    double* part_upd;      // [ncg][Bmax][n] eta partials
-    int64_t cstride;       // Bmax * n
+    double* part_upd;      // [ncg][B][n] eta partials
+    int64_t cstride;       // B * n
     int ncg;
     int max_iter;
     int B;

@@ -345,3 +345,34 @@ def test_tune_cache_keeps_layouts_apart(tmp_path, monkeypatch):
         timed.append(any(cox.mfma_tuning()["xtr_ms"]))
     assert timed == [True, True, True, False]
     assert cache.read_text().count('"xtr|') == 3
+
+
+@pytest.mark.parametrize("storage,n,p,B", [("f32", 60000, 40, 64), ("fp8", 60000, 400, 64), ("int8", 2000, 20000, 64),
+                                           ("fp8", 30000, 1000, 33), ("f32", 1000, 2000, 64), ("fp8", 200000, 64, 16)])
+def test_workspace_of_a_handle(storage, n, p, B):
+    """What a handle holds on the device: five B x n FP64 arrays of state and the FP32
+    residual, four column groups of eta updates (two from 128 x 1,024 rows on) and the
+    dense X beta's partial sums, four B x p FP64 arrays and the split sums of X'r, and on the
+    matrix cores three limbs per vector, row and column and five rounds of 256 x 256
+    sums per vector padded to 16.  Everything else is small beside it: 5% and the 64 MB that the
+    column groups of any batch may take."""
+    up = lambda a, m: (a + m - 1) // m * m  # noqa: E731
+    one = storage != "f32"
+    X = torch.zeros((p, up(n, 16)), dtype=torch.int8 if storage == "int8" else torch.uint8 if one else torch.float32)
+    time = np.arange(n, 0, -1.0)
+    event = (np.arange(n) % 5 == 0).astype(np.int32)
+    Xd = X.cuda()
+    torch.cuda.synchronize()
+    held = P.device_bytes()
+    cox = P.Cox(Xd, time, event, n=n, max_batch=B)
+    got = P.device_bytes() - held
+    pad, rs, nslab = up(B, 16), up(n, 8192), up(n, 1024) // 1024
+    wgs, chunks = -(-p // (64 if one else 16)), rs // 8192
+    nsplit = min(chunks, max(1, -(-12288 // wgs)))
+    gemv = max(8 * max(1, min(-(-2048 // nslab), -(-p // 256))), 4 * max(1, min(-(-2048 // (up(n, 4096) // 4096)), -(-p // 64))))
+    limit = 8 * 5 * B * n + 4 * B * rs + 8 * (max(1, min(4, 512 // nslab)) * B + gemv) * n + 8 * (4 + nsplit) * B * p
+    if one:
+        limit += 3 * pad * (rs + up(p, 64)) + 8 * 5 * 256 * 256 * pad
+    assert got <= 1.05 * limit + 64 * 2**20, (got, limit)
+    cox.close()
+    assert P.device_bytes() == held
