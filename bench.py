@@ -33,8 +33,9 @@ Workloads (synthetic, seeded; they stand in for the UK Biobank genotypes):
                the torch.autograd functions.
   dense-eta-c4: the dense X~ beta behind cox_loss_grad and warm starts, for
                B = 64 vectors over the default workload's 400,000 x 500,000 FP8
-               genotypes: milliseconds per product on the matrix cores (three
-               exact limb passes) and on the FP64 vector path.
+               genotypes: milliseconds per product on the matrix cores (nine
+               limbs per coefficient, X read once per 32 vectors) and on the
+               FP64 vector path.
 
 The batched workload times K steps from beta = 0 `--repeats` times (default
 3) and reports the median run; it also measures the HBM bandwidth the same
@@ -118,7 +119,11 @@ def stored_traffic(summary: str, sources, shape="all", per="launch") -> float | 
     return float(v) if v is not None else None
 
 
-MFMA_SOURCES = ("paper_2010_16114_amd/csrc/mfma.hip", "paper_2010_16114_amd/csrc/mfma.h")
+# a kernel's sources: its file and every header of the library that it is built from
+_MFMA_HEADERS = tuple(f"paper_2010_16114_amd/csrc/{h}" for h in
+                      ("mfma.h", "mfma_plan.h", "mfma_dev.h", "device_common.h", "internal.h"))
+MFMA_SOURCES = ("paper_2010_16114_amd/csrc/mfma.hip",) + _MFMA_HEADERS
+DENSE_SOURCES = ("paper_2010_16114_amd/csrc/mfma_dense.hip",) + _MFMA_HEADERS
 GEMVT_SOURCES = ("paper_2010_16114_amd/csrc/gemvt.hip", "paper_2010_16114_amd/csrc/gemvt_dev.h",
                  "paper_2010_16114_amd/csrc/device_common.h",
                  "paper_2010_16114_amd/csrc/internal.h")
@@ -812,7 +817,8 @@ def bench_dense_eta_c4(args):
         "roofline": {"bound": "hbm", "kernel": "mfma_dense_kernel+dense_sum_kernel (all launches of a product)",
                      "achieved": launch_bytes / (kms / 1e3) / 1e9 if kms else None, "peak": HBM_PEAK_GBS,
                      "unit": "GB/s", "frac": launch_bytes / (kms / 1e3) / 1e9 / HBM_PEAK_GBS if kms else None,
-                     "traffic": None,
+                     "traffic": stored_traffic(f"mfma_dense_kernel_geno_fp8_{n}x{p}_b{B}_traffic.md", DENSE_SOURCES,
+                                               per="product"),
                      "algorithmic_bytes_per_launch": launch_bytes, "kernel_ms": kms},
         "roofline_pass": {"what": "one dense product against a single read of X",
                           "bytes": alg, "achieved": alg / (dense / 1e3) / 1e9,

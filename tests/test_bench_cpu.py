@@ -60,3 +60,21 @@ def test_column_sum_traffic_summary():
         assert v is not None and abs(v / 4.0005e9 - 1) < 0.01
     else:
         assert v is None
+
+
+def _includes(path, seen):
+    import re
+    for h in re.findall(r'^#include "([^"]+)"', open(os.path.join(ROOT, path)).read(), re.M):
+        f = os.path.join(os.path.dirname(path), h)
+        if os.path.exists(os.path.join(ROOT, f)) and f not in seen:
+            seen.add(f)
+            _includes(f, seen)
+    return seen
+
+
+@pytest.mark.parametrize("sources", ["MFMA_SOURCES", "DENSE_SOURCES", "GEMVT_SOURCES"])
+def test_source_lists_hold_every_header(sources):
+    """The hash that ties a traffic summary to its kernels covers every file of the
+    library that they are built from, device helpers in headers included."""
+    files = getattr(bench, sources)
+    assert _includes(files[0], {files[0]}) == set(files)
