@@ -376,3 +376,86 @@ def test_workspace_of_a_handle(storage, n, p, B):
     assert got <= 1.05 * limit + 64 * 2**20, (got, limit)
     cox.close()
     assert P.device_bytes() == held
+
+
+@pytest.mark.parametrize("q,B", [(16, 16), (17, 9), (17, 48), (33, 40), (64, 16), (64, 64)])
+def test_batched_risk_rows_many_covariates(q, B):
+    """Covariates beside the batched form: Z' r takes them 16 at a time and reuses its
+    LDS between the chunks, Z beta holds up to 64 x 64 coefficients there; whole, ragged
+    and last chunks, rows of 16, 48 and 64 vectors.  Losses to the batched tests'
+    1e-12; gradients of the covariates to FP32 rounding, of the SNPs to the residual's
+    22 bits as well (s_j sum_i |g_ij - mu_j| q / 2)."""
+    n, p = 1203, 21
+    d = coxsim.genotype_problem(n, p, 3, 0.4, 5000 + q, days=True)
+    cox, _ = device_problem(d, "int8", ldx=1216, max_batch=B)
+    rng = np.random.Generator(np.random.PCG64(100 * q + B))
+    Z = rng.normal(size=(q, n)).astype(np.float32)
+    cox.set_covariates(torch.from_numpy(Z).cuda())
+    beta = (rng.normal(0, 0.1, (B, p + q)) * (rng.random((B, p + q)) < 0.7)).astype(np.float32)
+    loss, grad = cox.loss_grad(torch.from_numpy(beta).cuda())
+    grad = grad.cpu().numpy()
+    Xs = (d.G.astype(np.float64) - d.mu[:, None].astype(np.float64)) * d.s[:, None].astype(np.float64)
+    full = np.concatenate([Xs, Z.astype(np.float64)])
+    M = oracle.Matrix.dense(full)
+    for b in range(B):
+        negL, gl = oracle.loss_grad(M, d.time, d.event, beta[b].astype(np.float64))
+        assert loss[b] == pytest.approx(negL, rel=1e-12), b
+        r = oracle.loglik(full.T @ beta[b].astype(np.float64), d.time, d.event)[1]
+        tol = 2.0**-23 * np.abs(gl) + 1e-12 * n
+        tol[:p] += np.abs(Xs).sum(axis=1) * np.abs(r).max() * 2.0**-23
+        assert (np.abs(grad[b] + gl) <= tol).all(), (b, np.abs(grad[b] + gl).max())
+
+
+@pytest.mark.parametrize("n,p,B,bad", [(33000, 130, 64, (5, 40)), (700, 300, 20, (0,)), (513, 63, 33, (32, 31)),
+                                       (131100, 65, 16, (15,))])
+def test_dense_product_keeps_nonfinite_vectors_apart(n, p, B, bad):
+    """A vector with a NaN or an infinity makes the call return NUMERIC; the loss and
+    gradient of every other vector, which the call has written all the same, equal those of a
+    clean call bit for bit, in each launch of 32 vectors (blocks of 256 subjects) or 16
+    (blocks of 512)."""
+    d = coxsim.genotype_problem(n, p, 4, 0.5, 8200 + n, days=True)
+    cox, _ = device_problem(d, "fp8", ldx=(n + 15) // 16 * 16, max_batch=B)
+    rng = np.random.Generator(np.random.PCG64(n + p))
+    beta = torch.from_numpy((0.1 * rng.normal(size=(B, p))).astype(np.float32)).cuda()
+    loss, grad = cox.loss_grad(beta)
+    for k, b in enumerate(bad):
+        beta[b, p // 2] = float("inf") if k else float("nan")
+    got, ggot = np.zeros(B), torch.zeros_like(beta)
+    st = P.lib().cox_loss_grad(cox._h, beta.data_ptr(), B, P._np_ptr(got), ggot.data_ptr())
+    assert st == P.ERR_NUMERIC and not np.isfinite(got[list(bad)]).any()
+    good = np.setdiff1d(np.arange(B), bad)
+    _bits(got[good], loss[good])
+    _bits(ggot.cpu().numpy()[good], grad.cpu().numpy()[good])
+
+
+@pytest.mark.parametrize("n,M", [(3000, 257), (20000, 300), (30000, 384), (45000, 385), (9000, 400), (40000, 130)])
+def test_refit_gram_tiles(n, M):
+    """The Gram terms' four kinds of 128 x 128 tiles side by side (full ones off the
+    diagonal from 257 columns on, a last column of tiles of 1 to 128 columns, those on the
+    diagonal) at two to about forty chunks of rows each, for both terms (event times
+    without ties).  At the refit's coefficients a Newton step of the same equations in
+    NumPy's FP64 is no longer than the refit tests' 1e-8, and the errors are the root of
+    that information's inverse to 1e-8."""
+    rng = np.random.Generator(np.random.PCG64(19 * n + M))
+    X = rng.normal(size=(M, n)).astype(np.float32)
+    eta = 0.3 * X[:5].sum(axis=0)
+    time = rng.exponential(np.exp(-eta))
+    event = (rng.random(n) < 0.7).astype(np.int32)
+    ldx = (n + 15) // 16 * 16
+    Xd = torch.zeros((M, ldx), dtype=torch.float32)
+    Xd[:, :n] = torch.from_numpy(X)
+    cox = P.Cox(Xd.cuda(), time, event, n=n)
+    coef, se, _, L, _, st = cox.refit(np.arange(M), gtol=1e-7)
+    assert st == P.OK
+    order = np.argsort(-time, kind="stable")
+    D, ev = X[:, order].astype(np.float64), event[order].astype(np.float64)
+    w = np.exp(coef @ D)
+    W = np.cumsum(w)
+    wc = w * np.cumsum((ev / W)[::-1])[::-1]
+    at = ev > 0
+    mean = (np.cumsum(D * w, axis=1) / W)[:, at]
+    H = (D * wc) @ D.T - mean @ mean.T
+    step = np.linalg.solve(H, D @ (ev - wc))
+    assert np.abs(step).max() <= 1e-8 * np.abs(coef).max()
+    np.testing.assert_allclose(se, np.sqrt(np.diag(np.linalg.inv(H))), rtol=1e-8)
+    assert L == pytest.approx((np.log(w[at]) - np.log(W[at])).sum(), rel=1e-11)
