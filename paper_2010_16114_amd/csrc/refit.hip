@@ -564,8 +564,9 @@ __device__ __forceinline__ double bcast(double v, int src)
                             __builtin_amdgcn_readlane(__double2loint(v), src));
 }
 
-// a / d from inv = 1 / d: the rounded product and one correction of its remainder, a
-// chain of three where the division's own is about ten
+// a / d from inv = 1 / d: the rounded product and one correction by its remainder, which an
+// fma gives exactly (the last step of Markstein's division), a chain of three where the
+// division's own is about ten
 __device__ __forceinline__ double quotient(double a, double d, double inv)
 {
     const double q = a * inv;

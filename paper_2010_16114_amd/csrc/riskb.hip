@@ -131,7 +131,7 @@ __global__ __launch_bounds__(kBT) void riskb_max_kernel(RiskArgs a)
 }
 
 // A tile's w and the tiles' and workgroups' L terms are added with their rounding
-// errors kept (two sums), and the objective adds lambda |beta|_1 before its last
+// errors kept (Knuth's TwoSum: t + err = hi + v exactly), and the objective adds lambda |beta|_1 before its last
 // rounding.  Near the top of a path the w of a step are a few values just below 1,
 // whose additions all round the same way, and -L and the penalty change by 1e3 units
 // in the last place of L, their sum by none: with plain sums the objective of the
