@@ -750,8 +750,8 @@ def bench_dense_eta_c4(args):
     pass behind cox_loss_grad, warm starts and the dense-eta ablation: one exact
     product in nine int8 limbs per coefficient, X read once per 32 vectors, against
     the FP64 vector passes of 8 vectors each (COXHIP_NO_MFMA=1).  Timed through
-    cox_loss_grad without the gradient: the dense phase, its eta-update launches,
-    and the losses of both forms."""
+    cox_loss_grad without the gradient: the dense phase, its product launches, and
+    the losses of both forms."""
     import numpy as np
     import torch
 

@@ -15,13 +15,14 @@
 //    columns.  The 64 lane partials of a column are combined by a shuffle tree
 //    and written for the split.  Splitting rows gives enough workgroups to fill
 //    the chip evenly.
-// 2. Epilogue, one thread per column: the split partials are added in a fixed
-//    order, genotype columns are standardised, g_j = s_j (sum_i g_ij r_i -
-//    mu_j sum_i r_i), and the mode's output is written: RAW (g, FP64), GRAD
-//    (-g, FP32: the gradient of -L) or PROX (the soft-threshold step on the FP64
-//    iterate with threshold sigma lambda pf_j, pf_j the column's penalty factor,
-//    the list of columns whose coefficient changed and partial sums of
-//    pf_j |beta_j| before and after, for the next eta update and the objective).
+// 2. Epilogue, one thread per column, or, for 8 vectors and more, 8 or 16 that
+//    share a column's vectors: the split partials are added in a fixed order,
+//    genotype columns are standardised, g_j = s_j (sum_i g_ij r_i - mu_j sum_i
+//    r_i), and the mode's output is written: RAW (g, FP64), GRAD (-g, FP32: the
+//    gradient of -L) or PROX (the soft-threshold step on the FP64 iterate with
+//    threshold sigma lambda pf_j, pf_j the column's penalty factor, the list of
+//    columns whose coefficient changed and partial sums of pf_j |beta_j| before
+//    and after, for the next eta update and the objective).
 //
 // Arithmetic: FP32 X is multiplied in FP64 (exact products, FP64 sums).  One-
 // byte X (allele counts) is decoded to FP32 and accumulated in FP32 within an
