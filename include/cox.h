@@ -373,7 +373,8 @@ typedef enum {
  * times every shape of X~' R on the live data (one untimed and three timed
  * launches, the median kept) and keeps the fastest; the eta update's are timed
  * the same way on the first change list seen with 1,024 columns or half of X's
- * (looked at in a fit's first update and every `poll` steps).  (The
+ * (looked at every `poll` steps, and in the updates 1, 2, 4, 8, ... of the
+ * handle's fits 1, 2, 4, 8, ...).  (The
  * environment variable COXHIP_TUNE_CACHE names a file that caches the choice;
  * COXHIP_MFMA_VARIANT and COXHIP_ETA_VARIANT force one; COXHIP_ETA_SHARES sets
  * how many workgroups the eta shapes that share blocks between workgroups use,

@@ -123,6 +123,7 @@ struct cox_ctx {
     int64_t dstride = 0;
     double *dscale = nullptr, *dmaxp = nullptr;
     int xtr_variant = -1, eta_variant = -1;  // pipeline shapes last used (-1: not tuned yet)
+    int64_t untuned_fits = 0;    // batched fits begun while eta_variant was not tuned
     float xtr_tune_ms[kMfmaVariants] = {}, eta_tune_ms[kMfmaVariants] = {};
     int xtr_by_limbs[4] = {-1, -1, -1, -1};  // X~' R shape chosen for 2 and 3 residual limbs
     float xtr_ms_by_limbs[4][kMfmaVariants] = {};
@@ -712,9 +713,9 @@ int64_t eta_tune_columns(const cox_ctx* c) { return std::min<int64_t>(1024, (c->
 // The eta update's pipeline shape: forced, cached, or timed once per context on
 // these arguments (writing into scratch, since the update is in place) when the
 // change list is long enough.  The list is looked at where `look` is set (each look
-// waits for the stream); until then a shape that needs no timing serves: 10, the
-// fastest at 400,000 x 500,000 x 64 (23.1 ms; the others 23.3 to 33.6), or 0
-// where its 32-bit column offsets do not reach.
+// waits for the stream); until then shape 0 serves, the fastest on short lists or
+// near it: 130 columns, 16 vectors, 100,003 subjects 15.3 us (shape 10, the fastest on
+// long ones, 28.3); 160 columns, 64 vectors, 400,000 subjects 128 us (159).
 cox_status pick_eta_variant(cox_ctx* c, MfmaEtaArgs* m, bool look)
 {
     const int forced = forced_variant("COXHIP_ETA_VARIANT", kMfmaEtaVariants);
@@ -736,7 +737,7 @@ cox_status pick_eta_variant(cox_ctx* c, MfmaEtaArgs* m, bool look)
             tune_cache_store(key, c->eta_variant, c->eta_tune_ms, kMfmaEtaVariants);
         }
     }
-    m->variant = c->eta_variant >= 0 ? c->eta_variant : (m->ldx < (int64_t(1) << 32) ? 10 : 0);
+    m->variant = std::max(c->eta_variant, 0);
     return COX_OK;
 }
 
@@ -1580,6 +1581,7 @@ cox_status cox_fit_path(cox_ctx* c, const double* lambdas, int32_t B, const cox_
     // a resumed fit starts where the last one ended: after the risk-set pass of
     // its last step, with that step's proximal update still to take
     const int it0 = resume ? c->fit_max_iter : 0;
+    if (mfma && o.eta_mode == 0 && c->eta_variant < 0) ++c->untuned_fits;
     for (int it = it0; it <= o.max_iter && !o.persistent; ++it) {
         const bool first_resumed = resume && it == it0;
         if (it > 0 && !first_resumed) {
@@ -1590,8 +1592,11 @@ cox_status cox_fit_path(cox_ctx* c, const double* lambdas, int32_t B, const cox_
                                          c->dscale, c->stream),
                        "quantise eta update");
                 MfmaEtaArgs m = mfma_eta_args(c, c->sel, c->nsel, B, c->active);
-                // looked at in a call's first update and where the last step's poll waited already
-                STCHK(pick_eta_variant(c, &m, it == it0 + 1 || it % poll == 0));
+                // looked at where the last step's poll waited already, and in updates 1, 2, 4, 8, ...
+                // of fits 1, 2, 4, 8, ..., so that short lists do not cost every call a wait
+                // (in each call's first update: 45 us of 5.5 ms at 100,003 x 20,001 x 16, 10 steps)
+                auto pow2 = [](int64_t v) { return v > 0 && (v & (v - 1)) == 0; };
+                STCHK(pick_eta_variant(c, &m, it % poll == 0 || (pow2(it - it0) && pow2(c->untuned_fits))));
                 tmark(c, COX_PHASE_ETA_KERNEL);
                 HIPCHK(launch_mfma_eta(m, c->stream), "eta update on matrix cores");
                 tmark(c, COX_PHASE_ETA_KERNEL);
