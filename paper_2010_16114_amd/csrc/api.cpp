@@ -104,6 +104,9 @@ struct cox_ctx {
     // matrix-core passes (eta update, dense product, the last round of X~' R)
     double* part = nullptr;
     int64_t part_words = 0;
+    // of it, what the plans of the matrix-core passes may take: columns over all shares of
+    // a split X~' R, per vector, and words of a split dense product
+    int64_t tail_cols = 0, dense_words = 0;
     int64_t tile = 0;
     int ntile = 0, nfin = 0;
     double* part_xtr = nullptr;  // [nsplit][Bmax][p] split partials of X' r
@@ -754,7 +757,7 @@ cox_status dense_eta_mfma(cox_ctx* c, const double* coef, int B)
            "quantise coefficients");
     MfmaDenseArgs m{c->x.X,    c->x.xt,   c->n,   c->p, c->x.ldx,  c->climbs,
                     c->dstride, bpad,     B,      c->dscale, c->nonfin, c->eta,
-                    reinterpret_cast<long long*>(c->part), c->part_words, c->ncu};
+                    reinterpret_cast<long long*>(c->part), c->dense_words, c->ncu};
     tmark(c, COX_PHASE_ETA_KERNEL);
     HIPCHK(launch_mfma_dense(m, c->stream), "dense X beta on matrix cores");
     tmark(c, COX_PHASE_ETA_KERNEL);
@@ -879,7 +882,7 @@ cox_status run_gemvt(cox_ctx* c, GemvtArgs g, int B, bool rows, int rlimbs = 3)
         MfmaArgs m{c->x.X,   c->x.xt, c->n, c->p,      c->x.ldx,     c->limbs, c->rstride,
                    bpad,     rlimbs,  B,    c->qscale, c->part_xtr, 0};
         m.tail = reinterpret_cast<long long*>(c->part);
-        m.tail_cols = c->part_words / B;
+        m.tail_cols = c->tail_cols;
         m.ncu = c->ncu;
         int& chosen = c->xtr_by_limbs[rlimbs];
         const int forced = forced_variant("COXHIP_MFMA_VARIANT", kMfmaVariants);
@@ -1160,12 +1163,15 @@ cox_status cox_setup(cox_ctx** out, const cox_matrix* X, const double* time, con
     if (mfma_able && c->ncu > 0) {
         // the eta update's: [ncu][2][256][Bmax16]; the dense product's: up to 12 M words; X~' R's:
         // up to 6 shares of a full round of columns, 16 of a small one; at least the shares
-        // that int32 sums need
+        // that int32 sums need.  The plans keep to these though the buffer may hold more: their
+        // cost rule leaves out that shares of a block read different limb rows at once
+        // (400,000 x 500,000 x 64: 38.6 ms in elevenths, 38.2 in the thirds taken within these)
         const int64_t kn = min_shares((n + 127) / 128, 128), kp = min_shares((p + 63) / 64, 64);
         const int64_t bp = round_up(max_batch, 16), rows = round_up(n, 512) * 3 * 32;
-        const int64_t tail = std::max(std::min((int64_t)6 * c->ncu * 256, kMaxSplit * p), kn > 1 ? kn * p : 0);
-        c->part_words = std::max({c->part_words, (int64_t)c->ncu * 2 * bp * 256, max_batch * tail,
-                                  std::min(int64_t(12) << 20, kMaxSplit * rows), kp > 1 ? kp * rows : 0});
+        c->tail_cols = std::max(std::min((int64_t)6 * c->ncu * 256, kMaxSplit * p), kn > 1 ? kn * p : 0);
+        c->dense_words = std::max({(int64_t)c->ncu * 2 * bp * 256, std::min(int64_t(12) << 20, kMaxSplit * rows),
+                                   kp > 1 ? kp * rows : 0});
+        c->part_words = std::max({c->part_words, c->dense_words, max_batch * c->tail_cols});
     }
     // the eta update's limbs stand behind dcoef, the dense product's over both (no call
     // needs the change of its last step after one)
