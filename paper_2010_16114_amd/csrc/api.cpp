@@ -1161,16 +1161,10 @@ cox_status cox_setup(cox_ctx** out, const cox_matrix* X, const double* time, con
     c->part_words = std::max({gemv_words, (int64_t)c->ncg * std::min(max_batch, kGroup) * n,
                               std::min(c->ncg * Bn, std::max(few * Bn + gemv_words, kUpdRoom))});
     if (mfma_able && c->ncu > 0) {
-        // the eta update's: [ncu][2][256][Bmax16]; the dense product's: up to 12 M words; X~' R's:
-        // up to 6 shares of a full round of columns, 16 of a small one; at least the shares
-        // that int32 sums need.  The plans keep to these though the buffer may hold more: their
-        // cost rule leaves out that shares of a block read different limb rows at once
-        // (400,000 x 500,000 x 64: 38.6 ms in elevenths, 38.2 in the thirds taken within these)
-        const int64_t kn = min_shares((n + 127) / 128, 128), kp = min_shares((p + 63) / 64, 64);
-        const int64_t bp = round_up(max_batch, 16), rows = round_up(n, 512) * 3 * 32;
-        c->tail_cols = std::max(std::min((int64_t)6 * c->ncu * 256, kMaxSplit * p), kn > 1 ? kn * p : 0);
-        c->dense_words = std::max({(int64_t)c->ncu * 2 * bp * 256, std::min(int64_t(12) << 20, kMaxSplit * rows),
-                                   kp > 1 ? kp * rows : 0});
+        // the eta update's: [ncu][2][256][Bmax16]; the other two's: what their plans may take
+        const int64_t eta_words = (int64_t)c->ncu * 2 * round_up(max_batch, 16) * 256;
+        c->tail_cols = xtr_room(n, p, c->ncu);
+        c->dense_words = std::max(eta_words, dense_room(n, p));
         c->part_words = std::max({c->part_words, c->dense_words, max_batch * c->tail_cols});
     }
     // the eta update's limbs stand behind dcoef, the dense product's over both (no call

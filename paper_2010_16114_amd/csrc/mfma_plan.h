@@ -78,4 +78,21 @@ inline int xtr_split(int64_t ntail, int64_t nstage, int64_t slots, int64_t ptail
     return best;
 }
 
+// The room the two plans are given in the handle's buffer of partial sums, whatever more it
+// holds: columns over all shares of X~' R per vector, up to 6 shares of a full round of
+// columns and 16 of a small problem's, and words of the dense product's sums, up to 12 M;
+// at least the shares that int32 sums need.  X~' R's cost rule leaves out that shares of
+// a block read different limb rows at once, so room for more costs time (400,000 x
+// 500,000 x 64: 38.6 ms in elevenths, 38.2 in the thirds taken within this).
+inline int64_t xtr_room(int64_t n, int64_t p, int64_t ncu)
+{
+    const int64_t k = min_shares((n + 127) / 128, 128);
+    return std::max(std::min(6 * ncu * 256, kMaxSplit * p), k > 1 ? k * p : 0);
+}
+inline int64_t dense_room(int64_t n, int64_t p)
+{
+    const int64_t k = min_shares((p + 63) / 64, 64), rows = (n + 511) / 512 * 512 * 3 * 32;
+    return std::max(std::min(int64_t(12) << 20, kMaxSplit * rows), k > 1 ? k * rows : 0);
+}
+
 }  // namespace cox

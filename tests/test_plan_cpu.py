@@ -23,6 +23,8 @@ int xtr(int64_t ntail, int64_t nstage, int64_t slots, int64_t ptail, int B, int6
 }
 int64_t max_sum() { return kMfmaMaxSum; }
 int64_t shares(int64_t nstage, int64_t stage) { return min_shares(nstage, stage); }
+int64_t xroom(int64_t n, int64_t p, int64_t ncu) { return xtr_room(n, p, ncu); }
+int64_t droom(int64_t n, int64_t p) { return dense_room(n, p); }
 }
 """
 
@@ -38,7 +40,9 @@ def plan(tmp_path_factory):
     i64 = ctypes.c_int64
     lib.xtr.argtypes = [i64, i64, i64, i64, ctypes.c_int, i64]
     lib.shares.argtypes = [i64, i64]
-    lib.max_sum.restype = lib.shares.restype = i64
+    lib.xroom.argtypes = [i64, i64, i64]
+    lib.droom.argtypes = [i64, i64]
+    lib.max_sum.restype = lib.shares.restype = lib.xroom.restype = lib.droom.restype = i64
     return lib
 
 
@@ -102,3 +106,15 @@ def test_long_sums_are_split(plan, terms):
     assert ks >= 1 and -(-nstage // ks) * 128 <= m
     if k > 1:
         assert plan.xtr(ntail, nstage, 256, other, 64, 0) == 0
+
+
+@pytest.mark.parametrize("n,p,shares", [(400_000, 500_000, 3), (400_000, 62_500, 1), (200_000, 50_000, 5),
+                                        (3001, 701, 12)])
+def test_room_of_the_plans(plan, n, p, shares):
+    """Within the room that a handle gives it X~' R splits its last round as it was
+    measured best; the dense product always finds room to run."""
+    nblk, nstage = -(-p // 256), -(-n // 128)
+    ntail = nblk % 256
+    assert plan.xtr(ntail, nstage, 256, p - (nblk - ntail) * 256, 64, plan.xroom(n, p, 256)) == shares
+    for sub, words in ((256, 256 * 96), (512, 512 * 48)):
+        assert _dense(plan, -(-n // sub), -(-p // 64), 256, words, plan.droom(n, p))[1] >= 1
