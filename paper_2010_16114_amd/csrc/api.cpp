@@ -1603,10 +1603,9 @@ cox_status cox_fit_path(cox_ctx* c, const double* lambdas, int32_t B, const cox_
                 tmark(c, COX_PHASE_ETA);
             } else if (o.eta_mode == 0) {
                 tmark(c, COX_PHASE_ETA);
-                for (int b0 = 0; b0 < B; b0 += kGroup)
-                    HIPCHK(launch_eta_update(c->x, c->sel, c->nsel, c->dcoef, b0, std::min(kGroup, B - b0),
-                                             c->part, cstride, ra.ncg, c->active, c->stream),
-                           "eta update");
+                HIPCHK(launch_eta_update(c->x, c->sel, c->nsel, c->dcoef, B, c->part, cstride, ra.ncg, c->active,
+                                         c->stream),
+                       "eta update");
                 tmark(c, COX_PHASE_ETA);
             } else {
                 HIPCHK(launch_scale_coef(c->beta64, geno_scale(c), c->coef, c->p, B, c->stream), "coefficients");

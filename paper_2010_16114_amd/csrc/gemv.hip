@@ -178,6 +178,8 @@ __global__ __launch_bounds__(kT) void gemv16_kernel(XDesc x, const double* __res
     }
 }
 
+// Workgroups: row slab, column group, NB vectors (of several groups of NB only where
+// each is full).
 template <int XT, int NB, bool VEC>
 __global__ __launch_bounds__(kT) void eta_update_kernel(XDesc x, const int32_t* __restrict__ sel,
                                                         const int32_t* __restrict__ nsel_p,
@@ -186,8 +188,8 @@ __global__ __launch_bounds__(kT) void eta_update_kernel(XDesc x, const int32_t* 
                                                         const int32_t* __restrict__ active)
 {
     __shared__ UpdLds<NB> lds;
-    eta_update_blk<XT, NB, VEC>(x, sel, nsel_p, dcoef, b0, nb, part, cstride, ncg, active, blockIdx.x, blockIdx.y,
-                                lds);
+    eta_update_blk<XT, NB, VEC>(x, sel, nsel_p, dcoef, b0 + NB * blockIdx.z, nb, part, cstride, ncg, active,
+                                blockIdx.x, blockIdx.y, lds);
 }
 
 // One workgroup per chunk of 1024 blocks of columns.  Each adds up the counts
@@ -247,9 +249,9 @@ hipError_t gemv_x(const XDesc& x, const double* coef, int b0, int nb, double* pa
 
 template <int XT, int NB>
 hipError_t upd_t(const XDesc& x, const int32_t* sel, const int32_t* nsel, const double* dcoef, int b0, int nb,
-                 double* part, int64_t cstride, int ncg, const int32_t* active, hipStream_t s)
+                 int groups, double* part, int64_t cstride, int ncg, const int32_t* active, hipStream_t s)
 {
-    const dim3 grid((unsigned)((x.n + kRows - 1) / kRows), (unsigned)ncg);
+    const dim3 grid((unsigned)((x.n + kRows - 1) / kRows), (unsigned)ncg, (unsigned)groups);
     const bool vec = x.xt == XT_F32 ? x.vec16 : x.vec4;
     if (vec)
         hipLaunchKernelGGL((eta_update_kernel<XT, NB, true>), grid, dim3(kT), 0, s, x, sel, nsel, dcoef, b0, nb,
@@ -262,12 +264,12 @@ hipError_t upd_t(const XDesc& x, const int32_t* sel, const int32_t* nsel, const 
 
 template <int XT>
 hipError_t upd_x(const XDesc& x, const int32_t* sel, const int32_t* nsel, const double* dcoef, int b0, int nb,
-                 double* part, int64_t cstride, int ncg, const int32_t* active, hipStream_t s)
+                 int groups, double* part, int64_t cstride, int ncg, const int32_t* active, hipStream_t s)
 {
-    if (nb <= 1) return upd_t<XT, 1>(x, sel, nsel, dcoef, b0, nb, part, cstride, ncg, active, s);
-    if (nb <= 2) return upd_t<XT, 2>(x, sel, nsel, dcoef, b0, nb, part, cstride, ncg, active, s);
-    if (nb <= 4) return upd_t<XT, 4>(x, sel, nsel, dcoef, b0, nb, part, cstride, ncg, active, s);
-    return upd_t<XT, 8>(x, sel, nsel, dcoef, b0, nb, part, cstride, ncg, active, s);
+    if (nb <= 1) return upd_t<XT, 1>(x, sel, nsel, dcoef, b0, nb, groups, part, cstride, ncg, active, s);
+    if (nb <= 2) return upd_t<XT, 2>(x, sel, nsel, dcoef, b0, nb, groups, part, cstride, ncg, active, s);
+    if (nb <= 4) return upd_t<XT, 4>(x, sel, nsel, dcoef, b0, nb, groups, part, cstride, ncg, active, s);
+    return upd_t<XT, 8>(x, sel, nsel, dcoef, b0, nb, groups, part, cstride, ncg, active, s);
 }
 
 }  // namespace
@@ -312,16 +314,24 @@ hipError_t launch_gemv(const XDesc& x, const double* coef, int b0, int nb, doubl
     return hipGetLastError();
 }
 
-hipError_t launch_eta_update(const XDesc& x, const int32_t* sel, const int32_t* nsel, const double* dcoef, int b0,
-                             int nb, double* part, int64_t part_cstride, int ncg, const int32_t* active,
-                             hipStream_t s)
+// Every full group of 8 vectors in one launch, then the rest: with a launch to each, the
+// partial sums of 64 vectors leave room for 6 column groups at 20,000 subjects, 120
+// workgroups a launch (3.34 ms an update of 8,648 columns, 1.44 now).
+hipError_t launch_eta_update(const XDesc& x, const int32_t* sel, const int32_t* nsel, const double* dcoef, int B,
+                             double* part, int64_t part_cstride, int ncg, const int32_t* active, hipStream_t s)
 {
-    if (nb < 1 || nb > 8 || ncg < 1) return hipErrorInvalidValue;
-    switch (x.xt) {
-    case XT_F32: return upd_x<XT_F32>(x, sel, nsel, dcoef, b0, nb, part, part_cstride, ncg, active, s);
-    case XT_FP8: return upd_x<XT_FP8>(x, sel, nsel, dcoef, b0, nb, part, part_cstride, ncg, active, s);
-    default: return upd_x<XT_I8>(x, sel, nsel, dcoef, b0, nb, part, part_cstride, ncg, active, s);
-    }
+    if (B < 1 || ncg < 1) return hipErrorInvalidValue;
+    auto group = [&](int b0, int nb, int groups) {
+        switch (x.xt) {
+        case XT_F32: return upd_x<XT_F32>(x, sel, nsel, dcoef, b0, nb, groups, part, part_cstride, ncg, active, s);
+        case XT_FP8: return upd_x<XT_FP8>(x, sel, nsel, dcoef, b0, nb, groups, part, part_cstride, ncg, active, s);
+        default: return upd_x<XT_I8>(x, sel, nsel, dcoef, b0, nb, groups, part, part_cstride, ncg, active, s);
+        }
+    };
+    hipError_t e = hipSuccess;
+    if (B >= 8) e = group(0, 8, B / 8);
+    if (e == hipSuccess && B % 8) e = group(B / 8 * 8, B % 8, 1);
+    return e;
 }
 
 hipError_t launch_compact(const int32_t* chg_cnt, const int32_t* chg_idx, int nblk, int32_t* sel, int32_t* nsel,

@@ -177,10 +177,9 @@ hipError_t launch_gemvt(const GemvtArgs& a, hipStream_t s);       // sums, then 
 hipError_t launch_gemvt_sums(const GemvtArgs& a, hipStream_t s);  // the row-split column sums alone
 // the epilogue alone, on column sums already in a.part (nb may exceed 8)
 hipError_t launch_gemvt_epilogue(const GemvtArgs& a, hipStream_t s);
-// eta partials: part[cg][b][i] for b in [b0, b0+nb) from the compacted change list
-hipError_t launch_eta_update(const XDesc& x, const int32_t* sel, const int32_t* nsel, const double* dcoef,
-                             int b0, int nb, double* part, int64_t part_cstride, int ncg,
-                             const int32_t* active, hipStream_t s);
+// eta partials: part[cg][b][i] for b < B from the compacted change list
+hipError_t launch_eta_update(const XDesc& x, const int32_t* sel, const int32_t* nsel, const double* dcoef, int B,
+                             double* part, int64_t part_cstride, int ncg, const int32_t* active, hipStream_t s);
 // column blocks of the dense pass over one-byte X with 16-byte runs (the
 // partial buffer must hold gemv16_blocks(n, p) * 4 * n doubles)
 int gemv16_blocks(int64_t n, int64_t p);

@@ -459,3 +459,35 @@ def test_refit_gram_tiles(n, M):
     assert np.abs(step).max() <= 1e-8 * np.abs(coef).max()
     np.testing.assert_allclose(se, np.sqrt(np.diag(np.linalg.inv(H))), rtol=1e-8)
     assert L == pytest.approx((np.log(w[at]) - np.log(W[at])).sum(), rel=1e-11)
+
+
+@pytest.mark.parametrize("storage,B", [("f32", 8), ("f32", 9), ("f32", 16), ("f32", 23), ("f32", 64), ("int8", 20)])
+def test_vector_eta_update_groups(storage, B):
+    """The vector form's eta update takes every full group of 8 vectors in one launch, a rest
+    of 1 to 7 in another; with tolerances that stop vectors at different steps, groups whose
+    vectors have all stopped among them.  Each vector's fit is its own: it matches the same
+    fit alone, whose FP64 sums differ in their order only (1e-11 of the largest
+    coefficient over the steps), up to the FP32 rounding of the result."""
+    n, p = 1500, 300
+    rng = np.random.Generator(np.random.PCG64(900 + B))
+    if storage == "f32":
+        X = rng.normal(size=(p, n)).astype(np.float32)
+    else:
+        X = rng.integers(-3, 4, size=(p, n)).astype(np.int8)  # not allele counts: the vector form
+    time = rng.exponential(np.exp(-0.2 * X[:4].sum(axis=0).astype(np.float64)))
+    event = (rng.random(n) < 0.6).astype(np.int32)
+    xtype = P.X_F32 if storage == "f32" else P.X_INT8
+    Xd = torch.from_numpy(X).cuda()
+    cox = P.Cox(Xd, time, event, xtype=xtype, n=n, max_batch=B)
+    one = P.Cox(Xd, time, event, xtype=xtype, n=n, max_batch=1)
+    step = 1.0 / (2.0 * cox.opnorm2()[0])
+    lams = coxsim.lambda_grid(cox.lambda_max(), B, 0.05)
+    beta, iters, obj, _ = cox.fit_path(lams, max_iter=40, tol=1e-4, lag=2, step=step)
+    beta = beta.cpu().numpy()
+    assert len(set(np.asarray(iters).tolist())) > 1 or B < 16
+    for b in range(B):
+        alone, it, f, _ = one.fit_path([lams[b]], max_iter=40, tol=1e-4, lag=2, step=step)
+        alone = alone.cpu().numpy()[0]
+        assert it[0] == iters[b], b
+        assert (np.abs(beta[b] - alone) <= 2.0**-23 * np.abs(alone) + 1e-11 * np.abs(alone).max()).all(), b
+        assert obj[b] == pytest.approx(f[0], rel=1e-12), b
