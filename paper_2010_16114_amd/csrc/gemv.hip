@@ -189,7 +189,7 @@ __global__ __launch_bounds__(kT) void eta_update_kernel(XDesc x, const int32_t* 
 {
     __shared__ UpdLds<NB> lds;
     eta_update_blk<XT, NB, VEC>(x, sel, nsel_p, dcoef, b0 + NB * blockIdx.z, nb, part, cstride, ncg, active,
-                                blockIdx.x, blockIdx.y, lds);
+                                blockIdx.x, blockIdx.y, &lds);
 }
 
 // One workgroup per chunk of 1024 blocks of columns.  Each adds up the counts

@@ -63,12 +63,14 @@ struct UpdLds {
 // The group's column indices and coefficients come into LDS first, so that the
 // loads of X hang on nothing but LDS and kUpdAhead of them are in flight (the
 // change list, then X and the coefficients, one after another for every four
-// columns took 17 us for a 1,000 x 2,000 problem).
-template <int XT, int NB, bool VEC>
+// columns took 17 us for a 1,000 x 2,000 problem).  Without a stage (lds not read) the
+// lists come from memory, four columns at a time, every sum the same: for the persistent
+// kernel's instances that spill with it.
+template <int XT, int NB, bool VEC, bool STAGED = true>
 __device__ __forceinline__ void eta_update_blk(const XDesc& x, const int32_t* __restrict__ sel,
                                                const int32_t* __restrict__ nsel_p, const double* __restrict__ dcoef,
                                                int b0, int nb, double* __restrict__ part, int64_t cstride, int ncg,
-                                               const int32_t* __restrict__ active, int bx, int cg, UpdLds<NB>& lds)
+                                               const int32_t* __restrict__ active, int bx, int cg, UpdLds<NB>* lds)
 {
     const int nsel = *nsel_p;
     if (nsel == 0) return;
@@ -88,37 +90,63 @@ __device__ __forceinline__ void eta_update_blk(const XDesc& x, const int32_t* __
 #pragma unroll
         for (int e = 0; e < 4; ++e) acc[b][e] = 0.0;
     const int64_t r0 = slab0 + (int64_t)threadIdx.x * 4;
-    for (int qs = q0; qs < q1; qs += kUpdStage) {
-        const int m = min(kUpdStage, q1 - qs);
-        __syncthreads();
-        for (int t = threadIdx.x; t < m * NB; t += kT) {
-            const int b = t / m, q = t % m;
-            const int32_t j = sel[qs + q];
-            if (b == 0) lds.sel[q] = j;
-            lds.d[b][q] = b < nb ? dcoef[(int64_t)(b0 + b) * p + j] : 0.0;
+    auto load = [&](int64_t j, float (&v)[4]) {
+        if (VEC) {
+            load_rows4<XT, true>(x, j, r0, n, v);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int64_t r = row_of<false>(slab0, e);
+                v[e] = r < n ? load_x1<XT>(x.X, j * x.ldx + r) : 0.f;
+            }
         }
-        __syncthreads();
-        for (int q = 0; q < m; q += kUpdAhead) {
-            float xv[kUpdAhead][4];
+    };
+    if constexpr (STAGED) {
+        for (int qs = q0; qs < q1; qs += kUpdStage) {
+            const int m = min(kUpdStage, q1 - qs);
+            __syncthreads();
+            for (int t = threadIdx.x; t < m * NB; t += kT) {
+                const int b = t / m, q = t % m;
+                const int32_t j = sel[qs + q];
+                if (b == 0) lds->sel[q] = j;
+                lds->d[b][q] = b < nb ? dcoef[(int64_t)(b0 + b) * p + j] : 0.0;
+            }
+            __syncthreads();
+            for (int q = 0; q < m; q += kUpdAhead) {
+                float xv[kUpdAhead][4];
 #pragma unroll
-            for (int u = 0; u < kUpdAhead; ++u) {
-                const int64_t j = lds.sel[min(q + u, m - 1)];
-                if (VEC) {
-                    load_rows4<XT, true>(x, j, r0, n, xv[u]);
-                } else {
+                for (int u = 0; u < kUpdAhead; ++u) {
+                    const int64_t j = lds->sel[min(q + u, m - 1)];
+                    load(j, xv[u]);
+                }
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int64_t r = row_of<false>(slab0, e);
-                        xv[u][e] = r < n ? load_x1<XT>(x.X, j * x.ldx + r) : 0.f;
+                for (int u = 0; u < kUpdAhead; ++u) {
+                    if (q + u >= m) break;
+#pragma unroll
+                    for (int b = 0; b < NB; ++b) {
+                        const double d = lds->d[b][q + u];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[b][e] = fma((double)xv[u][e], d, acc[b][e]);
                     }
                 }
             }
+        }
+    } else {
+        for (int q = q0; q < q1; q += 4) {
+            float xv[4][4];
+            int64_t jj[4];
 #pragma unroll
-            for (int u = 0; u < kUpdAhead; ++u) {
-                if (q + u >= m) break;
+            for (int u = 0; u < 4; ++u) {
+                jj[u] = sel[min(q + u, q1 - 1)];
+                load(jj[u], xv[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (q + u >= q1) break;
 #pragma unroll
                 for (int b = 0; b < NB; ++b) {
-                    const double d = lds.d[b][q + u];
+                    if (b >= nb) break;
+                    const double d = dcoef[(int64_t)(b0 + b) * p + jj[u]];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) acc[b][e] = fma((double)xv[u][e], d, acc[b][e]);
                 }

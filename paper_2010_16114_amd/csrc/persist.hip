@@ -96,6 +96,14 @@ constexpr int persist_waves()
     else return NB == 1 || NB == 4 ? 3 : 2;
 }
 
+// Whether the eta update stages its change list.  All phases share one set of registers,
+// and with the stage some instances spill in the other phases' loops.  Steps with and
+// without it: FP32, 1 vector 1.53 and 1.23 ms (20,000 x 50,000; 242 and 253 us at 1,000 x
+// 2,000), 20,000 x 20,000 2 vectors 850 and 736 us, 4 777 and 803, 8 1,144 and 1,089;
+// one-byte, 40,000 x 40,000, 1 vector 637 and 644 us, 2 599 and 640, 4 1,265 and 1,413.
+template <int XT, int NB>
+constexpr bool persist_stage() { return XT != XT_F32 || NB == 4; }
+
 template <int XT, int NB>
 __global__ __launch_bounds__(kPT, (persist_waves<XT, NB>())) void fit_persistent_kernel(PersistArgs a, Barrier br)
 {
@@ -123,9 +131,9 @@ __global__ __launch_bounds__(kPT, (persist_waves<XT, NB>())) void fit_persistent
         if (it > 0) {
             // eta partials of the columns that changed in the last step
             for (int64_t v = blockIdx.x; v < slabs * a.ncg; v += G) {
-                gemvdev::eta_update_blk<XT, NB, true>(g.x, a.sel, a.nsel, a.dcoef, 0, B, a.part_upd, a.cstride,
-                                                      a.ncg, ra.ctl.active, (int)(v % slabs), (int)(v / slabs),
-                                                      *reinterpret_cast<gemvdev::UpdLds<NB>*>(big));
+                gemvdev::eta_update_blk<XT, NB, true, persist_stage<XT, NB>()>(
+                    g.x, a.sel, a.nsel, a.dcoef, 0, B, a.part_upd, a.cstride, a.ncg, ra.ctl.active, (int)(v % slabs),
+                    (int)(v / slabs), reinterpret_cast<gemvdev::UpdLds<NB>*>(big));
                 __syncthreads();
             }
             if (grid_barrier(br, nwg, &s_flag)) return;
